@@ -150,6 +150,9 @@ int make_geom2d(const ph_geom2d *g, bool fan, Geom2D *o)
     o->n_proj = g->n_proj;
     o->sid = fan ? g->sid : 0.0f;
     o->sdd = fan ? g->sdd : 0.0f;
+    const double ru = (fan ? (double)g->sdd : 1.0) / (double)g->det_spacing;
+    o->ru = (float)ru;
+    o->ru_lo = (float)(ru - (double)o->ru);
     o->curved = fan && g->fan_detector == 1 ? 1 : 0;
     o->step = (float)default_step(g->step_mm, std::fmin(g->vol_spacing[0], g->vol_spacing[1]));
     o->dbeta = (float)((double)g->angular_range / g->n_proj);

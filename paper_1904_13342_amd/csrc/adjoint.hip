@@ -12,9 +12,9 @@
 // accumulator (below).
 //
 // B^T in 2D, the transpose of the voxel-driven distance-weighted
-// back-projector, scatters each pixel's value times dbeta * weight into the
-// two detector bins of its linear footprint with float atomics (FP32 output);
-// the 3D B^T sits beside the back-projector it mirrors.
+// back-projector, gathers per detector bin over the pixels whose linear
+// footprint covers it (FP32 output); the 3D B^T sits beside the back-projector
+// it mirrors.
 #include "device_util.h"
 
 namespace ph {
@@ -358,40 +358,183 @@ __global__ void fill_zero_kernel(float *__restrict__ p, size_t n)
         p[i] = 0.0f;
 }
 
-template <typename TI, bool FAN>
-__global__ void __launch_bounds__(256) bpT2d_kernel(Geom2D g, const float2 *__restrict__ views,
-                                                    const TI *__restrict__ img, float *__restrict__ sino)
+// Gather over strips.  Strip j of a view holds the pixels whose detector
+// coordinate su lies in [j, j + 1); each adds (1 - t) of its value to bin j
+// and t to bin j + 1 (t = su - j).  A lane owns a strip and walks the image
+// along the axis its strip crosses most slowly: one row (or column) of pixels
+// at a time, the few candidates between the strip's two edge rays, each
+// tested against the strip with the very coordinate the back-projector uses.
+// Lane l then stores its own (1 - t) sum plus lane l - 1's t sum, so a wave
+// of 64 strips writes 63 bins, every bin once: no atomics, no zero fill, and
+// the same bits on every run.  The R waves of a workgroup share a wave's
+// strips, each taking every R-th row, and meet in LDS.
+//
+// The scatter this replaces (two global float atomics per pixel and view,
+// which neighbouring pixels aim at the same few bins) was bound by the
+// atomics: 13.0 ms for 8 x 256^2 and 360 parallel views of 363 bins.
+struct StripEdge {
+    float a, b;   // secondary index of the edge ray in row p of the walk: a + b p
+};
+
+// A point and the direction, in pixel indices, of the ray through detector
+// coordinate u (bins) in a view with central ray c.
+template <bool FAN>
+__device__ __forceinline__ void edge_ray(const Geom2D &g, float2 c, double u, double &px, double &py, double &dx,
+                                         double &dy)
 {
-    const int ix = blockIdx.x * 16 + (threadIdx.x & 15);
-    const int iy = blockIdx.y * 16 + (threadIdx.x >> 4);
-    const int b = blockIdx.z;
-    if (ix >= g.nx || iy >= g.ny)
-        return;
-    const float val = load_f32(img + ((size_t)b * g.ny + iy) * g.nx + ix);
-    if (val == 0.0f)
-        return;
-    float *sb = sino + (size_t)b * g.n_proj * g.nu;
-    const float x = fmaf((float)ix, g.sx, g.ox), y = fmaf((float)iy, g.sy, g.oy);
-    const float rdu = 1.0f / g.du;
-    for (int k = 0; k < g.n_proj; ++k) {
-        const float2 c = views[k];
-        int j;
-        float t, wt;
-        if (!FAN) {
-            const float su = fmaf(-x * c.y + y * c.x, rdu, g.cu);
-            const float fu = floorf(su);
-            j = (int)fu;
-            t = su - fu;
-            wt = 1.0f;
-        } else {
-            fan2d_point(g, c, ix, iy, j, t, wt);
-        }
-        const float v = g.dbeta * wt * val;
-        if (j >= 0 && j < g.nu)
-            unsafeAtomicAdd(sb + (size_t)k * g.nu + j, v * (1.0f - t));
-        if (j + 1 >= 0 && j + 1 < g.nu)
-            unsafeAtomicAdd(sb + (size_t)k * g.nu + j + 1, v * t);
+    const double U = (u - (double)g.cu) * (double)g.du, cx = c.x, cy = c.y;
+    if (!FAN) {
+        px = -U * cy;
+        py = U * cx;
+        dx = cx;
+        dy = cy;
+    } else {
+        px = -(double)g.sid * cx;
+        py = -(double)g.sid * cy;
+        double cg = (double)g.sdd, sg = U;
+        if (g.curved)
+            sincos(U / (double)g.sdd, &sg, &cg);
+        dx = cg * cx - sg * cy;
+        dy = cg * cy + sg * cx;
     }
+    // index units
+    px = (px - (double)g.ox) / (double)g.sx;
+    py = (py - (double)g.oy) / (double)g.sy;
+    dx /= (double)g.sx;
+    dy /= (double)g.sy;
+}
+
+constexpr int STRIP_ROWS = 4;   // rows whose candidates are loaded together
+
+// Called by whole waves; `used` is cleared for lanes without a strip.
+template <typename TI, bool FAN, int AX>
+__device__ __forceinline__ void strip_walk(const Geom2D &g, float2 c, const TI *im, int j, bool used, bool bounded,
+                                           StripEdge e0, StripEdge e1, int first, int stride, float &a0, float &a1)
+{
+    const int np = AX == 0 ? g.ny : g.nx, nq = AX == 0 ? g.nx : g.ny;
+    // widest strip over the walk (pixels), and a margin for the rounding of
+    // the edge lines and of the coordinates tested below
+    const float w0 = fabsf(e1.a - e0.a), w1 = fabsf(fmaf(e1.b - e0.b, (float)(np - 1), e1.a - e0.a));
+    const float wide = fmaxf(w0, w1), eps = fmaf(0.02f, wide, 0.02f);
+    float lo = 0.0f, hi = (float)(np - 1);
+    if (bounded) {
+        // rows where the first edge is within a strip's width of the image
+        const float qa = -1.0f - wide - eps, qb = (float)nq + wide + eps;
+        if (fabsf(e0.b) > 1e-12f) {
+            const float r = 1.0f / e0.b, t0 = (qa - e0.a) * r, t1 = (qb - e0.a) * r;
+            lo = fmaxf(lo, fminf(t0, t1) - 1.0f);
+            hi = fminf(hi, fmaxf(t0, t1) + 1.0f);
+        } else if (!(e0.a > qa && e0.a < qb)) {
+            hi = -1.0f;
+        }
+    }
+    // rows and candidates per row are shared by the wave, so that its lanes
+    // read neighbouring pixels of one row
+    int p0 = (int)fminf(fmaxf(lo, 0.0f), (float)np), p1 = (int)fminf(fmaxf(hi, -1.0f), (float)(np - 1));
+    int cand = bounded ? min((int)(wide + 2.0f * eps) + 1, nq) : nq;
+    if (!used || p0 > p1) {
+        p0 = np;
+        p1 = -1;
+        cand = 0;
+    }
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) {
+        p0 = min(p0, __shfl_xor(p0, o));
+        p1 = max(p1, __shfl_xor(p1, o));
+        cand = max(cand, __shfl_xor(cand, o));
+    }
+    p0 = __builtin_amdgcn_readfirstlane(p0);
+    p1 = __builtin_amdgcn_readfirstlane(p1);
+    cand = __builtin_amdgcn_readfirstlane(cand);
+    const float jf = (float)j;
+    p0 += (first - p0 % stride + stride) % stride;
+    for (int pb = p0; pb <= p1; pb += STRIP_ROWS * stride) {
+        int q0[STRIP_ROWS];
+#pragma unroll
+        for (int r = 0; r < STRIP_ROWS; ++r) {
+            const float fp = (float)(pb + r * stride);
+            const float qlo = bounded ? fminf(fmaf(fp, e0.b, e0.a), fmaf(fp, e1.b, e1.a)) - eps : 0.0f;
+            q0[r] = (int)ceilf(fminf(fmaxf(qlo, 0.0f), (float)nq));
+            if (pb + r * stride > p1)
+                q0[r] = nq;   // past the last row: no candidates
+        }
+        for (int n = 0; n < cand; ++n) {
+            float val[STRIP_ROWS];
+#pragma unroll
+            for (int r = 0; r < STRIP_ROWS; ++r) {
+                const bool in = q0[r] + n < nq;
+                const int q = in ? q0[r] + n : 0, p = in ? pb + r * stride : 0;
+                val[r] = load_f32(im + (size_t)(AX == 0 ? p : q) * g.nx + (AX == 0 ? q : p));
+            }
+#pragma unroll
+            for (int r = 0; r < STRIP_ROWS; ++r) {
+                const bool in = q0[r] + n < nq;
+                const int q = in ? q0[r] + n : 0, p = in ? pb + r * stride : 0;
+                const int ix = AX == 0 ? q : p, iy = AX == 0 ? p : q;
+                float fu, t, wt;
+                point2d<FAN>(g, c, fmaf((float)ix, g.sx, g.ox), fmaf((float)iy, g.sy, g.oy), fu, t, wt);
+                const float v = g.dbeta * wt * (in && fu == jf ? val[r] : 0.0f);
+                a0 = fmaf(v, 1.0f - t, a0);
+                a1 = fmaf(v, t, a1);
+            }
+        }
+    }
+}
+
+template <typename TI, bool FAN>
+__global__ void __launch_bounds__(1024) bpT2d_kernel(Geom2D g, const float2 *__restrict__ views,
+                                                     const TI *__restrict__ img, float *__restrict__ sino, int groups)
+{
+    extern __shared__ float2 part[];   // one entry per thread, for more than one wave
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, waves = blockDim.x >> 6;
+    const int grp = (int)(blockIdx.x % (unsigned)groups);
+    const long kb = blockIdx.x / (unsigned)groups;   // view of an item
+    const int k = (int)(kb % g.n_proj), b = (int)(kb / g.n_proj);
+    const int j = grp * 63 - 1 + lane;   // this lane's strip
+    const float2 c = views[k];
+    const TI *im = img + (size_t)b * g.nx * g.ny;
+    float a0 = 0.0f, a1 = 0.0f;
+    {
+        const bool used = j < g.nu;
+        const double jd = (double)(used ? j : g.nu - 1);
+        double px, py, dx0, dy0, qx, qy, dx1, dy1;
+        edge_ray<FAN>(g, c, jd, px, py, dx0, dy0);
+        edge_ray<FAN>(g, c, jd + 1.0, qx, qy, dx1, dy1);
+        // the wave walks along the axis its first strip's edges advance on
+        // faster (its strips span a few degrees); a strip whose edges do not
+        // both advance one way along it (a bin wider than a right angle, say)
+        // is not bounded by them: every pixel of a row is a candidate
+        const int ax = __builtin_amdgcn_readfirstlane(fabs(dy0) + fabs(dy1) >= fabs(dx0) + fabs(dx1) ? 0 : 1);
+        const double p0 = ax == 0 ? dy0 : dx0, p1 = ax == 0 ? dy1 : dx1;
+        const double s0 = ax == 0 ? dx0 : dy0, s1 = ax == 0 ? dx1 : dy1;
+        const bool bounded = p0 * p1 > 0.0 && fabs(p0) > 0.05 * fabs(s0) && fabs(p1) > 0.05 * fabs(s1);
+        StripEdge e0 = {0.0f, 0.0f}, e1 = {0.0f, 0.0f};
+        if (bounded) {
+            const double b0 = s0 / p0, b1 = s1 / p1;
+            e0.b = (float)b0;
+            e1.b = (float)b1;
+            e0.a = (float)(ax == 0 ? px - py * b0 : py - px * b0);
+            e1.a = (float)(ax == 0 ? qx - qy * b1 : qy - qx * b1);
+        }
+        if (ax == 0)
+            strip_walk<TI, FAN, 0>(g, c, im, j, used, bounded, e0, e1, wave, waves, a0, a1);
+        else
+            strip_walk<TI, FAN, 1>(g, c, im, j, used, bounded, e0, e1, wave, waves, a0, a1);
+    }
+    if (waves > 1) {
+        part[threadIdx.x] = make_float2(a0, a1);
+        __syncthreads();
+        if (wave > 0)
+            return;
+        for (int w = 1; w < waves; ++w) {
+            const float2 o = part[w * 64 + lane];
+            a0 += o.x;
+            a1 += o.y;
+        }
+    }
+    const float below = __shfl_up(a1, 1);
+    if (lane > 0 && j < g.nu)
+        sino[((size_t)b * g.n_proj + k) * g.nu + j] = a0 + below;
 }
 
 template <typename T, typename TI, bool FAN, int S>
@@ -496,20 +639,29 @@ template <typename TI>
 hipError_t bpT2d(bool fan, const Geom2D &g, const float2 *views, const void *img, float *sino, int batch,
                  hipStream_t stream)
 {
-    dim3 grid((g.nx + 15) / 16, (g.ny + 15) / 16, batch);
+    const int groups = (g.nu + 62) / 63;
+    const long blocks = (long)groups * g.n_proj * batch;
+    if (blocks > 0x7fffffffL)
+        return hipErrorInvalidConfiguration;
+    // waves per workgroup: enough for about 16 waves on every CU, at least
+    // eight rows each
+    int waves = 1;
+    while (waves < 16 && blocks * waves < 4096 && waves * 16 <= (g.nx < g.ny ? g.nx : g.ny))
+        waves *= 2;
+    const dim3 grid((unsigned)blocks), block(64 * waves);
+    const size_t lds = waves > 1 ? 64 * waves * sizeof(float2) : 0;
     if (fan)
-        hipLaunchKernelGGL((bpT2d_kernel<TI, true>), grid, dim3(256), 0, stream, g, views, (const TI *)img, sino);
+        hipLaunchKernelGGL((bpT2d_kernel<TI, true>), grid, block, lds, stream, g, views, (const TI *)img, sino,
+                           groups);
     else
-        hipLaunchKernelGGL((bpT2d_kernel<TI, false>), grid, dim3(256), 0, stream, g, views, (const TI *)img, sino);
+        hipLaunchKernelGGL((bpT2d_kernel<TI, false>), grid, block, lds, stream, g, views, (const TI *)img, sino,
+                           groups);
     return hipGetLastError();
 }
 
 hipError_t launch_backproject_adjoint_2d(int in_dtype, bool fan, const Geom2D &g, const float2 *views,
                                          const void *img, float *sino, int batch, hipStream_t stream)
 {
-    hipError_t e = fill_zero(sino, (size_t)batch * g.n_proj * g.nu, stream);
-    if (e != hipSuccess)
-        return e;
     switch (in_dtype) {
     case 0: return bpT2d<float>(fan, g, views, img, sino, batch, stream);
     case 1: return bpT2d<f16_t>(fan, g, views, img, sino, batch, stream);

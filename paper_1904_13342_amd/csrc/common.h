@@ -42,6 +42,7 @@ struct Geom2D {
     float inv_sx, inv_sy;  // 1 / spacing
     float sx, sy;
     float du, cu;          // detector spacing, (nu-1)/2
+    float ru, ru_lo;       // bins per mm (parallel: 1/du) or per unit of slope or fan angle (sdd/du), in two floats
     float sid, sdd;
     float step;            // ray sampling step (mm)
     float dbeta;           // range / n_proj

@@ -97,36 +97,77 @@ __device__ __forceinline__ void make_ray_2d(const Geom2D &g, float2 c, int j, fl
     eY = (float)((double)g.step * dy / (double)g.sy);
 }
 
-// Detector bin j, fraction t in [0, 1) and distance weight of pixel (ix, iy)
-// in a fan view with central ray c: central projection onto the flat detector
-// with weight (SID / w)^2, w the depth along the central ray; on the
-// equiangular detector the bin of the pixel's fan angle, with weight
-// (SID / L)^2, L the distance from the source.  All in FP32: the arctangent
-// places a wide fan's samples to a few 1e-6 bin.  The back-projector and its
-// transpose both use this, so they see the same coordinates.
-__device__ __forceinline__ void fan2d_point(const Geom2D &g, float2 c, int ix, int iy, int &j, float &t, float &wt)
+// 1/x from the hardware estimate refined by one Newton step
+__device__ __forceinline__ float rcp_nr(float x)
 {
-    if (g.curved) {
-        const float x = fmaf((float)ix, g.sx, g.ox), y = fmaf((float)iy, g.sy, g.oy);
-        const float xu = -x * c.y + y * c.x;
+    const float r = __builtin_amdgcn_rcpf(x);
+    return fmaf(r, fmaf(-x, r, 1.0f), r);
+}
+
+// n / d from rcp_nr with one more residual step: the correctly rounded
+// quotient in nearly every case, in five instructions
+__device__ __forceinline__ float div_nr(float n, float d)
+{
+    const float r = rcp_nr(d), q = n * r;
+    return fmaf(fmaf(-q, d, n), r, q);
+}
+
+// atan(z) / z - 1 = s Q(s), s = z^2, for |z| <= tan(pi / 8): Q interpolated at
+// six Chebyshev nodes of [0, tan^2(pi / 8)] (worst error of s Q 1.6e-9).
+__device__ __forceinline__ float atan_small(float z)
+{
+    const float s = z * z;
+    float q = fmaf(s, 0.050471332f, -0.08624286f);
+    q = fmaf(s, q, 0.110713124f);
+    q = fmaf(s, q, -0.14284149f);
+    q = fmaf(s, q, 0.19999978f);
+    q = fmaf(s, q, -0.33333334f);
+    return fmaf(z * s, q, z);
+}
+
+// Bin fu (a float whole number), fraction t and distance weight wt of world
+// point (x, y) in a 2D view with central ray c.  Parallel beams: the
+// orthogonal projection, weight 1.  Fan beams: central projection onto the
+// flat detector with weight (SID / w)^2, w the depth along the central ray; on
+// the equiangular detector the bin of the point's fan angle, with weight
+// (SID / L)^2, L the distance from the source.  All in FP32.  Two roundings
+// that a detector of a thousand bins would feel are kept out: the scale to
+// bins (ru) is held in two floats, and the fraction is formed from the
+// centred coordinate by one FMA, not by subtracting the bin from a rounded
+// sum (so it may leave [0, 1) by an ulp of the coordinate).  The fan angle is
+// atan_small of the slope, taken from the pi / 4 or pi / 2 direction beyond
+// tan(pi / 8) and tan(3 pi / 8).  The back-projector and its transpose both
+// use this, so they see the same coordinates.
+template <bool FAN>
+__device__ __forceinline__ void point2d(const Geom2D &g, float2 c, float x, float y, float &fu, float &t, float &wt)
+{
+    const float xu = fmaf(y, c.x, -(x * c.y));
+    float q = xu, off = 0.0f;   // offset, slope or fan angle: q + off
+    wt = 1.0f;
+    if (FAN) {
         const float w = fmaf(x, c.x, fmaf(y, c.y, g.sid));
-        const float s = fmaf(atan2f(xu, w), g.sdd / g.du, g.cu);
-        const float fs = floorf(s);
-        j = (int)fs;
-        t = s - fs;
-        wt = g.sid * g.sid / fmaf(w, w, xu * xu);
-    } else {
-        const float x = fmaf((float)ix, g.sx, g.ox), y = fmaf((float)iy, g.sy, g.oy);
-        const float xu = -x * c.y + y * c.x;
-        const float w = fmaf(x, c.x, fmaf(y, c.y, g.sid));
-        const float rw = 1.0f / w;
-        const float su = fmaf(g.sdd * xu * rw, 1.0f / g.du, g.cu);
-        const float fu = floorf(su);
-        j = (int)fu;
-        t = su - fu;
-        const float sw = g.sid * rw;
-        wt = sw * sw;
+        if (!g.curved) {
+            const float rw = rcp_nr(w), q0 = xu * rw, sw = g.sid * rw;
+            q = fmaf(fmaf(-q0, w, xu), rw, q0);   // xu / w
+            wt = sw * sw;
+        } else {
+            wt = g.sid * g.sid * rcp_nr(fmaf(w, w, xu * xu));
+            const float a = fabsf(xu);
+            float num = a, den = w;
+            if (a > 0.41421357f * w) {
+                const bool steep = a > 2.4142135f * w;
+                num = steep ? -w : a - w;
+                den = steep ? a : a + w;
+                off = copysignf(steep ? 1.57079633f : 0.78539816f, xu);
+            }
+            q = copysignf(1.0f, xu) * atan_small(div_nr(num, den));
+        }
     }
+    const float lo = FAN ? (q + off) * g.ru_lo : q * g.ru_lo;
+    const float base = FAN ? fmaf(off, g.ru, g.cu) : g.cu;
+    fu = floorf(fmaf(q, g.ru, base + lo));
+    const float back = FAN ? fmaf(off, g.ru, g.cu - fu) : g.cu - fu;
+    t = fmaf(q, g.ru, back) + lo;
 }
 
 // Narrow [lo, hi] to the parameters t with p + t e inside the open interval
@@ -158,13 +199,6 @@ __device__ __forceinline__ bool clip_line_rcp(float p, float e, float a, float b
 __device__ __forceinline__ float dot4(const float r[4], float x, float y, float z)
 {
     return fmaf(r[0], x, fmaf(r[1], y, fmaf(r[2], z, r[3])));
-}
-
-// 1/x from the hardware estimate refined by one Newton step
-__device__ __forceinline__ float rcp_nr(float x)
-{
-    const float r = __builtin_amdgcn_rcpf(x);
-    return fmaf(r, fmaf(-x, r, 1.0f), r);
 }
 
 // nearest integer of x (ties toward +inf) in one instruction; the

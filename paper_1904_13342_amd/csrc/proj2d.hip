@@ -86,22 +86,13 @@ __global__ void __launch_bounds__(256) bp2d_kernel(Geom2D g, const float2 *__res
         return;   // whole pixels only: the S lanes of a pixel leave together
     const TI *sb = sino + (size_t)b * g.n_proj * g.nu;
     const float x = fmaf((float)ix, g.sx, g.ox), y = fmaf((float)iy, g.sy, g.oy);
-    const float rdu = 1.0f / g.du;
     float acc = 0.0f;
 #pragma unroll 4   // several views' loads in flight at once
     for (int k = s; k < g.n_proj; k += S) {
         const float2 c = views[k];
-        int j;
-        float t, wt;
-        if (!FAN) {
-            const float su = fmaf(-x * c.y + y * c.x, rdu, g.cu);
-            const float fu = floorf(su);
-            j = (int)fu;
-            t = su - fu;
-            wt = 1.0f;
-        } else {
-            fan2d_point(g, c, ix, iy, j, t, wt);
-        }
+        float fu, t, wt;
+        point2d<FAN>(g, c, x, y, fu, t, wt);
+        const int j = (int)fu;
         const TI *row = sb + (size_t)k * g.nu;
         const float p0 = (j >= 0 && j < g.nu) ? load_f32(row + j) : 0.0f;
         const float p1 = (j + 1 >= 0 && j + 1 < g.nu) ? load_f32(row + j + 1) : 0.0f;

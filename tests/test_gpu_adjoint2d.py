@@ -1,0 +1,61 @@
+"""The 2D transposes at the edges of their work split, against the FP64
+oracle: bin counts around a wave's 63 strips, bins far narrower and far wider
+than a pixel, images of one row, one column and one pixel, and fans whose
+outer bins run across the axis the wave walks along."""
+import math
+
+import pytest
+
+import gpu_common as gc
+import synth
+from gpu_common import as_f32, check, say, to_dev, to_np
+
+pytestmark = pytest.mark.gpu
+
+FAN = dict(sid=120.0, sdd=200.0)
+# kind, (ny, nx), nu, du, views, range in degrees
+CASES = {
+    "par_62": ("par2d", (24, 31), 62, 0.7, 11, 180, {}),
+    "par_63": ("par2d", (31, 24), 63, 0.7, 7, 180, {}),
+    "par_64": ("par2d", (33, 32), 64, 0.7, 5, 360, {}),
+    "par_127_fine": ("par2d", (17, 40), 127, 0.31, 8, 180, {}),
+    "par_coarse": ("par2d", (64, 70), 9, 9.0, 12, 180, {}),
+    "par_1_bin": ("par2d", (20, 20), 1, 4.0, 6, 180, {}),
+    "par_row": ("par2d", (1, 33), 41, 1.0, 9, 180, {}),
+    "par_column": ("par2d", (33, 1), 41, 1.0, 9, 180, {}),
+    "par_pixel": ("par2d", (1, 1), 5, 0.6, 9, 180, {}),
+    "fan_126": ("fan2d", (40, 37), 126, 0.8, 13, 360, FAN),
+    "fan_wide": ("fan2d", (30, 30), 70, 9.0, 9, 360, dict(sid=40.0, sdd=60.0)),
+    "arc_190": ("fan2d_curved", (45, 52), 190, 0.6, 10, 360, FAN),
+    "arc_few_wide_bins": ("fan2d_curved", (26, 26), 4, 40.0, 9, 360, dict(sid=30.0, sdd=60.0)),
+    "arc_tiny": ("fan2d_curved", (2, 3), 9, 0.4, 8, 220, FAN),
+}
+
+
+@pytest.fixture(scope="module")
+def ph():
+    gc.device()
+    import paper_1904_13342_amd as ph
+    return ph
+
+
+def _setup(ph, name):
+    kind, shape, nu, du, views, turn, src = CASES[name]
+    spec = synth.config("par2d_64").with_(kind=kind, vol_shape=shape, vol_spacing=(1.0, 1.0), det_shape=(nu,),
+                                          det_spacing=(du,), n_proj=views, angular_range=turn * math.pi / 180, **src)
+    g = ph.from_spec(spec)
+    fan = kind != "par2d"
+    return spec, g, ph.ray_vectors_2d(g), fan
+
+
+@pytest.mark.parametrize("name", list(CASES))
+def test_backproject_adjoint_2d_edges(ph, ora, name):
+    import numpy as np
+    spec, g, rv, fan = _setup(ph, name)
+    rng = np.random.default_rng(5)
+    f = as_f32(rng.standard_normal((3,) + spec.vol_shape))
+    bT = ph.backproject_adjoint_fan2d if fan else ph.backproject_adjoint_par2d
+    out = bT(g, rv, to_dev(f))
+    say(f"[B^T 2D] {name}")
+    check(to_np(out), np.stack([ora.backproject_adjoint(spec, v) for v in f]), name)
+    assert (bT(g, rv, to_dev(f)) == out).all()   # the same bits on every run
