@@ -142,8 +142,8 @@ int make_geom2d(const ph_geom2d *g, bool fan, Geom2D *o)
     o->sx = g->vol_spacing[1];
     o->oy = g->vol_origin[0];
     o->ox = g->vol_origin[1];
-    o->inv_sx = (float)(1.0 / g->vol_spacing[1]);
-    o->inv_sy = (float)(1.0 / g->vol_spacing[0]);
+    o->inv_sx = 1.0 / g->vol_spacing[1];
+    o->inv_sy = 1.0 / g->vol_spacing[0];
     o->nu = g->det_shape;
     o->du = g->det_spacing;
     o->cu = 0.5f * (float)(g->det_shape - 1);
@@ -155,6 +155,8 @@ int make_geom2d(const ph_geom2d *g, bool fan, Geom2D *o)
     o->ru_lo = (float)(ru - (double)o->ru);
     o->curved = fan && g->fan_detector == 1 ? 1 : 0;
     o->step = (float)default_step(g->step_mm, std::fmin(g->vol_spacing[0], g->vol_spacing[1]));
+    o->step_sx = (double)o->step / g->vol_spacing[1];
+    o->step_sy = (double)o->step / g->vol_spacing[0];
     o->dbeta = (float)((double)g->angular_range / g->n_proj);
     return PH_OK;
 }

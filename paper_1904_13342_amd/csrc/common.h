@@ -39,7 +39,8 @@ struct Geom2D {
     int nx, ny, nu, n_proj;
     int curved;            // fan beams: 1 for the equiangular (arc) detector, 0 for the flat one
     float ox, oy;          // world mm of pixel (0,0)
-    float inv_sx, inv_sy;  // 1 / spacing
+    double inv_sx, inv_sy;    // 1 / spacing
+    double step_sx, step_sy;  // ray sampling step / spacing
     float sx, sy;
     float du, cu;          // detector spacing, (nu-1)/2
     float ru, ru_lo;       // bins per mm (parallel: 1/du) or per unit of slope or fan angle (sdd/du), in two floats

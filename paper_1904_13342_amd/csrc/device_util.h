@@ -11,6 +11,15 @@ struct Ray {
     float p[3], e[3];
 };
 
+// 1 / sqrt(x) from the hardware estimate refined by two Newton steps
+__device__ __forceinline__ double rsqrt_nr(double x)
+{
+    const double h = 0.5 * x;
+    double r = __builtin_amdgcn_rsq(x);
+    r = r * fma(-h * r, r, 1.5);
+    return r * fma(-h * r, r, 1.5);
+}
+
 // Ray of cone-beam detector pixel (j, i), set up in double precision (the
 // source is ~SID away, so an FP32 direction would misplace the ray by
 // ~SID * 2^-24 at the volume) and rounded once to FP32.  The direction is
@@ -25,11 +34,7 @@ __device__ __forceinline__ Ray make_cone_ray(const Geom3D &g, const ConeFPView &
 #pragma unroll
     for (int t = 0; t < 3; ++t)
         d[t] = fma(jc, v.du[t], fma(ic, v.dv[t], v.d0[t]));
-    const double n2 = fma(d[0], d[0], fma(d[1], d[1], d[2] * d[2]));
-    const double h = 0.5 * n2;
-    double rn = __builtin_amdgcn_rsq(n2);
-    rn = rn * fma(-h * rn, rn, 1.5);
-    rn = rn * fma(-h * rn, rn, 1.5);
+    const double rn = rsqrt_nr(fma(d[0], d[0], fma(d[1], d[1], d[2] * d[2])));
 #pragma unroll
     for (int t = 0; t < 3; ++t)
         d[t] *= rn;
@@ -73,28 +78,27 @@ __device__ __forceinline__ void make_ray_2d(const Geom2D &g, float2 c, int j, fl
         ay = u * ey;
         dx = cx;
         dy = cy;
-    } else if (g.curved) {
-        const double gam = u / (double)g.sdd, cg = cos(gam), sg = sin(gam);
-        const double sx = -(double)g.sid * cx, sy = -(double)g.sid * cy;
-        dx = cg * cx + sg * ex;
-        dy = cg * cy + sg * ey;
-        const double t0 = -(sx * dx + sy * dy);
-        ax = fma(t0, dx, sx);
-        ay = fma(t0, dy, sy);
     } else {
         const double sx = -(double)g.sid * cx, sy = -(double)g.sid * cy;
-        const double tx = (double)g.sdd * cx + u * ex, ty = (double)g.sdd * cy + u * ey;  // detector - source
-        const double rn = 1.0 / sqrt(tx * tx + ty * ty);
-        dx = tx * rn;
-        dy = ty * rn;
-        const double t0 = -(sx * dx + sy * dy);
+        if (g.curved) {
+            double cg, sg;
+            sincos(u / (double)g.sdd, &sg, &cg);
+            dx = fma(cg, cx, sg * ex);
+            dy = fma(cg, cy, sg * ey);
+        } else {
+            const double tx = fma((double)g.sdd, cx, u * ex), ty = fma((double)g.sdd, cy, u * ey);  // detector - source
+            const double rn = rsqrt_nr(fma(tx, tx, ty * ty));
+            dx = tx * rn;
+            dy = ty * rn;
+        }
+        const double t0 = -fma(sx, dx, sy * dy);
         ax = fma(t0, dx, sx);
         ay = fma(t0, dy, sy);
     }
-    X0 = (float)((ax - (double)g.ox) / (double)g.sx);
-    Y0 = (float)((ay - (double)g.oy) / (double)g.sy);
-    eX = (float)((double)g.step * dx / (double)g.sx);
-    eY = (float)((double)g.step * dy / (double)g.sy);
+    X0 = (float)((ax - (double)g.ox) * g.inv_sx);
+    Y0 = (float)((ay - (double)g.oy) * g.inv_sy);
+    eX = (float)(dx * g.step_sx);
+    eY = (float)(dy * g.step_sy);
 }
 
 // 1/x from the hardware estimate refined by one Newton step
@@ -237,6 +241,16 @@ template <int CTRL>
 __device__ __forceinline__ int dppi(int x)
 {
     return __builtin_amdgcn_update_dpp(0, x, CTRL, 0xF, 0xF, false);
+}
+__device__ __forceinline__ int imin4(int x)   // over four corners, lane mod 4
+{
+    x = min(x, dppi<0xB1>(x));
+    return min(x, dppi<0x4E>(x));
+}
+__device__ __forceinline__ int imax4(int x)
+{
+    x = max(x, dppi<0xB1>(x));
+    return max(x, dppi<0x4E>(x));
 }
 __device__ __forceinline__ int imin8(int x)
 {
