@@ -1,0 +1,56 @@
+"""2D projector and back-projector where the unchecked inner loops meet the
+checked ones, against the FP64 oracle: images whose border is inside every
+wave's four samples, images narrower than a cell, rays along an axis, an image
+far off the axis of rotation, few and many rays per wave, views in numbers
+that are no multiple of a lane's four."""
+import math
+
+import numpy as np
+import pytest
+
+import gpu_common as gc
+import synth
+from gpu_common import as_f32, check, say, to_dev, to_np
+
+pytestmark = pytest.mark.gpu
+
+FAN = dict(sid=700.0, sdd=1100.0)
+# kind, (ny, nx), nu, du, views, range in degrees, source, origin (y, x) or None
+CASES = {
+    "par_2x2": ("par2d", (2, 2), 7, 0.5, 4, 180, {}, None),
+    "par_row": ("par2d", (1, 70), 80, 1.0, 5, 180, {}, None),
+    "par_column": ("par2d", (70, 1), 80, 1.0, 5, 180, {}, None),
+    "par_axis_aligned": ("par2d", (96, 64), 101, 1.0, 4, 360, {}, None),
+    "par_one_view": ("par2d", (130, 90), 160, 1.0, 1, 180, {}, None),
+    "par_63_views": ("par2d", (40, 300), 310, 1.0, 63, 180, {}, None),
+    "par_off_axis": ("par2d", (60, 50), 500, 1.0, 9, 180, {}, (-180.0, 120.0)),
+    "fan_65_views": ("fan2d", (127, 129), 230, 1.0, 65, 360, FAN, None),
+    "fan_few_bins": ("fan2d", (100, 90), 3, 60.0, 33, 360, FAN, None),
+    "arc_short": ("fan2d_curved", (90, 128), 190, 1.1, 37, 220, FAN, None),
+}
+
+
+@pytest.fixture(scope="module")
+def ph():
+    gc.device()
+    import paper_1904_13342_amd as ph
+    return ph
+
+
+@pytest.mark.parametrize("name", list(CASES))
+def test_pair_2d_edges(ph, ora, name):
+    kind, shape, nu, du, views, turn, src, origin = CASES[name]
+    spec = synth.config("par2d_64").with_(kind=kind, vol_shape=shape, vol_spacing=(1.0, 1.0), det_shape=(nu,),
+                                          det_spacing=(du,), n_proj=views, angular_range=turn * math.pi / 180,
+                                          vol_origin=origin, **src)
+    g = ph.from_spec(spec)
+    rv, fan = ph.ray_vectors_2d(g), kind != "par2d"
+    rng = np.random.default_rng(3)
+    # positive values: a sum of terms that do not cancel keeps the coordinates'
+    # rounding (2^-17 pixel and bin) at 1e-5 of itself
+    f = as_f32(rng.uniform(0.5, 1.5, (2,) + spec.vol_shape))
+    p = as_f32(rng.uniform(0.5, 1.5, (2, views, nu)))
+    A, B = (ph.project_fan2d, ph.backproject_fan2d) if fan else (ph.project_par2d, ph.backproject_par2d)
+    say(f"[A, B 2D] {name}")
+    check(to_np(A(g, rv, to_dev(f))), np.stack([ora.project(spec, v) for v in f]), "A", tol=2e-5)
+    check(to_np(B(g, rv, to_dev(p))), np.stack([ora.backproject(spec, v) for v in p]), "B", tol=2e-5)
