@@ -179,6 +179,16 @@ int ph_backproject_adjoint_fan2d(const ph_geom2d *g, const float *ray_vecs, cons
 int ph_backproject_adjoint_cone3d(const ph_geom3d *g, const float *mats, const void *vol, void *proj, int batch,
                                   ph_dtype dtype, void *stream);
 
+/* A^T of a volume too small to fill the GPU with its bricks takes the views
+ * in shares, each on its own workgroups, whose FP64 partial sums are added in
+ * a fixed order: same result up to that order.  `ws` holds them:
+ * ph_project_adjoint_workspace_bytes_3d() bytes, at most 64 MiB, 0 for larger volumes
+ * (then ws may be NULL).  ph_project_adjoint_cone3d takes all views in one
+ * share. */
+size_t ph_project_adjoint_workspace_bytes_3d(const ph_geom3d *g, int batch);
+int ph_project_adjoint_ws_cone3d(const ph_geom3d *g, const float *mats, const void *proj, void *vol, void *ws,
+                                 size_t ws_bytes, int batch, ph_dtype dtype, void *stream);
+
 /* B^T with any storage type (extension 1): the scatter accumulates in FP32,
  * in the output itself for FP32 and otherwise in the workspace `ws` of
  * ph_backproject_adjoint_workspace_bytes_*() bytes (0 for FP32, where ws may

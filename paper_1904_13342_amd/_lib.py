@@ -75,6 +75,8 @@ SIGNATURES = {
     "ph_project_adjoint_par2d": (_I, [_G2, _FP, _P, _P, _I, _I, _P]),
     "ph_project_adjoint_fan2d": (_I, [_G2, _FP, _P, _P, _I, _I, _P]),
     "ph_project_adjoint_cone3d": (_I, [_G3, _FP, _P, _P, _I, _I, _P]),
+    "ph_project_adjoint_workspace_bytes_3d": (_SZ, [_G3, _I]),
+    "ph_project_adjoint_ws_cone3d": (_I, [_G3, _FP, _P, _P, _P, _SZ, _I, _I, _P]),
     "ph_backproject_adjoint_par2d": (_I, [_G2, _FP, _P, _P, _I, _I, _P]),
     "ph_backproject_adjoint_fan2d": (_I, [_G2, _FP, _P, _P, _I, _I, _P]),
     "ph_backproject_adjoint_cone3d": (_I, [_G3, _FP, _P, _P, _I, _I, _P]),

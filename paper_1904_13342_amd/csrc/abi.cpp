@@ -1249,10 +1249,10 @@ int ph_backproject_adjoint_fan2d(const ph_geom2d *g, const float *rv, const void
     return adjoint2d(g, true, false, rv, img, sino, batch, dtype, stream);
 }
 
-int ph_project_adjoint_cone3d(const ph_geom3d *g, const float *mats, const void *proj, void *vol, int batch,
-                              ph_dtype dtype, void *stream)
+// A^T in 3D; with a workspace the views of a small volume are taken in shares.
+static int fpT3d(const ph_geom3d *g, const float *mats, const void *proj, void *vol, void *ws, size_t ws_bytes,
+                 bool ws_call, int batch, int dtype, void *stream)
 {
-    CallScope scope;
     if (!proj || !vol)
         return PH_ERR_NULL;
     if (batch < 1)
@@ -1265,6 +1265,9 @@ int ph_project_adjoint_cone3d(const ph_geom3d *g, const float *mats, const void 
     st = validate3d(g, mats, &G, &P);
     if (st != PH_OK)
         return st;
+    const size_t need = ws_call ? project_adjoint_scratch(G, batch) : 0;
+    if (need > 0 && (!ws || ws_bytes < need))
+        return PH_ERR_WORKSPACE;
     const void *fv = nullptr, *bv = nullptr;
     bool axial = false;
     st = upload3d(g, mats, P, false, &fv, &axial);
@@ -1274,7 +1277,30 @@ int ph_project_adjoint_cone3d(const ph_geom3d *g, const float *mats, const void 
     if (st != PH_OK)
         return st;
     return to_status(launch_project_adjoint_cone(dtype, G, (const ConeFPView *)fv, (const ConeBPView *)bv, proj, vol,
-                                                 batch, (hipStream_t)stream));
+                                                 batch, need > 0 ? (double *)ws : nullptr, (hipStream_t)stream));
+}
+
+int ph_project_adjoint_cone3d(const ph_geom3d *g, const float *mats, const void *proj, void *vol, int batch,
+                              ph_dtype dtype, void *stream)
+{
+    CallScope scope;
+    return fpT3d(g, mats, proj, vol, nullptr, 0, false, batch, dtype, stream);
+}
+
+size_t ph_project_adjoint_workspace_bytes_3d(const ph_geom3d *g, int batch)
+{
+    CallScope scope;
+    Geom3D G;
+    if (batch < 1 || make_geom3d(g, &G) != PH_OK)
+        return 0;
+    return project_adjoint_scratch(G, batch);
+}
+
+int ph_project_adjoint_ws_cone3d(const ph_geom3d *g, const float *mats, const void *proj, void *vol, void *ws,
+                                 size_t ws_bytes, int batch, ph_dtype dtype, void *stream)
+{
+    CallScope scope;
+    return fpT3d(g, mats, proj, vol, ws, ws_bytes, true, batch, dtype, stream);
 }
 
 static int bpT3d(const ph_geom3d *g, const float *mats, const void *vol, void *proj, void *ws, size_t ws_bytes,
@@ -1496,7 +1522,9 @@ size_t ph_tv_workspace_bytes_3d(const ph_geom3d *g, int batch)
         return 0;
     const size_t np = (size_t)batch * g->n_proj * g->det_shape[0] * g->det_shape[1];
     const size_t nx = (size_t)batch * g->vol_shape[0] * g->vol_shape[1] * g->vol_shape[2];
-    return 2 * round_up(np * sizeof(float)) + round_up(nx * sizeof(float));
+    // the projections' residual and its gradient, the image gradient, A^T's partial sums
+    return 2 * round_up(np * sizeof(float)) + round_up(nx * sizeof(float)) +
+           ph_project_adjoint_workspace_bytes_3d(g, batch);
 }
 
 }  // extern "C"
@@ -1618,12 +1646,18 @@ int ph_tv_iterate_cone3d(const ph_geom3d *g, const float *mats, const float *pro
         return st;
     const size_t np = (size_t)batch * g->n_proj * g->det_shape[0] * g->det_shape[1];
     const size_t nimg = (size_t)batch * g->vol_shape[0] * g->vol_shape[1] * g->vol_shape[2];
+    // A^T's partial sums follow the buffers of the loop; a workspace without
+    // room for them serves too (all views in one share)
+    const size_t need = 2 * round_up(np * sizeof(float)) + round_up(nimg * sizeof(float));
+    const size_t extra = ph_project_adjoint_workspace_bytes_3d(g, batch);
+    void *const part = ws && extra > 0 && ws_bytes >= need + extra ? (char *)ws + need : nullptr;
     auto fwd = [&](const float *vol, float *pr) { return ph_project_cone3d(g, mats, vol, pr, batch, PH_F32, stream); };
     auto adj = [&](const float *pr, float *vol) {
-        return ph_project_adjoint_cone3d(g, mats, pr, vol, batch, PH_F32, stream);
+        return part ? ph_project_adjoint_ws_cone3d(g, mats, pr, vol, part, extra, batch, PH_F32, stream)
+                    : ph_project_adjoint_cone3d(g, mats, pr, vol, batch, PH_F32, stream);
     };
     return tv_iterate(fwd, adj, g->vol_shape[0], g->vol_shape[1], g->vol_shape[2], np, nimg, proj, x, m, v, t0, n_iter,
-                      prm, ws, ws_bytes, ph_tv_workspace_bytes_3d(g, batch), data_tv, batch, stream);
+                      prm, ws, ws_bytes, need, data_tv, batch, stream);
 }
 
 }  // extern "C"

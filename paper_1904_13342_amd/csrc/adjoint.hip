@@ -144,7 +144,7 @@ __global__ void __launch_bounds__(1024) fpT2d_kernel(Geom2D g, const float2 *__r
 // --------------------------------------------------------------- A^T, 3D
 //
 // A workgroup owns a 16 x 16 x 16 brick of voxels; each thread holds the
-// FP64 sums of one 16-voxel z-column of it in registers, over every view.
+// FP64 sums of 8 voxels of it in registers, over every view.
 // Per view, the rays that can reach the brick's support box (the detector
 // pixels of its footprint: 8 corners projected by eight lanes and reduced with
 // DPP) are set up exactly as the forward projector sets them up (FP64 set-up,
@@ -164,44 +164,56 @@ __global__ void __launch_bounds__(1024) fpT2d_kernel(Geom2D g, const float2 *__r
 // and with scale = 2^30 / bound no cell can overflow.  Each corner term is
 // rounded to the nearest integer; after the pass every thread adds its own
 // cells, divided by the scale, to its FP64 sums and clears them.  The waves
-// take the sorted rays in tasks of 64 from a shared counter, longest first.  Cells of
-// the two-voxel halo are never read (the neighbouring bricks own those
-// voxels), so they need no clearing and may wrap.
+// take the sorted rays in tasks of 64 from a shared counter, longest first.
+//
+// What the walk waits for is the LDS: rays of one length are mostly
+// neighbours, and neighbours in step add to the same cells, which one atomic
+// instruction serialises.  The lanes of a task therefore start an eighth of
+// their rays apart and wrap round: at 256^3 (1.6 rays per voxel) address
+// conflicts fell from 1.63e10 to 0.33e10 cycles and A^T of 248 views from
+// 87 to 63 ms (2, 4, 8 and 16 starts, two of them walking backwards in the
+// first: 73, 66, 63, 66 ms); at 512^3 (one ray per voxel) there were few and
+// it gains 4%.  VALU and LDS are then busy 67 and 76% of the time.  512
+// threads and 1024 rays, so that a view's footprint is one pass, measured 61
+// ms against 63 for 256 threads and 640 rays, and 4.4 against 5.1 ms at 128^3.
 //
 // Sample ranges come from a clip with hardware reciprocals (relative error
 // ~1e-7 of a few thousand steps), widened by 0.01 step: every sample inside
 // the support box is visited, and a visited sample lies at most 0.01 step
-// outside it, so its cell stays inside the padded accumulator
-// (floor coordinates x0 - 2 .. x0 + 17).  Its rows and planes have odd
-// pitches: the rays of a wave, sorted by length, often sit at one x at the
-// same step, and even pitches would put their cells on a quarter of the
-// banks.
+// outside it, so its cell is one of floor coordinates x0 - 2 .. x0 + 16 and
+// its corners reach x0 + 17.  Cells of the halo (x0 - 2, x0 - 1, x0 + 16 and
+// x0 + 17 on any axis) are never read, since the neighbouring bricks own those
+// voxels, so they need no clearing, and the first and the last share a column
+// (of the row before), a row and a plane.  Rows and planes have odd pitches:
+// even ones would put cells in line along an axis on a quarter of the banks.
 
 constexpr int AT_B = 16;                       // brick edge (voxels)
-constexpr int AT_P = AT_B + 4;                 // accumulator edge (cells)
-constexpr int AT_PY = AT_P + 1;                // row pitch (words)
-constexpr int AT_PZ = AT_P * AT_PY + 1;        // plane pitch (words)
-constexpr int AT_CELLS = AT_P * AT_PZ;
-constexpr int AT_RAYS = 536;                   // footprint pixels per pass (ray-table capacity; with the
-                                               // accumulator, three workgroups fit a CU's LDS)
-constexpr int AT_PER_THREAD = (AT_RAYS + 255) / 256;
+constexpr int AT_PY = AT_B + 3;                // row pitch (words)
+constexpr int AT_PZ = AT_PY * AT_PY;           // plane pitch (words)
+constexpr int AT_ZERO = AT_PZ + AT_PY + 1;     // word of cell (x0 - 1, y0 - 1, z0 - 1)
+constexpr int AT_CELLS = AT_ZERO + (AT_B + 3) * AT_PZ;
+constexpr int AT_T = 512;                      // threads
+constexpr int AT_RAYS = 1024;                  // footprint pixels per pass (ray-table capacity; with the
+                                               // accumulator, two workgroups fit a CU's LDS)
+constexpr int AT_Z = AT_B * AT_B * AT_B / AT_T;   // voxels per thread (a piece of a z-column)
+constexpr int AT_PER_THREAD = (AT_RAYS + AT_T - 1) / AT_T;
 constexpr int AT_BINS = 256;                   // sample-count bins of the ray sort
 constexpr float AT_EPS = 0.01f;                // clip widening (steps)
 constexpr float AT_FIX = 1073741824.0f;        // 2^30
 
 template <typename T, typename TI>
-__global__ void __launch_bounds__(256) fpT_cone_kernel(Geom3D g, const ConeFPView *__restrict__ fviews,
-                                                       const ConeBPView *__restrict__ bviews,
-                                                       const TI *__restrict__ proj, T *__restrict__ vol, int nbx,
-                                                       int nby, int nbz)
+__global__ void __launch_bounds__(AT_T, 4) fpT_cone_kernel(Geom3D g, const ConeFPView *__restrict__ fviews,
+                                                        const ConeBPView *__restrict__ bviews,
+                                                        const TI *__restrict__ proj, T *__restrict__ vol,
+                                                        double *__restrict__ part, int nbx, int nby, int nbz)
 {
     __shared__ int acc[AT_CELLS];
     __shared__ float4 s_ra[AT_RAYS];   // biased anchor X, Y, Z and the ray's value
     __shared__ float4 s_rb[AT_RAYS];   // step e_x, e_y, e_z and the first sample (int bits)
     __shared__ int s_cnt[AT_RAYS];
     __shared__ int hist[AT_BINS];
-    __shared__ int s_wsum[4];
-    __shared__ float s_wbound[4];
+    __shared__ int s_wsum[AT_BINS / 64];
+    __shared__ float s_wbound[AT_T / 64];
     __shared__ int s_nhit;
     __shared__ int s_next;   // next 64-ray task of the walk
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -209,17 +221,18 @@ __global__ void __launch_bounds__(256) fpT_cone_kernel(Geom3D g, const ConeFPVie
     const int bzb = (int)(blockIdx.x / (unsigned)(nbx * nby));
     const int bzi = bzb % nbz, b = bzb / nbz;
     const int x0 = bxi * AT_B, y0 = byi * AT_B, z0 = bzi * AT_B;
-    for (int n = tid; n < AT_CELLS; n += 256)
+    for (int n = tid; n < AT_CELLS; n += AT_T)
         acc[n] = 0;
-    hist[tid] = 0;
+    if (tid < AT_BINS)
+        hist[tid] = 0;
     if (tid == 0)
         s_next = 0;
-    // this thread's voxel column (x0 + lx, y0 + ly, z0 .. z0 + 15) and its cells
-    const int lx = tid % AT_B, ly = tid / AT_B;
-    const int own = 2 * AT_PZ + (ly + 2) * AT_PY + lx + 2;   // cell of (lx, ly, 0); + AT_PZ per z
-    double out[AT_B];
+    // this thread's voxels (x0 + lx, y0 + ly, z0 + lz .. z0 + lz + AT_Z - 1) and their cells
+    const int lx = tid % AT_B, ly = (tid / AT_B) % AT_B, lz = tid / (AT_B * AT_B) * AT_Z;
+    const int own = AT_ZERO + (lz + 1) * AT_PZ + (ly + 1) * AT_PY + lx + 1;   // cell of (lx, ly, lz); + AT_PZ per z
+    double out[AT_Z];
 #pragma unroll
-    for (int z = 0; z < AT_B; ++z)
+    for (int z = 0; z < AT_Z; ++z)
         out[z] = 0.0;
     __syncthreads();
 
@@ -237,12 +250,15 @@ __global__ void __launch_bounds__(256) fpT_cone_kernel(Geom3D g, const ConeFPVie
     const float sx0 = (float)(x0 - 1), sx1 = (float)xe;
     const float sy0 = (float)(y0 - 1), sy1 = (float)ye;
     const float sz0 = (float)(z0 - 1), sz1 = (float)ze;
-    // biased floor coordinate -> accumulator cell: floor(X) - (x0 - 2) = (int)(X + 4) - (x0 + 2);
+    // biased floor coordinate -> accumulator cell: floor(X) - (x0 - 1) = (int)(X + 4) - (x0 + 3);
     // the cell's byte address is 4 (iz PZ + iy PY + ix) + base (modulo 2^32)
-    const unsigned base = 0u - 4u * (unsigned)((z0 + 2) * AT_PZ + (y0 + 2) * AT_PY + (x0 + 2));
+    const unsigned base = 4u * (unsigned)AT_ZERO - 4u * (unsigned)((z0 + 3) * AT_PZ + (y0 + 3) * AT_PY + (x0 + 3));
     const TI *pb = proj + (size_t)b * g.n_proj * g.nv * g.nu;
 
-    for (int k = 0; k < g.n_proj; ++k) {
+    // this workgroup's share of the views
+    const int k0 = (int)((long)g.n_proj * blockIdx.y / gridDim.y);
+    const int k1 = (int)((long)g.n_proj * (blockIdx.y + 1) / gridDim.y);
+    for (int k = k0; k < k1; ++k) {
         const ConeBPView bv = bviews[k];
         const float rw = rcp_nr(dot4(bv.r[2], bcx, bcy, bcz));
         const float cu = dot4(bv.r[0], bcx, bcy, bcz) * rw, cv = dot4(bv.r[1], bcx, bcy, bcz) * rw;
@@ -257,6 +273,7 @@ __global__ void __launch_bounds__(256) fpT_cone_kernel(Geom3D g, const ConeFPVie
         const ConeFPView &fv = fviews[k];
         const TI *qk = pb + (size_t)k * g.nv * g.nu;
         const int nfp = W * H;
+        const float rW = 1.0f / (float)W;
         for (int c0 = 0; c0 < nfp; c0 += AT_RAYS) {
             const int nc = min(AT_RAYS, nfp - c0);
             // set-up: this thread's footprint pixels of the pass
@@ -266,10 +283,12 @@ __global__ void __launch_bounds__(256) fpT_cone_kernel(Geom3D g, const ConeFPVie
 #pragma unroll
             for (int u = 0; u < AT_PER_THREAD; ++u) {
                 cnt[u] = 0;
-                const int idx = tid + 256 * u;
+                const int idx = tid + AT_T * u;
                 if (idx >= nc)
                     continue;
-                const int f = c0 + idx, ii = f / W, jj = f - ii * W;
+                // row and column of footprint pixel f (below 2^22 the rounded quotient is exact)
+                const int f = c0 + idx, ii = nfp < (1 << 22) ? (int)(((float)f + 0.5f) * rW) : f / W;
+                const int jj = f - ii * W;
                 const int i = i_lo + ii, j = j_lo + jj;
                 const float gv = load_f32(qk + (size_t)i * g.nu + j);
                 if (gv == 0.0f)
@@ -299,10 +318,10 @@ __global__ void __launch_bounds__(256) fpT_cone_kernel(Geom3D g, const ConeFPVie
             __syncthreads();
             // slots in descending order of sample count: bin AT_BINS - 1 - tid
             // starts after the rays of all longer bins
-            {
-                const int bin = AT_BINS - 1 - tid;
-                const int v = hist[bin];
-                int x = v;
+            const int bin = AT_BINS - 1 - tid;
+            int v = 0, x = 0;
+            if (tid < AT_BINS) {   // whole waves
+                v = x = hist[bin];
 #pragma unroll
                 for (int o = 1; o < 64; o <<= 1) {
                     const int y = __shfl_up(x, o);
@@ -311,12 +330,14 @@ __global__ void __launch_bounds__(256) fpT_cone_kernel(Geom3D g, const ConeFPVie
                 }
                 if (lane == 63)
                     s_wsum[wave] = x;
-                __syncthreads();
+            }
+            __syncthreads();
+            if (tid < AT_BINS) {
                 int off = 0;
                 for (int w = 0; w < wave; ++w)
                     off += s_wsum[w];
                 hist[bin] = off + x - v;
-                if (tid == 255)
+                if (tid == AT_BINS - 1)
                     s_nhit = off + x;
             }
             __syncthreads();
@@ -332,7 +353,10 @@ __global__ void __launch_bounds__(256) fpT_cone_kernel(Geom3D g, const ConeFPVie
             __syncthreads();
             const int nhit = s_nhit;
             // summed in a fixed order: the result does not depend on the waves' timing
-            const float bound = (s_wbound[0] + s_wbound[1]) + (s_wbound[2] + s_wbound[3]);
+            float bound = 0.0f;
+#pragma unroll
+            for (int w = 0; w < AT_T / 64; ++w)
+                bound += s_wbound[w];
             if (nhit > 0) {   // uniform
                 const float scale = AT_FIX / bound;
                 // the waves take 64-ray tasks in order of decreasing ray length
@@ -347,9 +371,13 @@ __global__ void __launch_bounds__(256) fpT_cone_kernel(Geom3D g, const ConeFPVie
                         continue;
                     const float4 A = s_ra[slot], E = s_rb[slot];
                     const float gs = A.w * scale;
-                    float fm = (float)__float_as_int(E.w);
-                    const float fend = fm + (float)s_cnt[slot];
-                    for (; fm < fend; fm += 1.0f) {
+                    // every lane walks its whole ray, starting an eighth of it later than the
+                    // lane before and wrapping round: neighbouring lanes hold neighbouring rays,
+                    // which in step would add to the same cells
+                    const int cnt_l = s_cnt[slot];
+                    const float f0 = (float)__float_as_int(E.w), f1 = f0 + (float)cnt_l;
+                    float fm = f0 + floorf((float)(lane & 7) * 0.125f * (float)cnt_l);
+                    for (int n = cnt_l; n > 0; --n, fm = fm + 1.0f < f1 ? fm + 1.0f : f0) {
                         // the projector's biased sample position (positive: near the support box)
                         const float X = fmaf(fm, E.x, A.x), Y = fmaf(fm, E.y, A.y), Z = fmaf(fm, E.z, A.z);
                         const unsigned ix = (unsigned)X, iy = (unsigned)Y, iz = (unsigned)Z;
@@ -377,17 +405,25 @@ __global__ void __launch_bounds__(256) fpT_cone_kernel(Geom3D g, const ConeFPVie
                 // fold this thread's cells into its FP64 sums and clear them
                 const double inv = 1.0 / (double)scale;
 #pragma unroll
-                for (int z = 0; z < AT_B; ++z) {
+                for (int z = 0; z < AT_Z; ++z) {
                     const int n = own + z * AT_PZ;
                     out[z] = fma((double)acc[n], inv, out[z]);
                     acc[n] = 0;
                 }
             }
-            hist[tid] = 0;
+            if (tid < AT_BINS)
+                hist[tid] = 0;
             if (tid == 0)
                 s_next = 0;
             __syncthreads();
         }
+    }
+    if (part) {   // a share of the views: the brick's partial sums, thread by thread
+        double *pp = part + ((size_t)blockIdx.y * gridDim.x + blockIdx.x) * (AT_B * AT_B * AT_B);
+#pragma unroll
+        for (int z = 0; z < AT_Z; ++z)
+            pp[z * AT_T + tid] = out[z];
+        return;
     }
     // write the brick's own voxels
     const size_t plane = (size_t)g.nx * g.ny;
@@ -395,10 +431,34 @@ __global__ void __launch_bounds__(256) fpT_cone_kernel(Geom3D g, const ConeFPVie
     const int ix = x0 + lx, iy = y0 + ly;
     if (ix < g.nx && iy < g.ny) {
 #pragma unroll
-        for (int z = 0; z < AT_B; ++z)
-            if (z0 + z < g.nz)
-                store_f32(vb + (size_t)(z0 + z) * plane + (size_t)iy * g.nx + ix, (float)((double)g.step * out[z]));
+        for (int z = 0; z < AT_Z; ++z)
+            if (z0 + lz + z < g.nz)
+                store_f32(vb + (size_t)(z0 + lz + z) * plane + (size_t)iy * g.nx + ix, (float)((double)g.step * out[z]));
     }
+}
+
+// Adds the shares' partial sums in order and writes the volume: one thread per
+// voxel of a brick, in the order the bricks' threads wrote them.
+template <typename T>
+__global__ void __launch_bounds__(256) fpT_cone_sum_kernel(Geom3D g, const double *__restrict__ part,
+                                                           T *__restrict__ vol, int nbx, int nby, int nbz, int shares,
+                                                           unsigned bricks)
+{
+    const unsigned brick = blockIdx.x / (AT_B * AT_B * AT_B / 256);
+    const int e = (int)(blockIdx.x % (AT_B * AT_B * AT_B / 256)) * 256 + threadIdx.x;
+    const int z = e / AT_T, t = e % AT_T;
+    const int bxi = (int)(brick % (unsigned)nbx), byi = (int)((brick / (unsigned)nbx) % (unsigned)nby);
+    const int bzb = (int)(brick / (unsigned)(nbx * nby));
+    const int ix = bxi * AT_B + t % AT_B, iy = byi * AT_B + (t / AT_B) % AT_B;
+    const int iz = bzb % nbz * AT_B + t / (AT_B * AT_B) * AT_Z + z;
+    if (ix >= g.nx || iy >= g.ny || iz >= g.nz)
+        return;
+    const size_t stride = (size_t)bricks * (AT_B * AT_B * AT_B);
+    const double *p = part + (size_t)brick * (AT_B * AT_B * AT_B) + e;
+    double sum = 0.0;
+    for (int s = 0; s < shares; ++s)
+        sum += p[s * stride];
+    store_f32(vol + (((size_t)(bzb / nbz) * g.nz + iz) * g.ny + iy) * g.nx + ix, (float)((double)g.step * sum));
 }
 
 // --------------------------------------------------------------- B^T, 2D
@@ -615,14 +675,19 @@ hipError_t fpT2d(bool fan, const Geom2D &g, const float2 *views, const void *sin
 
 template <typename T>
 hipError_t fpT_cone(const Geom3D &g, const ConeFPView *fviews, const ConeBPView *bviews, const void *proj, void *vol,
-                    int batch, hipStream_t s)
+                    int batch, double *part, int shares, hipStream_t s)
 {
     const int nbx = (g.nx + AT_B - 1) / AT_B, nby = (g.ny + AT_B - 1) / AT_B, nbz = (g.nz + AT_B - 1) / AT_B;
     const long blocks = (long)nbx * nby * nbz * batch;
     if (blocks > 0x7fffffffL)
         return hipErrorInvalidConfiguration;
-    hipLaunchKernelGGL((fpT_cone_kernel<T, T>), dim3((unsigned)blocks), dim3(256), 0, s, g, fviews, bviews,
-                       (const T *)proj, (T *)vol, nbx, nby, nbz);
+    hipLaunchKernelGGL((fpT_cone_kernel<T, T>), dim3((unsigned)blocks, (unsigned)shares), dim3(AT_T), 0, s, g, fviews,
+                       bviews, (const T *)proj, (T *)vol, shares > 1 ? part : nullptr, nbx, nby, nbz);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess || shares == 1)
+        return e;
+    hipLaunchKernelGGL(fpT_cone_sum_kernel<T>, dim3((unsigned)blocks * (AT_B * AT_B * AT_B / 256)), dim3(256), 0, s, g,
+                       part, (T *)vol, nbx, nby, nbz, shares, (unsigned)blocks);
     return hipGetLastError();
 }
 
@@ -664,14 +729,39 @@ hipError_t launch_project_adjoint_2d(int dtype, bool fan, const Geom2D &g, const
     }
 }
 
+static size_t at_bricks(const Geom3D &g, int batch)
+{
+    const size_t n = AT_B;
+    return ((size_t)g.nx + n - 1) / n * (((size_t)g.ny + n - 1) / n) * (((size_t)g.nz + n - 1) / n) * (size_t)batch;
+}
+
+// Shares of the views: 512 workgroups are resident at a time, and four times
+// as many even out their lengths (128^3, 124 views: 6.50, 6.28, 6.04 and
+// 5.97 ms for 1, 2, 3 and 4 shares of 512 bricks, with A), but a share of a
+// few views spends its time on partial sums (32^3, 360 views: 0.195, 0.209
+// and 0.248 ms for 64, 128 and 256 shares of 8 bricks).
+static int at_shares(const Geom3D &g, int batch)
+{
+    const size_t bricks = at_bricks(g, batch), most = bricks < 2048 ? 2048 / bricks : 1;
+    const size_t shares = most < (size_t)g.n_proj / 6 ? most : (size_t)g.n_proj / 6;
+    return shares > 1 ? (int)shares : 1;
+}
+
+size_t project_adjoint_scratch(const Geom3D &g, int batch)
+{
+    const int shares = at_shares(g, batch);
+    return shares > 1 ? at_bricks(g, batch) * (size_t)shares * (AT_B * AT_B * AT_B * sizeof(double)) : 0;
+}
+
 hipError_t launch_project_adjoint_cone(int dtype, const Geom3D &g, const ConeFPView *fviews,
                                        const ConeBPView *bviews, const void *proj, void *vol, int batch,
-                                       hipStream_t stream)
+                                       double *scratch, hipStream_t stream)
 {
+    const int shares = scratch ? at_shares(g, batch) : 1;
     switch (dtype) {
-    case 0: return fpT_cone<float>(g, fviews, bviews, proj, vol, batch, stream);
-    case 1: return fpT_cone<f16_t>(g, fviews, bviews, proj, vol, batch, stream);
-    default: return fpT_cone<bf16_t>(g, fviews, bviews, proj, vol, batch, stream);
+    case 0: return fpT_cone<float>(g, fviews, bviews, proj, vol, batch, scratch, shares, stream);
+    case 1: return fpT_cone<f16_t>(g, fviews, bviews, proj, vol, batch, scratch, shares, stream);
+    default: return fpT_cone<bf16_t>(g, fviews, bviews, proj, vol, batch, scratch, shares, stream);
     }
 }
 

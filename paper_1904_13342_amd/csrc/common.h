@@ -121,9 +121,12 @@ hipError_t static_scratch(void **ptr, size_t *bytes);
 // FP32 in and out (scatter with float atomics into a zero-filled output).
 hipError_t launch_project_adjoint_2d(int dtype, bool fan, const Geom2D &g, const float2 *views, const void *sino,
                                      void *img, int batch, hipStream_t stream);
+// scratch: project_adjoint_scratch() bytes for the partial sums of a small
+// volume's shares of the views, or NULL to take all views in one share.
+size_t project_adjoint_scratch(const Geom3D &g, int batch);
 hipError_t launch_project_adjoint_cone(int dtype, const Geom3D &g, const ConeFPView *fviews,
                                        const ConeBPView *bviews, const void *proj, void *vol, int batch,
-                                       hipStream_t stream);
+                                       double *scratch, hipStream_t stream);
 hipError_t launch_backproject_adjoint_2d(int in_dtype, bool fan, const Geom2D &g, const float2 *views,
                                          const void *img, float *sino, int batch, hipStream_t stream);
 // The output is zero-filled first.

@@ -150,7 +150,7 @@ def _traj(g, traj):
     return _host_traj(traj, (g.n_proj, 2))
 
 
-def _unary(fn, g, traj, x, in_tail, out_tail, out=None):
+def _unary(fn, g, traj, x, in_tail, out_tail, out=None, ws=None):
     batch = _dev(x, "input", in_tail)
     t = _traj(g, traj)
     shape = (tuple(x.shape[:1]) if x.dim() == len(in_tail) + 1 else ()) + tuple(out_tail)
@@ -158,8 +158,9 @@ def _unary(fn, g, traj, x, in_tail, out_tail, out=None):
         out = torch.empty(shape, dtype=x.dtype, device=x.device)
     elif tuple(out.shape) != shape or out.dtype != x.dtype or not out.is_contiguous() or out.device != x.device:
         raise ValueError("out has the wrong shape, dtype, device or layout")
+    scratch = () if ws is None else (ctypes.c_void_p(ws.data_ptr()), ws.numel())
     status = getattr(lib(), fn)(ctypes.byref(g), _fptr(t), ctypes.c_void_p(x.data_ptr()),
-                                ctypes.c_void_p(out.data_ptr()), batch, _DTYPES[x.dtype], _stream(x))
+                                ctypes.c_void_p(out.data_ptr()), *scratch, batch, _DTYPES[x.dtype], _stream(x))
     check(fn, status)
     return out
 
@@ -200,7 +201,13 @@ def project_adjoint_fan2d(g, ray_vecs, sino, out=None):
 
 
 def project_adjoint_cone3d(g, mats, proj, out=None):
-    return _unary("ph_project_adjoint_cone3d", g, mats, proj, _sino_tail(g), _vol_tail(g), out)
+    batch = _dev(proj, "input", _sino_tail(g))
+    nbytes = int(lib().ph_project_adjoint_workspace_bytes_3d(ctypes.byref(g), batch))
+    if nbytes == 0:
+        return _unary("ph_project_adjoint_cone3d", g, mats, proj, _sino_tail(g), _vol_tail(g), out)
+    # a small volume: its views are taken in shares whose partial sums meet in a workspace
+    ws = torch.empty(nbytes, dtype=torch.uint8, device=proj.device)
+    return _unary("ph_project_adjoint_ws_cone3d", g, mats, proj, _sino_tail(g), _vol_tail(g), out, ws)
 
 
 def _bpT(fn, g, traj, x, out):

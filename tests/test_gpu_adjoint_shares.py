@@ -1,0 +1,96 @@
+"""A^T of small volumes: the views taken in shares (workspace entry point, and
+the binding, which uses it) against all views in one share and against the
+FP64 oracle; bricks at the volume's edges, fewer views than shares, several
+items, half-precision storage."""
+import ctypes
+import math
+
+import numpy as np
+import pytest
+import torch
+
+import gpu_common as gc
+import synth
+from gpu_common import as_f32, check, say, to_dev, to_np
+
+pytestmark = pytest.mark.gpu
+
+# vol shape, detector, views
+CASES = {
+    "one_brick": ((16, 16, 16), (31, 33), 90),
+    "edges": ((17, 15, 33), (45, 47), 41),
+    "12_views": ((20, 20, 20), (40, 44), 12),
+    "11_views_one_share": ((20, 20, 20), (40, 44), 11),
+    "fine_rays": ((18, 19, 20), (120, 130), 13),
+}
+
+
+@pytest.fixture(scope="module")
+def ph():
+    gc.device()
+    import paper_1904_13342_amd as ph
+    return ph
+
+
+@pytest.mark.parametrize("name", list(CASES))
+def test_project_adjoint_shares(ph, ora, name):
+    vol, det, views = CASES[name]
+    # the detector covers the volume at any pixel count
+    d = 2.4 * max(vol) / det[1]
+    spec = synth.config("cone3d_crop32").with_(vol_shape=vol, vol_spacing=(1.0, 1.0, 1.0), det_shape=det,
+                                               det_spacing=(d, d), n_proj=views, sid=300.0, sdd=500.0)
+    g = ph.from_spec(spec)
+    mats = ph.projection_matrices_3d(g)
+    L = ph._lib.lib()
+    rng = np.random.default_rng(7)
+    p = as_f32(rng.uniform(0.5, 1.5, (2, views) + det))
+    pd = to_dev(p)
+    out = ph.project_adjoint_cone3d(g, mats, pd)
+    nbytes = L.ph_project_adjoint_workspace_bytes_3d(ctypes.byref(g), 2)
+    say(f"[A^T shares] {name}: workspace {nbytes} bytes")
+    assert (nbytes > 0) == (views >= 12)
+    check(to_np(out), np.stack([ora.project_adjoint(spec, v) for v in p]), name)
+    whole = torch.empty_like(out)
+    t = np.ascontiguousarray(mats, dtype=np.float32)
+    args = (ctypes.byref(g), t.ctypes.data_as(ctypes.POINTER(ctypes.c_float)), ctypes.c_void_p(pd.data_ptr()),
+            ctypes.c_void_p(whole.data_ptr()))
+    stream = ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    assert L.ph_project_adjoint_cone3d(*args, 2, 0, stream) == 0
+    torch.cuda.synchronize()
+    # FP64 sums in another order, rounded once to FP32
+    assert (out - whole).abs().max() <= 2.0 ** -23 * whole.abs().max()
+    if nbytes:
+        assert L.ph_project_adjoint_ws_cone3d(*args, None, 0, 2, 0, stream) == -5
+    half = ph.project_adjoint_cone3d(g, mats, pd.half())
+    ref = ph.project_adjoint_cone3d(g, mats, pd.half().float()).half()
+    assert (half.float() - ref.float()).abs().max() <= 2.0 ** -10 * ref.float().abs().max()
+
+
+def test_tv_workspace_without_room_for_shares(ph):
+    """A workspace of the loop's buffers alone is still accepted."""
+    spec = synth.config("cone3d_crop32").with_(vol_shape=(20, 20, 20), vol_spacing=(1.0, 1.0, 1.0), det_shape=(40, 44),
+                                               det_spacing=(1.2, 1.2), n_proj=24, sid=300.0, sdd=500.0,
+                                               angular_range=200 * math.pi / 180)
+    g = ph.from_spec(spec)
+    mats = ph.projection_matrices_3d(g)
+    gen = torch.Generator(device=gc.device()).manual_seed(3)
+    p = torch.rand((24, 40, 44), device=gc.device(), generator=gen)
+    runs = []
+    full = ph.tv_workspace_bytes(g, 1)
+    small = full - ph._lib.lib().ph_project_adjoint_workspace_bytes_3d(ctypes.byref(g), 1)
+    assert small < full
+    L = ph._lib.lib()
+    prm = ph._lib.TvParams(1e-3, 1e-2, 1e-2, 0.9, 0.999, 1e-8, 0)
+    t = np.ascontiguousarray(mats, dtype=np.float32)
+    for nbytes in (full, small):
+        x, m, v = (torch.zeros((20, 20, 20), device=gc.device()) for _ in range(3))
+        ws = torch.empty(nbytes, dtype=torch.uint8, device=gc.device())
+        st = L.ph_tv_iterate_cone3d(ctypes.byref(g), t.ctypes.data_as(ctypes.POINTER(ctypes.c_float)),
+                                    ctypes.c_void_p(p.data_ptr()), ctypes.c_void_p(x.data_ptr()),
+                                    ctypes.c_void_p(m.data_ptr()), ctypes.c_void_p(v.data_ptr()), 0, 1,
+                                    ctypes.byref(prm), ctypes.c_void_p(ws.data_ptr()), nbytes, None, 1,
+                                    ctypes.c_void_p(torch.cuda.current_stream().cuda_stream))
+        assert st == 0
+        torch.cuda.synchronize()
+        runs.append(m.clone())
+    assert (runs[0] - runs[1]).abs().max() <= 2.0 ** -22 * runs[0].abs().max()
