@@ -13,10 +13,11 @@
 //
 // The exact transpose B^T (below) mirrors this kernel.
 //
-// For a circular trajectory about z (AXIAL: the matrices have no z term in
-// the u and w rows) the column coordinate, the depth w and the weight are
-// constant along a column, and only the row coordinate moves with z: one FMA
-// per voxel.  General matrices take the per-voxel path, projected in FP64.
+// For a circular trajectory about z (axial: the matrices have no z term in the
+// u and w rows) the column coordinate, the depth w and the weight are constant
+// along a column, and only the row coordinate moves with z: one FMA per voxel.
+// General matrices project every voxel in FP64; they, and volumes of few
+// bricks, are taken by single waves without staging (bp_cone_wave_kernel).
 #include "device_util.h"
 
 namespace ph {
@@ -34,10 +35,13 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t det_row(const float *row, unsi
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(row), (short)0, (int)bytes, 0x00020000);
 }
 
+// pixel (i, j), zero outside the detector: read at the clamped index and masked
 template <typename TI>
 __device__ __forceinline__ float det_pix(const TI *q, int nu, int nv, int i, int j)
 {
-    return (i >= 0 && j >= 0 && i < nv && j < nu) ? load_f32(q + (size_t)i * nu + j) : 0.0f;
+    const int ci = min(max(i, 0), nv - 1), cj = min(max(j, 0), nu - 1);
+    const float v = load_f32(q + (size_t)ci * nu + cj);
+    return ci == i && cj == j ? v : 0.0f;
 }
 
 // bilinear fetch at tile-local coordinates, unit-stride columns
@@ -124,22 +128,38 @@ __device__ __forceinline__ float det_coord(float c, float centre)
 // precision from the FP64 rows: the cell (j, i) of its bilinear footprint
 // relative to (u_lo, v_lo) (a staged tile's corner, or 0 for the detector
 // itself), the fractions within the cell and the distance weight
-// (SID/w)^2.  Shared by B and B^T, so the pair sees bitwise the same
-// positions.
+// (SID/w)^2.  The rows' values at a column's (x, y) are formed once per view;
+// a voxel adds its z term and takes the reciprocal of its depth from the FP32
+// estimate and one Newton step (relative error below 1e-13, under 1e-10
+// pixel).  Shared by B and B^T, so the pair sees bitwise the same positions.
 struct DetPoint {
     int j, i;
     float fu, fv, wt;
 };
 
-__device__ __forceinline__ DetPoint general_point(const ConeBPView64 &v, const Geom3D &g, float xc, float yc,
-                                                  float zc, int u_lo, int v_lo)
+struct GeneralCol {
+    double u, v, w;      // the rows at (x, y, 0)
+    double dz[3];       // and their z terms
+};
+
+__device__ __forceinline__ GeneralCol general_col(const ConeBPView64 &v, float xc, float yc)
+{
+    GeneralCol c;
+    c.u = fma(v.r[0][0], (double)xc, fma(v.r[0][1], (double)yc, v.r[0][3]));
+    c.v = fma(v.r[1][0], (double)xc, fma(v.r[1][1], (double)yc, v.r[1][3]));
+    c.w = fma(v.r[2][0], (double)xc, fma(v.r[2][1], (double)yc, v.r[2][3]));
+    for (int a = 0; a < 3; ++a)
+        c.dz[a] = v.r[a][2];
+    return c;
+}
+
+__device__ __forceinline__ DetPoint general_point(const GeneralCol &c, const Geom3D &g, float zc, int u_lo, int v_lo)
 {
 #pragma clang fp contract(off)
-    const double x = xc, y = yc, z = zc;
-    const double U = fma(v.r[0][0], x, fma(v.r[0][1], y, fma(v.r[0][2], z, v.r[0][3])));
-    const double V = fma(v.r[1][0], x, fma(v.r[1][1], y, fma(v.r[1][2], z, v.r[1][3])));
-    const double W = fma(v.r[2][0], x, fma(v.r[2][1], y, fma(v.r[2][2], z, v.r[2][3])));
-    const double rW = 1.0 / W;
+    const double z = zc;
+    const double U = fma(c.dz[0], z, c.u), V = fma(c.dz[1], z, c.v), W = fma(c.dz[2], z, c.w);
+    const double r0 = (double)__builtin_amdgcn_rcpf((float)W);
+    const double rW = fma(r0, fma(-W, r0, 1.0), r0);
     const double su = fma(U, rW, (double)g.cu - (double)u_lo);
     const double sv = fma(V, rW, (double)g.cv - (double)v_lo);
     const double fsu = floor(su), fsv = floor(sv);
@@ -163,9 +183,8 @@ __device__ __forceinline__ float bilerp_cell(const TI *q, const Geom3D &g, int j
     return fmaf(fv, a1 - a0, a0);
 }
 
-template <typename T, typename TI, int BP_NZ, bool AXIAL>
+template <typename T, typename TI, int BP_NZ>
 __global__ void __launch_bounds__(256) bp_cone_kernel(Geom3D g, const ConeBPView *__restrict__ views,
-                                                      const ConeBPView64 *__restrict__ views64,
                                                       const TI *__restrict__ proj, T *__restrict__ vol, int nbx,
                                                       int nby, int nzb, int accumulate)
 {
@@ -237,53 +256,39 @@ __global__ void __launch_bounds__(256) bp_cone_kernel(Geom3D g, const ConeBPView
         }
         if (!active)
             continue;
-        if (AXIAL) {
-            const AxialCol ac = axial_col(v, g.sid, xc, yc, zc0);
-            const float wt = ac.wt, dvz = ac.dvz;
-            if (staged) {
-                // tile-local coordinates are >= 1 (one-pixel margin): floor == truncation
-                const float su = tile_coord(ac.uc, g.cu, u_lo);
-                const float sv0 = tile_coord(ac.vc0, g.cv, v_lo);
-                const int iu = (int)su;
-                const float fu = __builtin_amdgcn_fractf(su);
-                const float *col = tile + iu;
-                if (zcount == BP_NZ) {
+        const AxialCol ac = axial_col(v, g.sid, xc, yc, zc0);
+        const float wt = ac.wt, dvz = ac.dvz;
+        if (staged) {
+            // tile-local coordinates are >= 1 (one-pixel margin): floor == truncation
+            const float su = tile_coord(ac.uc, g.cu, u_lo);
+            const float sv0 = tile_coord(ac.vc0, g.cv, v_lo);
+            const int iu = (int)su;
+            const float fu = __builtin_amdgcn_fractf(su);
+            const float *col = tile + iu;
+            if (zcount == BP_NZ) {
 #pragma unroll
-                    for (int z = 0; z < BP_NZ; ++z) {
-                        const float sv = fmaf((float)z, dvz, sv0);
-                        const int iv = (int)sv;
-                        acc[z] = fmaf(wt, bilerp_tile(col + iv * BP_TS, fu, __builtin_amdgcn_fractf(sv)), acc[z]);
-                    }
-                } else {
-#pragma unroll
-                    for (int z = 0; z < BP_NZ; ++z) {
-                        if (z < zcount) {
-                            const float sv = fmaf((float)z, dvz, sv0);
-                            const int iv = (int)sv;
-                            acc[z] = fmaf(wt, bilerp_tile(col + iv * BP_TS, fu, __builtin_amdgcn_fractf(sv)),
-                                          acc[z]);
-                        }
-                    }
+                for (int z = 0; z < BP_NZ; ++z) {
+                    const float sv = fmaf((float)z, dvz, sv0);
+                    const int iv = (int)sv;
+                    acc[z] = fmaf(wt, bilerp_tile(col + iv * BP_TS, fu, __builtin_amdgcn_fractf(sv)), acc[z]);
                 }
             } else {
-                const float su = det_coord(ac.uc, g.cu), sv0 = det_coord(ac.vc0, g.cv);
 #pragma unroll
-                for (int z = 0; z < BP_NZ; ++z)
-                    if (z < zcount)
-                        acc[z] = fmaf(wt, bilerp_global(qk, g, su, fmaf((float)z, dvz, sv0)), acc[z]);
-            }
-        } else {
-            const ConeBPView64 &v64 = views64[k];
-#pragma unroll
-            for (int z = 0; z < BP_NZ; ++z) {
-                if (z < zcount) {
-                    const DetPoint d =
-                        general_point(v64, g, xc, yc, zc0 + (float)z, staged ? u_lo : 0, staged ? v_lo : 0);
-                    const float val = staged ? bilerp_tile(tile + d.i * BP_TS + d.j, d.fu, d.fv)
-                                             : bilerp_cell(qk, g, d.j, d.i, d.fu, d.fv);
-                    acc[z] = fmaf(d.wt, val, acc[z]);
+                for (int z = 0; z < BP_NZ; ++z) {
+                    if (z < zcount) {
+                        const float sv = fmaf((float)z, dvz, sv0);
+                        const int iv = (int)sv;
+                        acc[z] = fmaf(wt, bilerp_tile(col + iv * BP_TS, fu, __builtin_amdgcn_fractf(sv)),
+                                      acc[z]);
+                    }
                 }
             }
+        } else {
+            const float su = det_coord(ac.uc, g.cu), sv0 = det_coord(ac.vc0, g.cv);
+#pragma unroll
+            for (int z = 0; z < BP_NZ; ++z)
+                if (z < zcount)
+                    acc[z] = fmaf(wt, bilerp_global(qk, g, su, fmaf((float)z, dvz, sv0)), acc[z]);
         }
     }
     if (!active)
@@ -294,6 +299,122 @@ __global__ void __launch_bounds__(256) bp_cone_kernel(Geom3D g, const ConeBPView
         if (z < zcount) {
             T *p = out + (size_t)(z0 + z) * g.ny * g.nx;
             // accumulate: add to the volume (a later share of the views)
+            store_f32(p, accumulate ? load_f32(p) + g.dbeta * acc[z] : g.dbeta * acc[z]);
+        }
+    }
+}
+
+// The same operator for volumes whose bricks would not fill the GPU: a wave
+// owns 8 x 8 columns of WV_NZ voxels and takes one view at a time, reading the
+// projections directly (they stay in L2; the 64 lanes read a dozen
+// neighbouring pixels of a row or two).  The W waves of a workgroup share the
+// columns, wave w taking views w, w + W, ..., and meet in LDS in a fixed order.
+// Where every cell of the wave lies on the detector, a cell is read as two
+// pairs at 32-bit offsets from the view; elsewhere pixel by pixel, masked.
+// Bound by the scattered loads for circular views (256^3: 36 lane slots per
+// update, against 13 in bricks) and by FP64 for general ones.  32^3, 200
+// views: 637 us in bricks, 24 by waves; 64^3, 62 views 206 and 23 us; four
+// voxels per column against two and eight: 24, 20 and 43 us at 32^3, 2.19, 2.25
+// and 2.68 ms at 256^3 with 124 general views.
+constexpr int WV_NZ = 4;
+
+template <typename T, typename TI, bool AXIAL>
+__global__ void __launch_bounds__(1024) bp_cone_wave_kernel(Geom3D g, const ConeBPView *__restrict__ views,
+                                                            const ConeBPView64 *__restrict__ views64,
+                                                            const TI *__restrict__ proj, T *__restrict__ vol, int ntx,
+                                                            int nty, int ntz, int nz_seg, int accumulate)
+{
+    extern __shared__ float part[];   // WV_NZ per thread, for more than one wave
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int waves = blockDim.x >> 6;
+    const unsigned lin = blockIdx.x;
+    const int tx = (int)(lin % (unsigned)ntx), ty = (int)((lin / (unsigned)ntx) % (unsigned)nty);
+    const int tzb = (int)(lin / ((unsigned)ntx * (unsigned)nty));
+    const int z0 = tzb % ntz * WV_NZ, b = tzb / ntz;
+    const int ix = tx * 8 + (lane & 7), iy = ty * 8 + (lane >> 3);
+    // lanes outside the volume repeat its border (and are not stored)
+    const float xc = (float)min(ix, g.nx - 1) - 0.5f * (g.nx - 1), yc = (float)min(iy, g.ny - 1) - 0.5f * (g.ny - 1);
+    // rows are counted from the first voxel of the brick that the transpose
+    // takes this voxel in, so that the pair's coordinates round alike
+    const int zoff = z0 % nz_seg;
+    const float zc0 = (float)z0 - 0.5f * (g.nz - 1), zcb = (float)(z0 - zoff) - 0.5f * (g.nz - 1);
+    const TI *pb = proj + (size_t)b * g.n_proj * g.nv * g.nu;
+    float acc[WV_NZ];
+#pragma unroll
+    for (int z = 0; z < WV_NZ; ++z)
+        acc[z] = 0.0f;
+    for (int k = wave; k < g.n_proj; k += waves) {
+        const TI *qk = pb + (size_t)k * g.nv * g.nu, *qk1 = qk + g.nu;
+        int j[WV_NZ], i[WV_NZ];
+        float fu[WV_NZ], fv[WV_NZ], wt[WV_NZ];
+        bool inside = (size_t)g.nv * g.nu * sizeof(TI) <= 0xffffffffu;
+        if (AXIAL) {
+            const AxialCol ac = axial_col(views[k], g.sid, xc, yc, zcb);
+            const float su = det_coord(ac.uc, g.cu), sv0 = det_coord(ac.vc0, g.cv);
+            const float ju = floorf(su), iv = floorf(sv0);
+#pragma unroll
+            for (int z = 0; z < WV_NZ; ++z) {
+                // relative to the first row, so that the fraction keeps its bits
+                const float sv = fmaf((float)(zoff + z), ac.dvz, sv0 - iv), fl = floorf(sv);
+                j[z] = (int)ju;
+                fu[z] = su - ju;
+                i[z] = (int)iv + (int)fl;
+                fv[z] = sv - fl;
+                wt[z] = ac.wt;
+            }
+        } else {
+            const GeneralCol col = general_col(views64[k], xc, yc);
+#pragma unroll
+            for (int z = 0; z < WV_NZ; ++z) {
+                const DetPoint d = general_point(col, g, zc0 + (float)min(z, g.nz - 1 - z0), 0, 0);
+                j[z] = d.j;
+                i[z] = d.i;
+                fu[z] = d.fu;
+                fv[z] = d.fv;
+                wt[z] = d.wt;
+            }
+        }
+#pragma unroll
+        for (int z = 0; z < WV_NZ; ++z)
+            inside = inside && (unsigned)j[z] < (unsigned)(g.nu - 1) && (unsigned)i[z] < (unsigned)(g.nv - 1);
+        if (__all(inside)) {
+            float2 p[WV_NZ], q[WV_NZ];
+#pragma unroll
+            for (int z = 0; z < WV_NZ; ++z) {
+                const unsigned off = ((unsigned)i[z] * (unsigned)g.nu + (unsigned)j[z]) * (unsigned)sizeof(TI);
+                p[z] = load_pair(qk, off);
+                q[z] = load_pair(qk1, off);
+            }
+#pragma unroll
+            for (int z = 0; z < WV_NZ; ++z) {
+                const float a0 = fmaf(fu[z], p[z].y - p[z].x, p[z].x), a1 = fmaf(fu[z], q[z].y - q[z].x, q[z].x);
+                acc[z] = fmaf(wt[z], fmaf(fv[z], a1 - a0, a0), acc[z]);
+            }
+        } else {
+#pragma unroll
+            for (int z = 0; z < WV_NZ; ++z)
+                acc[z] = fmaf(wt[z], bilerp_cell(qk, g, j[z], i[z], fu[z], fv[z]), acc[z]);
+        }
+    }
+    if (waves > 1) {
+#pragma unroll
+        for (int z = 0; z < WV_NZ; ++z)
+            part[z * blockDim.x + threadIdx.x] = acc[z];
+        __syncthreads();
+        if (wave > 0)
+            return;
+        for (int w = 1; w < waves; ++w)
+#pragma unroll
+            for (int z = 0; z < WV_NZ; ++z)
+                acc[z] += part[z * blockDim.x + w * 64 + lane];
+    }
+    if (ix >= g.nx || iy >= g.ny)
+        return;
+    T *out = vol + ((size_t)b * g.nz + z0) * g.ny * g.nx + (size_t)iy * g.nx + ix;
+#pragma unroll
+    for (int z = 0; z < WV_NZ; ++z) {
+        if (z0 + z < g.nz) {
+            T *p = out + (size_t)z * g.ny * g.nx;
             store_f32(p, accumulate ? load_f32(p) + g.dbeta * acc[z] : g.dbeta * acc[z]);
         }
     }
@@ -479,7 +600,10 @@ __global__ void __launch_bounds__(256) bpT_axial_kernel(Geom3D g, const ConeBPVi
         return;   // the brick adds nothing (uniform)
     clear_tile(tile, tid);   // ordered before the first splat by the view loop's barrier
 
-    for (int k = 0; k < g.n_proj; ++k) {
+    // this workgroup's share of the views
+    const int k0 = (int)((long)g.n_proj * blockIdx.y / gridDim.y);
+    const int k1 = (int)((long)g.n_proj * (blockIdx.y + 1) / gridDim.y);
+    for (int k = k0; k < k1; ++k) {
         const ConeBPView v = views[k];
         // rays mostly along x (depth row dominated by x): put the lanes along y
         const int orient = fabsf(v.r[2][0]) >= fabsf(v.r[2][1]) ? 0 : 1;
@@ -588,7 +712,10 @@ __global__ void __launch_bounds__(256) bpT_general_kernel(Geom3D g, const ConeBP
     float *pb = proj + (size_t)b * g.n_proj * g.nv * g.nu;
     clear_tile(tile, tid);   // ordered before the first splat by the view loop's barrier
 
-    for (int k = 0; k < g.n_proj; ++k) {
+    // this workgroup's share of the views
+    const int k0 = (int)((long)g.n_proj * blockIdx.y / gridDim.y);
+    const int k1 = (int)((long)g.n_proj * (blockIdx.y + 1) / gridDim.y);
+    for (int k = k0; k < k1; ++k) {
         const ConeBPView v = views[k];
         const Footprint fp = brick_footprint(v, g, cx, cy, cz);
         const bool staged = fp.tw <= BP_TW && fp.th <= BP_TH;
@@ -597,11 +724,11 @@ __global__ void __launch_bounds__(256) bpT_general_kernel(Geom3D g, const ConeBP
         if (staged)
             __syncthreads();   // the previous tile has been flushed and cleared
         if (active) {
-            const ConeBPView64 &v64 = views64[k];
+            const GeneralCol col = general_col(views64[k], xc, yc);
 #pragma unroll
             for (int z = 0; z < BP_NZ; ++z) {
                 if (z < zcount) {
-                    const DetPoint d = general_point(v64, g, xc, yc, zc0 + (float)z, staged ? fp.u_lo : 0,
+                    const DetPoint d = general_point(col, g, zc0 + (float)z, staged ? fp.u_lo : 0,
                                                      staged ? fp.v_lo : 0);
                     if (staged)
                         splat_tile(tile + d.i * BPT_TS + d.j, d.wt * scale * val[z], d.fu, d.fv, BPT_TS);
@@ -618,17 +745,13 @@ __global__ void __launch_bounds__(256) bpT_general_kernel(Geom3D g, const ConeBP
 }
 
 template <typename T, typename TI, int NZ>
-hipError_t bp_cone_nz(const Geom3D &g, const ConeBPView *views, const ConeBPView64 *views64, bool axial,
-                      const void *proj, void *vol, int batch, int acc, hipStream_t s)
+hipError_t bp_cone_nz(const Geom3D &g, const ConeBPView *views, const void *proj, void *vol, int batch, int acc,
+                      hipStream_t s)
 {
     const int nbx = (g.nx + 15) / 16, nby = (g.ny + 15) / 16, nzb = (g.nz + NZ - 1) / NZ;
     const unsigned blocks = (unsigned)(nbx * nby * nzb * batch);
-    if (axial)
-        hipLaunchKernelGGL((bp_cone_kernel<T, TI, NZ, true>), dim3(blocks), dim3(256), 0, s, g, views,
-                           (const ConeBPView64 *)nullptr, (const TI *)proj, (T *)vol, nbx, nby, nzb, acc);
-    else
-        hipLaunchKernelGGL((bp_cone_kernel<T, TI, NZ, false>), dim3(blocks), dim3(256), 0, s, g, views, views64,
-                           (const TI *)proj, (T *)vol, nbx, nby, nzb, acc);
+    hipLaunchKernelGGL((bp_cone_kernel<T, TI, NZ>), dim3(blocks), dim3(256), 0, s, g, views, (const TI *)proj,
+                       (T *)vol, nbx, nby, nzb, acc);
     return hipGetLastError();
 }
 
@@ -638,9 +761,32 @@ hipError_t bp_cone(const Geom3D &g, const ConeBPView *views, const ConeBPView64 
 {
     if (!axial && !views64)
         return hipErrorInvalidValue;
-    if (nz_seg >= 32)
-        return bp_cone_nz<T, TI, 32>(g, views, views64, axial, proj, vol, batch, acc, s);
-    return bp_cone_nz<T, TI, 16>(g, views, views64, axial, proj, vol, batch, acc, s);
+    // Bricks are worth their staging once there are two for each CU: circular
+    // views, 128^3 (256 bricks, 124 views) 470 us in bricks and 254 by waves,
+    // 176^3 (726 bricks, 133 views) 568 and 687 us.  General views spend their
+    // time in FP64 and are taken by waves at every size: 256^3, 124 views 2.47
+    // and 2.19 ms, 512^3, 30 views 4.29 and 4.25 ms.
+    const long bricks = (long)((g.nx + 15) / 16) * ((g.ny + 15) / 16) * ((g.nz + nz_seg - 1) / nz_seg) * batch;
+    if (axial && bricks >= 512)
+        return nz_seg >= 32 ? bp_cone_nz<T, TI, 32>(g, views, proj, vol, batch, acc, s)
+                            : bp_cone_nz<T, TI, 16>(g, views, proj, vol, batch, acc, s);
+    const int ntx = (g.nx + 7) / 8, nty = (g.ny + 7) / 8, ntz = (g.nz + WV_NZ - 1) / WV_NZ;
+    const long tiles = (long)ntx * nty * ntz * batch;
+    if (tiles > 0x7fffffffL)
+        return hipErrorInvalidConfiguration;
+    // at least 64 waves per CU in all, four views each
+    int waves = 1;
+    while (waves < 16 && tiles * waves < 16384 && 4 * waves <= g.n_proj)
+        waves *= 2;
+    const dim3 grid((unsigned)tiles), block(64 * waves);
+    const size_t lds = waves > 1 ? (size_t)WV_NZ * 64 * waves * sizeof(float) : 0;
+    if (axial)
+        hipLaunchKernelGGL((bp_cone_wave_kernel<T, TI, true>), grid, block, lds, s, g, views,
+                           (const ConeBPView64 *)nullptr, (const TI *)proj, (T *)vol, ntx, nty, ntz, nz_seg, acc);
+    else
+        hipLaunchKernelGGL((bp_cone_wave_kernel<T, TI, false>), grid, block, lds, s, g, views, views64,
+                           (const TI *)proj, (T *)vol, ntx, nty, ntz, nz_seg, acc);
+    return hipGetLastError();
 }
 
 }  // namespace
@@ -669,7 +815,17 @@ hipError_t bpT_cone(const Geom3D &g, const ConeBPView *views, const ConeBPView64
         return hipErrorInvalidValue;
     const int NZ = nz_seg >= 32 ? 32 : 16;
     const int nbx = (g.nx + 15) / 16, nby = (g.ny + 15) / 16, nzb = (g.nz + NZ - 1) / NZ;
-    const dim3 grid((unsigned)(nbx * nby * nzb * batch));
+    const long bricks = (long)nbx * nby * nzb * batch;
+    // Shares of the views, which have projections of their own: a small volume
+    // has few bricks, and a larger one a last round of workgroups that is
+    // partly empty.  Up to 8192 workgroups of at least six views: 61 x 64 x 67,
+    // 62 views: 300 -> 53 us; with the back-projection, 128^3, 124 views 1068 ->
+    // 825 us (B^T alone 377), 200^3, 193 views 3.26 -> 2.74 ms, 256^3, 248 views
+    // 6.97 -> 6.69 ms (4096 and 16384 workgroups: 2.80 and 2.81, 6.75 and 6.75).
+    long shares = bricks < 8192 ? 8192 / bricks : 1;
+    if (shares > g.n_proj / 6)
+        shares = g.n_proj / 6 > 1 ? g.n_proj / 6 : 1;
+    const dim3 grid((unsigned)bricks, (unsigned)shares);
     const TI *v = (const TI *)vol;
     if (NZ == 32) {
         if (axial)

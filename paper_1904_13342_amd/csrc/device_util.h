@@ -5,6 +5,17 @@
 
 namespace ph {
 
+// Two neighbouring elements in one load (the pair is aligned like its element).
+template <typename T>
+__device__ __forceinline__ float2 load_pair(const T *base, unsigned bytes)
+{
+    struct Pair {
+        T a, b;
+    } p;
+    __builtin_memcpy(&p, (const char *)base + (size_t)bytes, sizeof p);
+    return make_float2(load_f32(&p.a), load_f32(&p.b));
+}
+
 // Index coordinates (x, y, z) of a ray's anchor (its point closest to the
 // isocentre) and of one sampling step: sample m sits at p + m * e.
 struct Ray {

@@ -17,17 +17,6 @@ __device__ __forceinline__ float pix(const T *img, int nx, int ny, int ix, int i
     return cx == ix && cy == iy ? v : 0.0f;
 }
 
-// Two neighbouring elements in one load (the pair is aligned like its element).
-template <typename T>
-__device__ __forceinline__ float2 load_pair(const T *base, unsigned bytes)
-{
-    struct Pair {
-        T a, b;
-    } p;
-    __builtin_memcpy(&p, (const char *)base + (size_t)bytes, sizeof p);
-    return make_float2(load_f32(&p.a), load_f32(&p.b));
-}
-
 constexpr int UNROLL2D = 4;   // samples (A) or views (B) per lane whose loads are in flight together
 
 // Narrow [lo, hi] to the sample range inside the open interval (a, b) of

@@ -94,3 +94,16 @@ def test_tv_workspace_without_room_for_shares(ph):
         torch.cuda.synchronize()
         runs.append(m.clone())
     assert (runs[0] - runs[1]).abs().max() <= 2.0 ** -22 * runs[0].abs().max()
+
+
+@pytest.mark.parametrize("views", [5, 6, 11, 12, 13, 100])
+@pytest.mark.parametrize("batch", [1, 3])
+def test_backproject_adjoint_shares(ph, ora, views, batch):
+    """B^T with its views dealt to one, two or many workgroups of a brick."""
+    spec = synth.config("cone3d_crop32").with_(vol_shape=(33, 17, 18), vol_spacing=(1.0, 1.0, 1.0), det_shape=(70, 45),
+                                               det_spacing=(1.1, 1.2), n_proj=views, sid=300.0, sdd=500.0)
+    g = ph.from_spec(spec)
+    f = as_f32(np.random.default_rng(9).uniform(0.5, 1.5, (batch,) + spec.vol_shape))
+    say(f"[B^T shares] {views} views, batch {batch}")
+    check(to_np(ph.backproject_adjoint_cone3d(g, ph.projection_matrices_3d(g), to_dev(f))),
+          np.stack([ora.backproject_adjoint(spec, v) for v in f]), "B^T")
