@@ -37,6 +37,7 @@ struct Entry {
     int device;
     std::string key;
     void *ptr;
+    int tag;   // what a build has to say about its table (0 if nothing)
 };
 std::mutex g_mu;
 std::vector<std::shared_ptr<Entry>> g_cache;
@@ -54,8 +55,9 @@ struct CallScope {
     }
 };
 
-template <typename Build>
-const void *cached(const std::string &key, Build build, int *status)
+// The table of `key` on the current device, pinned for the call; NULL if it is
+// not there (or on a HIP error, which sets *status).
+const void *find_table(const std::string &key, int *status, int *tag = nullptr)
 {
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess) {
@@ -63,14 +65,30 @@ const void *cached(const std::string &key, Build build, int *status)
         return nullptr;
     }
     std::lock_guard<std::mutex> lock(g_mu);
-    for (size_t n = 0; n < g_cache.size(); ++n) {
+    for (size_t n = g_cache.size(); n-- > 0;) {
         if (g_cache[n]->device == dev && g_cache[n]->key == key) {
             std::shared_ptr<Entry> e = g_cache[n];
             g_cache.erase(g_cache.begin() + (long)n);
             g_cache.push_back(e);
             t_pins.push_back(e);
+            if (tag)
+                *tag = e->tag;
             return e->ptr;
         }
+    }
+    return nullptr;
+}
+
+template <typename Build>
+const void *cached(const std::string &key, Build build, int *status, int tag = 0)
+{
+    const void *found = find_table(key, status);
+    if (found || *status != PH_OK)
+        return found;
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess) {
+        *status = PH_ERR_HIP;
+        return nullptr;
     }
     std::vector<unsigned char> host = build();
     void *p = nullptr;
@@ -83,6 +101,9 @@ const void *cached(const std::string &key, Build build, int *status)
         *status = PH_ERR_HIP;
         return nullptr;
     }
+    std::lock_guard<std::mutex> lock(g_mu);
+    // another thread may have built the same table meanwhile: both stay valid,
+    // the older one ages out
     if (g_cache.size() >= kMaxEntries) {
         // the least recently used table that no thread has pinned (hipFree
         // waits for outstanding work that may still read it)
@@ -94,7 +115,7 @@ const void *cached(const std::string &key, Build build, int *status)
             }
         }
     }
-    auto e = std::make_shared<Entry>(Entry{dev, key, p});
+    auto e = std::make_shared<Entry>(Entry{dev, key, p, tag});
     g_cache.push_back(e);
     t_pins.push_back(e);
     return p;
@@ -534,95 +555,137 @@ const float *wred_table(int kind, int n_proj, int nu, double du, double range, d
 
 int to_status(hipError_t e) { return e == hipSuccess ? PH_OK : PH_ERR_HIP; }
 
-// Host-only validation of a 2D call's geometry and ray vectors.
-int validate2d(const ph_geom2d *g, bool fan, const float *rv)
-{
+// The trajectory of a call.  A table is only ever uploaded for a trajectory
+// that passed validation, and it is found by the exact bytes of the geometry
+// and the ray vectors or matrices, so finding it stands for validating them
+// again: per view that is a matrix inverse, three norms and eight corners,
+// which a call on a known trajectory should not pay for.
+struct Traj2D {
     Geom2D G;
-    int st = make_geom2d(g, fan, &G);
+    std::string key;
+    std::vector<float2> v;            // empty if the table was found
+    const float2 *views = nullptr;
+};
+
+// Validation of a 2D call's geometry and ray vectors; uploads nothing.
+int check2d(const ph_geom2d *g, bool fan, const float *rv, Traj2D *t)
+{
+    int st = make_geom2d(g, fan, &t->G);
     if (st != PH_OK)
         return st;
     if (!rv)
         return PH_ERR_NULL;
-    std::vector<float2> v;
-    return views2d(g, fan, rv, &v);
+    t->key = fan ? "v2f" : "v2p";
+    append(t->key, g, 1);
+    append(t->key, rv, 2 * (size_t)g->n_proj);
+    t->views = (const float2 *)find_table(t->key, &st);
+    return t->views ? PH_OK : views2d(g, fan, rv, &t->v);   // (a HIP error shows when the table is uploaded)
 }
 
-int prep2d(const ph_geom2d *g, bool fan, const float *rv, Geom2D *G, const float2 **views)
+// Table of a checked 2D trajectory (uploaded on first use).
+int table2d(Traj2D *t)
 {
-    int st = make_geom2d(g, fan, G);
-    if (st != PH_OK)
-        return st;
-    if (!rv)
-        return PH_ERR_NULL;
-    std::vector<float2> v;
-    st = views2d(g, fan, rv, &v);
-    if (st != PH_OK)
-        return st;
-    std::string key = fan ? "v2f" : "v2p";
-    append(key, g, 1);
-    append(key, rv, 2 * (size_t)g->n_proj);
-    st = PH_OK;
-    *views = (const float2 *)cached(key, [&] { return as_bytes(v); }, &st);
+    int st = PH_OK;
+    if (!t->views)
+        t->views = (const float2 *)cached(t->key, [&] { return as_bytes(t->v); }, &st);
     return st;
 }
 
-// Host-only validation of a 3D call's geometry and matrices.
-int validate3d(const ph_geom3d *g, const float *mats, Geom3D *G, std::vector<double> *P)
+struct Traj3D {
+    Geom3D G;
+    const ph_geom3d *g = nullptr;
+    const float *mats = nullptr;
+    std::vector<double> P;            // normalised matrices, formed when first needed
+    const ConeFPView *fp = nullptr;
+    const ConeBPView *bp = nullptr;
+    bool axial = false;
+
+    std::string key(bool for_bp) const
+    {
+        std::string k = for_bp ? "bp3" : "fp3";
+        k.reserve(k.size() + sizeof *g + 12 * (size_t)g->n_proj * sizeof *mats);
+        append(k, g, 1);
+        append(k, mats, 12 * (size_t)g->n_proj);
+        return k;
+    }
+    const ConeBPView64 *bp64() const
+    {
+        // the FP64 rows that follow the FP32 ones of a trajectory that is not a rotation about z
+        return axial ? nullptr : reinterpret_cast<const ConeBPView64 *>(bp + g->n_proj);
+    }
+};
+
+// Validation of a 3D call's geometry and matrices; uploads nothing, finds the
+// back-projector's (for_bp) or the projector's table if it is there.
+int check3d(const ph_geom3d *g, const float *mats, bool for_bp, Traj3D *t)
 {
-    int st = make_geom3d(g, G);
+    int st = make_geom3d(g, &t->G);
     if (st != PH_OK)
         return st;
     if (!mats)
         return PH_ERR_NULL;
-    return normalised_mats(g, mats, P);
+    t->g = g;
+    t->mats = mats;
+    int tag = 0;
+    const void *p = find_table(t->key(for_bp), &st, &tag);
+    if (!p)   // (a HIP error shows when the table is uploaded)
+        return normalised_mats(g, mats, &t->P);
+    if (for_bp) {
+        t->bp = (const ConeBPView *)p;
+        t->axial = tag != 0;
+    } else {
+        t->fp = (const ConeFPView *)p;
+    }
+    return PH_OK;
 }
 
-// Per-view tables of a validated 3D call (uploaded on first use).
-int upload3d(const ph_geom3d *g, const float *mats, const std::vector<double> &P, bool for_bp, const void **views,
-             bool *axial)
+// Tables of a checked 3D trajectory (uploaded on first use).
+int tables3d(Traj3D *t, bool for_bp)
 {
-    std::string key = for_bp ? "bp3" : "fp3";
-    append(key, g, 1);
-    append(key, mats, 12 * (size_t)g->n_proj);
+    if (for_bp ? t->bp != nullptr : t->fp != nullptr)
+        return PH_OK;
     int st = PH_OK;
+    const std::string key = t->key(for_bp);
+    if (t->P.empty()) {
+        int tag = 0;
+        const void *p = find_table(key, &st, &tag);
+        if (st != PH_OK)
+            return st;
+        if (p) {
+            if (for_bp) {
+                t->bp = (const ConeBPView *)p;
+                t->axial = tag != 0;
+            } else {
+                t->fp = (const ConeFPView *)p;
+            }
+            return PH_OK;
+        }
+        st = normalised_mats(t->g, t->mats, &t->P);
+        if (st != PH_OK)
+            return st;
+    }
     if (for_bp) {
         std::vector<ConeBPView> v;
         std::vector<ConeBPView64> v64;
-        bp_views(g, P, &v, axial, &v64);
-        *views = cached(
+        bp_views(t->g, t->P, &v, &t->axial, &v64);
+        t->bp = (const ConeBPView *)cached(
             key,
             [&] {
                 // the FP64 rows follow the FP32 ones for the general (per-voxel) paths
                 std::vector<unsigned char> b = as_bytes(v);
-                if (!*axial) {
+                if (!t->axial) {
                     const std::vector<unsigned char> b64 = as_bytes(v64);
                     b.insert(b.end(), b64.begin(), b64.end());
                 }
                 return b;
             },
-            &st);
+            &st, t->axial ? 1 : 0);
     } else {
         std::vector<ConeFPView> v;
-        fp_views(g, P, &v);
-        *views = cached(key, [&] { return as_bytes(v); }, &st);
+        fp_views(t->g, t->P, &v);
+        t->fp = (const ConeFPView *)cached(key, [&] { return as_bytes(v); }, &st);
     }
     return st;
-}
-
-// The FP64 rows that follow the FP32 ones in a back-projector table of a
-// trajectory that is not a rotation about z; NULL for a circular one.
-const ConeBPView64 *views64_of(const void *views, bool axial, int n_proj)
-{
-    return axial ? nullptr : reinterpret_cast<const ConeBPView64 *>((const ConeBPView *)views + n_proj);
-}
-
-int prep3d(const ph_geom3d *g, const float *mats, bool for_bp, Geom3D *G, const void **views, bool *axial)
-{
-    std::vector<double> P;
-    int st = validate3d(g, mats, G, &P);
-    if (st != PH_OK)
-        return st;
-    return upload3d(g, mats, P, for_bp, views, axial);
 }
 
 // Host-only check of the filter length; returns the length to use in *Mout.
@@ -697,12 +760,13 @@ int project2d(const ph_geom2d *g, bool fan, const float *rv, const void *img, vo
     int st = check_dtype(dtype);
     if (st != PH_OK)
         return st;
-    Geom2D G;
-    const float2 *views = nullptr;
-    st = prep2d(g, fan, rv, &G, &views);
+    Traj2D t;
+    st = check2d(g, fan, rv, &t);
+    if (st == PH_OK)
+        st = table2d(&t);
     if (st != PH_OK)
         return st;
-    return to_status(launch_project_2d(dtype, fan, G, views, img, sino, batch, (hipStream_t)stream));
+    return to_status(launch_project_2d(dtype, fan, t.G, t.views, img, sino, batch, (hipStream_t)stream));
 }
 
 int backproject2d(const ph_geom2d *g, bool fan, const float *rv, const void *sino, void *img, int batch, int dtype,
@@ -715,12 +779,13 @@ int backproject2d(const ph_geom2d *g, bool fan, const float *rv, const void *sin
     int st = check_dtype(dtype);
     if (st != PH_OK)
         return st;
-    Geom2D G;
-    const float2 *views = nullptr;
-    st = prep2d(g, fan, rv, &G, &views);
+    Traj2D t;
+    st = check2d(g, fan, rv, &t);
+    if (st == PH_OK)
+        st = table2d(&t);
     if (st != PH_OK)
         return st;
-    return to_status(launch_backproject_2d(dtype, fan, G, views, sino, false, img, batch, (hipStream_t)stream));
+    return to_status(launch_backproject_2d(dtype, fan, t.G, t.views, sino, false, img, batch, (hipStream_t)stream));
 }
 
 int weight_filter2d(const ph_geom2d *g, bool fan, const void *sino, float *out, const float *K, int M,
@@ -758,25 +823,16 @@ int fbp2d(const ph_geom2d *g, bool fan, const float *rv, const void *sino, void 
     int st = check_dtype(dtype);
     if (st != PH_OK)
         return st;
-    Geom2D G;
-    st = make_geom2d(g, fan, &G);
+    Traj2D t;
+    st = check2d(g, fan, rv, &t);
     if (st != PH_OK)
         return st;
-    if (!rv)
-        return PH_ERR_NULL;
-    {
-        std::vector<float2> tmp;
-        st = views2d(g, fan, rv, &tmp);
-        if (st != PH_OK)
-            return st;
-    }
     if (!ws || ws_bytes < ph_workspace_bytes_2d(g, batch))
         return PH_ERR_WORKSPACE;
     st = filter_len(K, M, g->det_shape, &M);
     if (st != PH_OK)
         return st;
-    const float2 *views = nullptr;
-    st = prep2d(g, fan, rv, &G, &views);
+    st = table2d(&t);
     if (st != PH_OK)
         return st;
     FilterArgs a;
@@ -788,7 +844,7 @@ int fbp2d(const ph_geom2d *g, bool fan, const float *rv, const void *sino, void 
     st = to_status(launch_weight_filter(dtype, a, sino, q, (hipStream_t)stream));
     if (st != PH_OK)
         return st;
-    return to_status(launch_backproject_2d(dtype, fan, G, views, q, true, img, batch, (hipStream_t)stream));
+    return to_status(launch_backproject_2d(dtype, fan, t.G, t.views, q, true, img, batch, (hipStream_t)stream));
 }
 
 // B^T accumulates with float atomics: FP32 output directly, half-precision
@@ -805,22 +861,21 @@ int adjoint2d(const ph_geom2d *g, bool fan, bool of_projector, const float *rv, 
         return st;
     if (!of_projector && dtype != PH_F32 && !ws_call)
         return PH_ERR_UNSUPPORTED;
-    Geom2D G;
-    const float2 *views = nullptr;
-    st = validate2d(g, fan, rv);
+    Traj2D t;
+    st = check2d(g, fan, rv, &t);
     if (st != PH_OK)
         return st;
     const size_t n_out = (size_t)batch * g->n_proj * g->det_shape;
     const bool via_ws = !of_projector && dtype != PH_F32;
     if (via_ws && (!ws || ws_bytes < round_up(n_out * sizeof(float))))
         return PH_ERR_WORKSPACE;
-    st = prep2d(g, fan, rv, &G, &views);
+    st = table2d(&t);
     if (st != PH_OK)
         return st;
     if (of_projector)
-        return to_status(launch_project_adjoint_2d(dtype, fan, G, views, in, out, batch, (hipStream_t)stream));
+        return to_status(launch_project_adjoint_2d(dtype, fan, t.G, t.views, in, out, batch, (hipStream_t)stream));
     float *acc = via_ws ? (float *)ws : (float *)out;
-    st = to_status(launch_backproject_adjoint_2d(dtype, fan, G, views, in, acc, batch, (hipStream_t)stream));
+    st = to_status(launch_backproject_adjoint_2d(dtype, fan, t.G, t.views, in, acc, batch, (hipStream_t)stream));
     if (st != PH_OK || !via_ws)
         return st;
     return to_status(launch_cast_from_f32(dtype, acc, out, n_out, (hipStream_t)stream));
@@ -958,15 +1013,16 @@ int ph_project_cone3d(const ph_geom3d *g, const float *mats, const void *vol, vo
     int st = check_dtype(dtype);
     if (st != PH_OK)
         return st;
-    Geom3D G;
-    const void *views = nullptr;
-    bool axial = false;
-    st = prep3d(g, mats, false, &G, &views, &axial);
+    Traj3D t;
+    st = check3d(g, mats, false, &t);
+    if (st == PH_OK)
+        st = tables3d(&t, false);
     if (st != PH_OK)
         return st;
+    const Geom3D &G = t.G;
     const hipStream_t s = (hipStream_t)stream;
     if (dtype == PH_F32)
-        return to_status(launch_project_cone(dtype, G, (const ConeFPView *)views, (const float *)vol, proj, batch, s));
+        return to_status(launch_project_cone(dtype, G, t.fp, (const float *)vol, proj, batch, s));
     // A half-precision volume is widened (exactly) into a stream-ordered FP32
     // copy, projected by the FP32 kernel, and the projections are stored in
     // half precision: the values and arithmetic of FP32 staging, without a
@@ -977,7 +1033,7 @@ int ph_project_cone3d(const ph_geom3d *g, const float *mats, const void *vol, vo
         return PH_ERR_HIP;
     hipError_t e = launch_cast_to_f32(dtype, vol, (float *)wide, n_vox, s);
     if (e == hipSuccess)
-        e = launch_project_cone(dtype, G, (const ConeFPView *)views, (const float *)wide, proj, batch, s);
+        e = launch_project_cone(dtype, G, t.fp, (const float *)wide, proj, batch, s);
     const hipError_t ef = hipFreeAsync(wide, s);
     return to_status(e != hipSuccess ? e : ef);
 }
@@ -993,14 +1049,14 @@ int ph_backproject_cone3d(const ph_geom3d *g, const float *mats, const void *pro
     int st = check_dtype(dtype);
     if (st != PH_OK)
         return st;
-    Geom3D G;
-    const void *views = nullptr;
-    bool axial = false;
-    st = prep3d(g, mats, true, &G, &views, &axial);
+    Traj3D t;
+    st = check3d(g, mats, true, &t);
+    if (st == PH_OK)
+        st = tables3d(&t, true);
     if (st != PH_OK)
         return st;
-    return to_status(launch_backproject_cone(dtype, G, (const ConeBPView *)views, views64_of(views, axial, g->n_proj),
-                                             axial, bp_segment(g), proj, false, vol, batch, (hipStream_t)stream));
+    return to_status(launch_backproject_cone(dtype, t.G, t.bp, t.bp64(), t.axial, bp_segment(g), proj, false, vol, batch,
+                                             (hipStream_t)stream));
 }
 
 int ph_weight_filter_2d(const ph_geom2d *g, int fan, const void *sino, float *out, const float *K, int M,
@@ -1088,9 +1144,8 @@ int ph_fdk_cone3d(const ph_geom3d *g, const float *mats, const void *proj, void 
     int st = check_dtype(dtype);
     if (st != PH_OK)
         return st;
-    Geom3D G;
-    std::vector<double> P;
-    st = validate3d(g, mats, &G, &P);
+    Traj3D t;
+    st = check3d(g, mats, true, &t);
     if (st != PH_OK)
         return st;
     if (!ws || ws_bytes < ph_workspace_bytes_3d(g, batch))
@@ -1098,9 +1153,7 @@ int ph_fdk_cone3d(const ph_geom3d *g, const float *mats, const void *proj, void 
     st = filter_len(K, M, g->det_shape[1], &M);
     if (st != PH_OK)
         return st;
-    const void *views = nullptr;
-    bool axial = false;
-    st = upload3d(g, mats, P, true, &views, &axial);
+    st = tables3d(&t, true);
     if (st != PH_OK)
         return st;
     FilterArgs a;
@@ -1112,8 +1165,8 @@ int ph_fdk_cone3d(const ph_geom3d *g, const float *mats, const void *proj, void 
     st = to_status(launch_weight_filter(dtype, a, proj, q, (hipStream_t)stream));
     if (st != PH_OK)
         return st;
-    return to_status(launch_backproject_cone(dtype, G, (const ConeBPView *)views, views64_of(views, axial, g->n_proj),
-                                             axial, bp_segment(g), q, true, vol, batch, (hipStream_t)stream));
+    return to_status(launch_backproject_cone(dtype, t.G, t.bp, t.bp64(), t.axial, bp_segment(g), q, true, vol, batch,
+                                             (hipStream_t)stream));
 }
 
 int ph_fdk_cone3d_static(const ph_geom3d *g, const float *mats, const void *proj, void *vol, const float *K, int M,
@@ -1129,7 +1182,12 @@ int ph_fdk_cone3d_static(const ph_geom3d *g, const float *mats, const void *proj
         return st;
     Geom3D G;
     std::vector<double> P;
-    st = validate3d(g, mats, &G, &P);
+    st = make_geom3d(g, &G);
+    if (st != PH_OK)
+        return st;
+    if (!mats)
+        return PH_ERR_NULL;
+    st = normalised_mats(g, mats, &P);
     if (st != PH_OK)
         return st;
     st = filter_len(K, M, g->det_shape[1], &M);
@@ -1260,24 +1318,20 @@ static int fpT3d(const ph_geom3d *g, const float *mats, const void *proj, void *
     int st = check_dtype(dtype);
     if (st != PH_OK)
         return st;
-    Geom3D G;
-    std::vector<double> P;
-    st = validate3d(g, mats, &G, &P);
+    Traj3D t;
+    st = check3d(g, mats, false, &t);
     if (st != PH_OK)
         return st;
-    const size_t need = ws_call ? project_adjoint_scratch(G, batch) : 0;
+    const size_t need = ws_call ? project_adjoint_scratch(t.G, batch) : 0;
     if (need > 0 && (!ws || ws_bytes < need))
         return PH_ERR_WORKSPACE;
-    const void *fv = nullptr, *bv = nullptr;
-    bool axial = false;
-    st = upload3d(g, mats, P, false, &fv, &axial);
+    st = tables3d(&t, false);
+    if (st == PH_OK)
+        st = tables3d(&t, true);
     if (st != PH_OK)
         return st;
-    st = upload3d(g, mats, P, true, &bv, &axial);
-    if (st != PH_OK)
-        return st;
-    return to_status(launch_project_adjoint_cone(dtype, G, (const ConeFPView *)fv, (const ConeBPView *)bv, proj, vol,
-                                                 batch, need > 0 ? (double *)ws : nullptr, (hipStream_t)stream));
+    return to_status(launch_project_adjoint_cone(dtype, t.G, t.fp, t.bp, proj, vol, batch,
+                                                 need > 0 ? (double *)ws : nullptr, (hipStream_t)stream));
 }
 
 int ph_project_adjoint_cone3d(const ph_geom3d *g, const float *mats, const void *proj, void *vol, int batch,
@@ -1315,24 +1369,20 @@ static int bpT3d(const ph_geom3d *g, const float *mats, const void *vol, void *p
         return st;
     if (dtype != PH_F32 && !ws_call)
         return PH_ERR_UNSUPPORTED;
-    Geom3D G;
-    std::vector<double> P;
-    st = validate3d(g, mats, &G, &P);
+    Traj3D t;
+    st = check3d(g, mats, true, &t);
     if (st != PH_OK)
         return st;
     const size_t n_out = (size_t)batch * g->n_proj * g->det_shape[0] * g->det_shape[1];
     const bool via_ws = dtype != PH_F32;
     if (via_ws && (!ws || ws_bytes < round_up(n_out * sizeof(float))))
         return PH_ERR_WORKSPACE;
-    const void *views = nullptr;
-    bool axial = false;
-    st = upload3d(g, mats, P, true, &views, &axial);
+    st = tables3d(&t, true);
     if (st != PH_OK)
         return st;
     float *acc = via_ws ? (float *)ws : (float *)proj;
-    st = to_status(launch_backproject_adjoint_cone(dtype, G, (const ConeBPView *)views,
-                                                   views64_of(views, axial, g->n_proj), axial, bp_segment(g), vol, acc,
-                                                   batch, (hipStream_t)stream));
+    st = to_status(launch_backproject_adjoint_cone(dtype, t.G, t.bp, t.bp64(), t.axial, bp_segment(g), vol, acc, batch,
+                                                   (hipStream_t)stream));
     if (st != PH_OK || !via_ws)
         return st;
     return to_status(launch_cast_from_f32(dtype, acc, proj, n_out, (hipStream_t)stream));

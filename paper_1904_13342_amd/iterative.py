@@ -14,6 +14,8 @@ only owns the buffers.
 """
 from __future__ import annotations
 
+import math
+
 import torch
 
 from . import ops
@@ -71,7 +73,7 @@ class TVReconstruction:
         without a host round trip per kernel); returns the float64 device
         tensor [data term, TV per item] at the iterate before the last update."""
         if self._ws is None:
-            batch = self.x.numel() // max(1, int(torch.tensor(list(self.g.vol_shape)).prod()))
+            batch = self.x.numel() // max(1, math.prod(self.g.vol_shape))
             self._ws = torch.empty(ops.tv_workspace_bytes(self.g, batch), dtype=torch.uint8, device=self.x.device)
         b1, b2 = self.betas
         out = ops.tv_iterate(self.kind, self.g, self.traj, self.p, self.x, self.m, self.v, self.t, iters, self.lam,

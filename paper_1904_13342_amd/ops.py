@@ -80,7 +80,7 @@ def from_spec(spec):
 
 
 def _fptr(a):
-    return a.ctypes.data_as(ctypes.POINTER(ctypes.c_float))
+    return a.ctypes.data
 
 
 def ray_vectors_2d(g):
@@ -105,16 +105,16 @@ def _host_traj(traj, shape):
 
 
 def _dev(t, name, expect_tail):
-    if not isinstance(t, torch.Tensor) or t.device.type != "cuda":
+    if not isinstance(t, torch.Tensor) or not t.is_cuda:
         raise ValueError(f"{name} must be a GPU tensor")
     if t.dtype not in _DTYPES:
         raise ValueError(f"{name} has unsupported dtype {t.dtype}")
     if not t.is_contiguous():
         raise ValueError(f"{name} must be contiguous")
-    tail = tuple(t.shape[-len(expect_tail):]) if t.dim() >= len(expect_tail) else None
-    if tail != tuple(expect_tail) or t.dim() not in (len(expect_tail), len(expect_tail) + 1):
-        raise ValueError(f"{name} has shape {tuple(t.shape)}, expected [B,] {tuple(expect_tail)}")
-    batch = 1 if t.dim() == len(expect_tail) else t.shape[0]
+    shape, lead = tuple(t.shape), t.dim() - len(expect_tail)
+    if lead not in (0, 1) or shape[lead:] != expect_tail:
+        raise ValueError(f"{name} has shape {shape}, expected [B,] {tuple(expect_tail)}")
+    batch = shape[0] if lead else 1
     if batch < 1:
         raise ValueError(f"{name} has an empty batch")
     return batch
@@ -131,7 +131,8 @@ def _f32_dev(t, name, n):
 
 
 def _stream(t):
-    return ctypes.c_void_p(torch.cuda.current_stream(t.device).cuda_stream)
+    """Handle of torch's current stream on t's device (no Stream object is made for it)."""
+    return torch._C._cuda_getCurrentRawStream(t.get_device())
 
 
 def _vol_tail(g):
@@ -158,9 +159,9 @@ def _unary(fn, g, traj, x, in_tail, out_tail, out=None, ws=None):
         out = torch.empty(shape, dtype=x.dtype, device=x.device)
     elif tuple(out.shape) != shape or out.dtype != x.dtype or not out.is_contiguous() or out.device != x.device:
         raise ValueError("out has the wrong shape, dtype, device or layout")
-    scratch = () if ws is None else (ctypes.c_void_p(ws.data_ptr()), ws.numel())
-    status = getattr(lib(), fn)(ctypes.byref(g), _fptr(t), ctypes.c_void_p(x.data_ptr()),
-                                ctypes.c_void_p(out.data_ptr()), *scratch, batch, _DTYPES[x.dtype], _stream(x))
+    scratch = () if ws is None else (ws.data_ptr(), ws.numel())
+    status = getattr(lib(), fn)(ctypes.byref(g), _fptr(t), x.data_ptr(),
+                                out.data_ptr(), *scratch, batch, _DTYPES[x.dtype], _stream(x))
     check(fn, status)
     return out
 
@@ -226,8 +227,8 @@ def _bpT(fn, g, traj, x, out):
     nbytes = int(q(ctypes.byref(g), batch, _DTYPES[x.dtype]))
     ws = torch.empty(nbytes, dtype=torch.uint8, device=x.device)
     name = fn.replace("ph_backproject_adjoint_", "ph_backproject_adjoint_ws_")
-    status = getattr(lib(), name)(ctypes.byref(g), _fptr(t), ctypes.c_void_p(x.data_ptr()),
-                                  ctypes.c_void_p(out.data_ptr()), ctypes.c_void_p(ws.data_ptr()), nbytes, batch,
+    status = getattr(lib(), name)(ctypes.byref(g), _fptr(t), x.data_ptr(),
+                                  out.data_ptr(), ws.data_ptr(), nbytes, batch,
                                   _DTYPES[x.dtype], _stream(x))
     check(name, status)
     return out
@@ -258,8 +259,8 @@ def weight_filter_2d(g, sino, fan, K=None, M=None, W_red=None, out=None):
     shape = tuple(sino.shape)
     if out is None:
         out = torch.empty(shape, dtype=torch.float32, device=sino.device)
-    status = lib().ph_weight_filter_2d(ctypes.byref(g), int(bool(fan)), ctypes.c_void_p(sino.data_ptr()),
-                                       ctypes.c_void_p(out.data_ptr()), _f32_dev(K, "K", M), M,
+    status = lib().ph_weight_filter_2d(ctypes.byref(g), int(bool(fan)), sino.data_ptr(),
+                                       out.data_ptr(), _f32_dev(K, "K", M), M,
                                        _f32_dev(W_red, "W_red", g.n_proj * g.det_shape), batch,
                                        _DTYPES[sino.dtype], _stream(sino))
     check("ph_weight_filter_2d", status)
@@ -272,8 +273,8 @@ def weight_filter_3d(g, proj, K=None, M=None, W_red=None, W=None, out=None):
     nv, nu = g.det_shape[0], g.det_shape[1]
     if out is None:
         out = torch.empty(tuple(proj.shape), dtype=torch.float32, device=proj.device)
-    status = lib().ph_weight_filter_3d(ctypes.byref(g), ctypes.c_void_p(proj.data_ptr()),
-                                       ctypes.c_void_p(out.data_ptr()), _f32_dev(K, "K", M), M,
+    status = lib().ph_weight_filter_3d(ctypes.byref(g), proj.data_ptr(),
+                                       out.data_ptr(), _f32_dev(K, "K", M), M,
                                        _f32_dev(W_red, "W_red", g.n_proj * nu), _f32_dev(W, "W", nv * nu), batch,
                                        _DTYPES[proj.dtype], _stream(proj))
     check("ph_weight_filter_3d", status)
@@ -306,7 +307,7 @@ def _f32_like(t, name, numel=None):
         raise ValueError(f"{name} must be contiguous")
     if numel is not None and t.numel() != numel:
         raise ValueError(f"{name} must have {numel} elements, has {t.numel()}")
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def mse_grad(x, ref, mask=None, grad=None, loss=None):
@@ -321,7 +322,7 @@ def mse_grad(x, ref, mask=None, grad=None, loss=None):
         loss = torch.empty((), dtype=torch.float64, device=x.device)
     if loss.dtype != torch.float64 or loss.numel() != 1 or loss.device != x.device:
         raise ValueError("loss must be a one-element float64 tensor on the device of x")
-    status = lib().ph_mse_grad(px, pr, pm, n, _f32_like(grad, "grad", n), ctypes.c_void_p(loss.data_ptr()),
+    status = lib().ph_mse_grad(px, pr, pm, n, _f32_like(grad, "grad", n), loss.data_ptr(),
                                _stream(x))
     check("ph_mse_grad", status)
     return loss, grad
@@ -343,8 +344,8 @@ def corrector_grad_3d(g, proj, grad_q, K, W_red=None, W=None, dK=None, dW=None, 
         dW = torch.empty((nv, nu), dtype=torch.float32, device=proj.device)
     if not want_dW:
         dW = None
-    status = lib().ph_corrector_grad_3d(ctypes.byref(g), ctypes.c_void_p(proj.data_ptr()),
-                                        ctypes.c_void_p(grad_q.data_ptr()), _f32_like(K, "K"), M,
+    status = lib().ph_corrector_grad_3d(ctypes.byref(g), proj.data_ptr(),
+                                        grad_q.data_ptr(), _f32_like(K, "K"), M,
                                         _f32_dev(W_red, "W_red", g.n_proj * nu), _f32_dev(W, "W", nv * nu),
                                         _f32_like(dK, "dK", M), None if dW is None else _f32_like(dW, "dW", nv * nu),
                                         batch, _stream(proj))
@@ -362,8 +363,8 @@ def corrector_grad_2d(g, sino, grad_q, K, fan, W_red=None, dK=None):
     M = K.numel()
     if dK is None:
         dK = torch.empty(M, dtype=torch.float32, device=sino.device)
-    status = lib().ph_corrector_grad_2d(ctypes.byref(g), int(bool(fan)), ctypes.c_void_p(sino.data_ptr()),
-                                        ctypes.c_void_p(grad_q.data_ptr()), _f32_like(K, "K"), M,
+    status = lib().ph_corrector_grad_2d(ctypes.byref(g), int(bool(fan)), sino.data_ptr(),
+                                        grad_q.data_ptr(), _f32_like(K, "K"), M,
                                         _f32_dev(W_red, "W_red", g.n_proj * g.det_shape), _f32_like(dK, "dK", M),
                                         batch, _stream(sino))
     check("ph_corrector_grad_2d", status)
@@ -404,10 +405,10 @@ def tv(x, eps, dims, weight=1.0, grad=None, want_value=True, anisotropic=False):
         if grad.data_ptr() == x.data_ptr():
             raise ValueError("grad must not alias x")
     value = torch.empty(max(batch, 1), dtype=torch.float64, device=x.device) if want_value else None
-    status = lib().ph_tv_3d(ctypes.c_void_p(x.data_ptr()), nz, ny, nx, batch, int(bool(anisotropic)), float(eps),
+    status = lib().ph_tv_3d(x.data_ptr(), nz, ny, nx, batch, int(bool(anisotropic)), float(eps),
                             float(weight),
-                            None if grad is None else ctypes.c_void_p(grad.data_ptr()),
-                            None if value is None else ctypes.c_void_p(value.data_ptr()), _stream(x))
+                            None if grad is None else grad.data_ptr(),
+                            None if value is None else value.data_ptr(), _stream(x))
     check("ph_tv_3d", status)
     if value is not None:
         value = value.reshape(lead) if lead else value[0]
@@ -431,7 +432,7 @@ def tv_iterate(kind, g, traj, proj, x, m, v, t0, n_iter, lam, eps, lr=1e-2, beta
     batch = _dev(proj, "proj", _sino_tail(g))
     if proj.dtype != torch.float32:
         raise ValueError("proj must be float32")
-    nimg = batch * int(torch.tensor(list(g.vol_shape)).prod())
+    nimg = batch * math.prod(g.vol_shape)
     for t, name in ((x, "x"), (m, "m"), (v, "v")):
         _f32_like(t, name, nimg)
     t = _traj(g, traj)
@@ -442,11 +443,11 @@ def tv_iterate(kind, g, traj, proj, x, m, v, t0, n_iter, lam, eps, lr=1e-2, beta
         data_tv = torch.empty(1 + batch, dtype=torch.float64, device=proj.device)
     prm = TvParams(float(lam), float(eps), float(lr), float(beta1), float(beta2), float(adam_eps),
                    int(bool(anisotropic)))
-    status = getattr(lib(), fns[kind])(ctypes.byref(g), _fptr(t), ctypes.c_void_p(proj.data_ptr()),
-                                       ctypes.c_void_p(x.data_ptr()), ctypes.c_void_p(m.data_ptr()),
-                                       ctypes.c_void_p(v.data_ptr()), int(t0), int(n_iter), ctypes.byref(prm),
-                                       ctypes.c_void_p(ws.data_ptr()), ws.numel() * ws.element_size(),
-                                       ctypes.c_void_p(data_tv.data_ptr()), batch, _stream(proj))
+    status = getattr(lib(), fns[kind])(ctypes.byref(g), _fptr(t), proj.data_ptr(),
+                                       x.data_ptr(), m.data_ptr(),
+                                       v.data_ptr(), int(t0), int(n_iter), ctypes.byref(prm),
+                                       ws.data_ptr(), ws.numel() * ws.element_size(),
+                                       data_tv.data_ptr(), batch, _stream(proj))
     check(fns[kind], status)
     return data_tv
 
@@ -473,9 +474,9 @@ def _fbp2d(fn, g, ray_vecs, sino, K, M, W_red, out, ws):
     nbytes = workspace_bytes_2d(g, batch)
     if ws is None:
         ws = torch.empty(nbytes, dtype=torch.uint8, device=sino.device)
-    status = getattr(lib(), fn)(ctypes.byref(g), _fptr(t), ctypes.c_void_p(sino.data_ptr()),
-                                ctypes.c_void_p(out.data_ptr()), _f32_dev(K, "K", M), M,
-                                _f32_dev(W_red, "W_red", g.n_proj * g.det_shape), ctypes.c_void_p(ws.data_ptr()),
+    status = getattr(lib(), fn)(ctypes.byref(g), _fptr(t), sino.data_ptr(),
+                                out.data_ptr(), _f32_dev(K, "K", M), M,
+                                _f32_dev(W_red, "W_red", g.n_proj * g.det_shape), ws.data_ptr(),
                                 ws.numel() * ws.element_size(), batch, _DTYPES[sino.dtype], _stream(sino))
     check(fn, status)
     return out
@@ -500,10 +501,10 @@ def fdk_cone3d(g, mats, proj, K=None, M=None, W_red=None, W=None, out=None, ws=N
     nbytes = fdk_workspace_bytes(g, M, batch, proj.dtype)
     if ws is None:
         ws = torch.empty(nbytes, dtype=torch.uint8, device=proj.device)
-    status = lib().ph_fdk_cone3d(ctypes.byref(g), _fptr(t), ctypes.c_void_p(proj.data_ptr()),
-                                 ctypes.c_void_p(out.data_ptr()), _f32_dev(K, "K", M), M,
+    status = lib().ph_fdk_cone3d(ctypes.byref(g), _fptr(t), proj.data_ptr(),
+                                 out.data_ptr(), _f32_dev(K, "K", M), M,
                                  _f32_dev(W_red, "W_red", g.n_proj * nu), _f32_dev(W, "W", nv * nu),
-                                 ctypes.c_void_p(ws.data_ptr()), ws.numel() * ws.element_size(), batch,
+                                 ws.data_ptr(), ws.numel() * ws.element_size(), batch,
                                  _DTYPES[proj.dtype], _stream(proj))
     check("ph_fdk_cone3d", status)
     return out
@@ -519,8 +520,8 @@ def fdk_cone3d_static(g, mats, proj, out, K=None, M=None, W_red=None, W=None):
     shape = (tuple(proj.shape[:1]) if proj.dim() == 4 else ()) + _vol_tail(g)
     if tuple(out.shape) != shape or out.dtype != proj.dtype or out.device != proj.device or not out.is_contiguous():
         raise ValueError(f"out must be a contiguous {proj.dtype} tensor of shape {shape} on {proj.device}")
-    status = lib().ph_fdk_cone3d_static(ctypes.byref(g), _fptr(t), ctypes.c_void_p(proj.data_ptr()),
-                                        ctypes.c_void_p(out.data_ptr()), _f32_dev(K, "K", M), M,
+    status = lib().ph_fdk_cone3d_static(ctypes.byref(g), _fptr(t), proj.data_ptr(),
+                                        out.data_ptr(), _f32_dev(K, "K", M), M,
                                         _f32_dev(W_red, "W_red", g.n_proj * nu), _f32_dev(W, "W", nv * nu), batch,
                                         _DTYPES[proj.dtype], _stream(proj))
     check("ph_fdk_cone3d_static", status)
