@@ -84,15 +84,19 @@ __device__ __forceinline__ bool in_slab(int m, float eA, float PA0, int offA)
 
 // Trilinear sample at (float) index fm from the LDS slab ([c][b][a], a
 // fastest).  Biased coordinates are positive, so truncation is floor; the
-// cell's byte offset is formed with 24-bit multiplies (every factor is below
-// 2^24), and `base` folds the slab's offsets in (bytes, modulo 2^32).
+// cell's byte offset is formed with 24-bit multiply-adds (every factor is below
+// 2^24; written out, since the compiler splits the chain into products and
+// sums), and `base` folds the slab's offsets in (bytes, modulo 2^32).
 __device__ __forceinline__ float sample_lds(const float *slab, float fm, float PA0, float eA, float PB0, float eB,
                                             float PC0, float eC, unsigned base, unsigned sc)
 {
     const float A = fmaf(fm, eA, PA0), B = fmaf(fm, eB, PB0), C = fmaf(fm, eC, PC0);
     const unsigned iA = (unsigned)A, iB = (unsigned)B, iC = (unsigned)C;
     const float tA = __builtin_amdgcn_fractf(A), tB = __builtin_amdgcn_fractf(B), tC = __builtin_amdgcn_fractf(C);
-    const unsigned off = __umul24(iC, 4u * sc) + __umul24(iB, 4u * FP_WA) + (iA << 2) + base;   // bytes
+    unsigned off;   // bytes
+    asm("v_mad_u32_u24 %0, %1, %2, %3" : "=v"(off) : "v"(iC), "s"(4u * sc), "v"(base));
+    asm("v_mad_u32_u24 %0, %1, %2, %3" : "=v"(off) : "v"(iB), "I"(4u * FP_WA), "v"(off));
+    off += iA << 2;
     const float *p = (const float *)((const char *)slab + off);
     constexpr int sb = FP_WA;
     const float l00 = fmaf(tA, p[1] - p[0], p[0]);
@@ -286,16 +290,15 @@ __device__ __forceinline__ float slab_walk(const Geom3D &g, const float *f, floa
             // LDS cell of biased coordinates (A, B, C), as a byte offset
             const unsigned base = 4u * (unsigned)(-(offC * HB + offB) * FP_WA - offA);
             const unsigned sc = (unsigned)(FP_WA * HB);
-            // two samples per pass (sample indices are exact in FP32); an odd
-            // last pass repeats the final sample and drops it, so a wave
-            // runs ceil(n / 2) passes for the longest lane's n samples
+            // two samples per pass (sample indices are exact in FP32), then an odd last one
             const float fend = (float)m_end;
-            for (float fm = (float)m; fm < fend; fm += 2.0f) {
+            float fm = (float)m;
+            for (; fm + 1.0f < fend; fm += 2.0f) {
                 acc += sample_lds(buf, fm, PA0, eA, PB0, eB, PC0, eC, base, sc);
-                const float f1 = fm + 1.0f;
-                const float s1 = sample_lds(buf, fminf(f1, fend - 1.0f), PA0, eA, PB0, eB, PC0, eC, base, sc);
-                acc += f1 < fend ? s1 : 0.0f;
+                acc += sample_lds(buf, fm + 1.0f, PA0, eA, PB0, eB, PC0, eC, base, sc);
             }
+            if (fm < fend)
+                acc += sample_lds(buf, fm, PA0, eA, PB0, eB, PC0, eC, base, sc);
             m = m_end;
         } else {
             for (; m < m_end; ++m) {
