@@ -24,13 +24,13 @@ namespace {
 
 // A wave owns a tile of 8 x 8 pixels and takes one view at a time.  The rays
 // that can cross the tile (the bins of its footprint, a few dozen) are set up
-// once for all its pixels, a ray per lane, in double precision and exactly as
-// the projector sets them up, and put in LDS with the reciprocals of their
-// steps; then every lane gathers over the two or three rays that cross its
-// own pixel's support, clipping each to it.  Setting the ray up in every
+// once for all its pixels, a ray per lane and up to four views at once, in
+// double precision and exactly as the projector sets them up, and put in LDS
+// with the reciprocals of their steps; then every lane gathers over the two or
+// three rays that cross its own pixel's support, clipping each to it.  Setting the ray up in every
 // pixel instead is what the time went to: 3.19 ms for 512^2 and 360 fan views
-// of 725 bins, against 0.80 ms; 256^2 with 30 parallel views of 363 bins went
-// from 46 to 16 us.  VALU-bound: about 330 lane operations per pixel and view.  The W waves of a workgroup share a tile, wave w taking views
+// of 725 bins, against 0.61 ms (0.80 ms setting up one view at a time); 256^2
+// with 30 parallel views of 363 bins went from 46 to 16 us.  VALU-bound.  The W waves of a workgroup share a tile, wave w taking views
 // w, w + W, ..., and meet in LDS in a fixed order.
 struct TileRay {
     float X0, Y0, eX, eY;   // sample m sits at (X0 + m eX, Y0 + m eY)
@@ -45,6 +45,14 @@ __device__ __forceinline__ float step_rcp(float e)
     return fabsf(e) < 1e-20f ? copysignf(1e20f, e) : __builtin_amdgcn_rcpf(e);
 }
 
+// max(1 - |d|, 0) in one instruction
+__device__ __forceinline__ float hat(float d)
+{
+    float r;
+    asm("v_sub_f32_e64 %0, 1.0, |%1| clamp" : "=v"(r) : "v"(d));
+    return r;
+}
+
 __device__ __forceinline__ void wave_lds_fence()
 {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -52,11 +60,12 @@ __device__ __forceinline__ void wave_lds_fence()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-template <typename T, typename TI, bool FAN>
+template <typename T, typename TI, bool FAN, int V>
 __global__ void __launch_bounds__(1024) fpT2d_kernel(Geom2D g, const float2 *__restrict__ views,
                                                      const TI *__restrict__ sino, T *__restrict__ img, int ntx,
                                                      int nty)
 {
+    constexpr int L = 64 / V;   // lanes (and rays) per view
     extern __shared__ TileRay s_rays[];   // 64 per wave
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int waves = blockDim.x >> 6;
@@ -73,56 +82,68 @@ __global__ void __launch_bounds__(1024) fpT2d_kernel(Geom2D g, const float2 *__r
     const float margin = fmaf(1e-6f, (float)g.nu, 0.02f);   // rounding of the coordinates (bins)
     const TI *sb = sino + (size_t)b * g.n_proj * g.nu;
     float acc = 0.0f;
-    for (int k = wave; k < g.n_proj; k += waves) {
-        const float2 c = views[k];
-        float fu, t, wt;
-        point2d<FAN>(g, c, qx, qy, fu, t, wt);
-        const int jc = (int)fu;
-        const int j_lo = max(__builtin_amdgcn_readfirstlane(imin4(jc)), 0);
-        const int j_hi = min(__builtin_amdgcn_readfirstlane(imax4(jc)) + 1, g.nu - 1);
-        if (j_lo > j_hi)
-            continue;
-        // bins whose rays cross this pixel's support: its centre's coordinate
-        // and a bound on the support's half width (central projection of the
-        // box |dx| < sx, |dy| < sy; the fan angle moves no faster than the slope)
-        point2d<FAN>(g, c, x, y, fu, t, wt);
-        const float ac = fabsf(c.x), as = fabsf(c.y);
-        float h = fmaf(as, g.sx, ac * g.sy);
-        if (FAN) {
-            const float xu = fmaf(y, c.x, -(x * c.y)), w = fmaf(x, c.x, fmaf(y, c.y, g.sid));
-            const float dw = fmaf(ac, g.sx, as * g.sy);
-            h = fmaf(fabsf(xu) * __builtin_amdgcn_rcpf(w), dw, h) * __builtin_amdgcn_rcpf(w - dw);
+    for (int k0 = wave * V; k0 < g.n_proj; k0 += waves * V) {
+        // the tile's bins in this lane's view
+        const int kv = min(k0 + lane / L, g.n_proj - 1);
+        const float2 cl = views[kv];
+        int j_lo, j_hi;
+        {
+            float fu, t, wt;
+            point2d<FAN>(g, cl, qx, qy, fu, t, wt);
+            const int jc = (int)fu;
+            j_lo = max(imin4(jc), 0);
+            j_hi = min(imax4(jc) + 1, g.nu - 1);
         }
-        h = fmaf(h, g.ru, margin);
-        const int ja = (int)ceilf(fmaxf(fu + (t - h), (float)j_lo)), jb = (int)floorf(fminf(fu + (t + h), (float)j_hi));
-        for (int c0 = j_lo; c0 <= j_hi; c0 += 64) {
-            if (c0 + lane <= j_hi) {
+        for (int c0 = 0; __any(j_lo + c0 <= j_hi); c0 += L) {
+            const int jl = j_lo + c0 + lane % L;
+            if (jl <= j_hi) {
                 TileRay r;
-                make_ray_2d<FAN>(g, c, c0 + lane, r.X0, r.Y0, r.eX, r.eY);
+                make_ray_2d<FAN>(g, cl, jl, r.X0, r.Y0, r.eX, r.eY);
                 r.rX = step_rcp(r.eX);
                 r.rY = step_rcp(r.eY);
-                r.g = load_f32(sb + (size_t)k * g.nu + c0 + lane);
+                r.g = load_f32(sb + (size_t)kv * g.nu + jl);
                 rays[lane] = r;
             }
             wave_lds_fence();
-            for (int j = max(ja, c0); j <= min(jb, c0 + 63); ++j) {
-                const TileRay r = rays[j - c0];
-                // the samples inside the support; the clip only picks the
-                // range to visit (hardware reciprocals, widened), the weights
-                // decide every sample
-                const float cx = (fx - r.X0) * r.rX, cy = (fy - r.Y0) * r.rY;
-                const float lo = fmaxf(cx - fabsf(r.rX), cy - fabsf(r.rY));
-                const float hi = fminf(cx + fabsf(r.rX), cy + fabsf(r.rY));
-                if (!(lo < hi + 0.02f))
-                    continue;
-                float w = 0.0f;
-                const int m1 = (int)floorf(hi + 0.02f);
-                for (int m = (int)ceilf(lo - 0.02f); m <= m1; ++m) {
-                    const float wx = 1.0f - fabsf(fmaf((float)m, r.eX, r.X0) - fx);
-                    const float wy = 1.0f - fabsf(fmaf((float)m, r.eY, r.Y0) - fy);
-                    w = fmaf(fmaxf(wx, 0.0f), fmaxf(wy, 0.0f), w);
+#pragma unroll 1
+            for (int v = 0; v < V && k0 + v < g.n_proj; ++v) {
+                const float2 c = views[k0 + v];
+                const int jv = __builtin_amdgcn_readlane(j_lo, v * L) + c0;   // bin of the view's first ray
+                const int je = min(__builtin_amdgcn_readlane(j_hi, v * L), jv + L - 1);
+                // bins whose rays cross this pixel's support: its centre's
+                // coordinate and a bound on the support's half width (central
+                // projection of the box |dx| < sx, |dy| < sy; the fan angle
+                // moves no faster than the slope)
+                float fu, t, wt;
+                point2d<FAN>(g, c, x, y, fu, t, wt);
+                const float ac = fabsf(c.x), as = fabsf(c.y);
+                float h = fmaf(as, g.sx, ac * g.sy);
+                if (FAN) {
+                    const float xu = fmaf(y, c.x, -(x * c.y)), w = fmaf(x, c.x, fmaf(y, c.y, g.sid));
+                    const float dw = fmaf(ac, g.sx, as * g.sy);
+                    h = fmaf(fabsf(xu) * __builtin_amdgcn_rcpf(w), dw, h) * __builtin_amdgcn_rcpf(w - dw);
                 }
-                acc = fmaf(r.g, w, acc);
+                h = fmaf(h, g.ru, margin);
+                const int ja = (int)ceilf(fmaxf(fu + (t - h), (float)jv)), jb = (int)floorf(fminf(fu + (t + h), (float)je));
+                for (int j = ja; j <= jb; ++j) {
+                    const TileRay r = rays[v * L + j - jv];
+                    // the samples inside the support; the clip only picks the
+                    // range to visit (hardware reciprocals, widened), the
+                    // weights decide every sample
+                    const float cx = (fx - r.X0) * r.rX, cy = (fy - r.Y0) * r.rY;
+                    const float lo = fmaxf(cx - fabsf(r.rX), cy - fabsf(r.rY));
+                    const float hi = fminf(cx + fabsf(r.rX), cy + fabsf(r.rY));
+                    if (!(lo < hi + 0.02f))
+                        continue;
+                    float w = 0.0f;
+                    const int m1 = (int)floorf(hi + 0.02f);
+                    for (int m = (int)ceilf(lo - 0.02f); m <= m1; ++m) {
+                        const float wx = hat(fmaf((float)m, r.eX, r.X0) - fx);
+                        const float wy = hat(fmaf((float)m, r.eY, r.Y0) - fy);
+                        w = fmaf(wx, wy, w);
+                    }
+                    acc = fmaf(r.g, w, acc);
+                }
             }
             wave_lds_fence();
         }
@@ -649,8 +670,8 @@ __global__ void __launch_bounds__(1024) bpT2d_kernel(Geom2D g, const float2 *__r
         sino[((size_t)b * g.n_proj + k) * g.nu + j] = a0 + below;
 }
 
-template <typename T, typename TI, bool FAN>
-hipError_t fpT2d_f(const Geom2D &g, const float2 *views, const void *sino, void *img, int batch, hipStream_t s)
+template <typename T, typename TI, bool FAN, int V>
+hipError_t fpT2d_v(const Geom2D &g, const float2 *views, const void *sino, void *img, int batch, hipStream_t s)
 {
     const int ntx = (g.nx + 7) / 8, nty = (g.ny + 7) / 8;
     const long tiles = (long)ntx * nty * batch;
@@ -658,11 +679,26 @@ hipError_t fpT2d_f(const Geom2D &g, const float2 *views, const void *sino, void 
         return hipErrorInvalidConfiguration;
     // waves per tile: about 32 on every CU, at least two views each
     int waves = 1;
-    while (waves < 16 && tiles * waves < 8192 && 4 * waves <= g.n_proj)
+    while (waves < 16 && tiles * waves < 8192 && 2 * V * waves <= g.n_proj)
         waves *= 2;
-    hipLaunchKernelGGL((fpT2d_kernel<T, TI, FAN>), dim3((unsigned)tiles), dim3(64 * waves),
+    hipLaunchKernelGGL((fpT2d_kernel<T, TI, FAN, V>), dim3((unsigned)tiles), dim3(64 * waves),
                        64 * waves * sizeof(TileRay), s, g, views, (const TI *)sino, (T *)img, ntx, nty);
     return hipGetLastError();
+}
+
+template <typename T, typename TI, bool FAN>
+hipError_t fpT2d_f(const Geom2D &g, const float2 *views, const void *sino, void *img, int batch, hipStream_t s)
+{
+    // Views set up together, so that the rays of an 8 x 8 tile's support at the
+    // isocentre (its diagonal and three bins for the rounded-out ends) fill the
+    // wave; a view that needs more lanes is set up in several passes.  512^2,
+    // 360 fan views, 13 bins: 850, 625 and 605 us for one, two and four views.
+    const float diag = 9.0f * sqrtf(g.sx * g.sx + g.sy * g.sy), n = diag * (FAN ? g.ru / g.sid : g.ru) + 3.0f;
+    if (n <= 16.0f)
+        return fpT2d_v<T, TI, FAN, 4>(g, views, sino, img, batch, s);
+    if (n <= 32.0f)
+        return fpT2d_v<T, TI, FAN, 2>(g, views, sino, img, batch, s);
+    return fpT2d_v<T, TI, FAN, 1>(g, views, sino, img, batch, s);
 }
 
 template <typename T, typename TI>
