@@ -53,13 +53,6 @@ __device__ __forceinline__ float hat(float d)
     return r;
 }
 
-__device__ __forceinline__ void wave_lds_fence()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 template <typename T, typename TI, bool FAN, int V>
 __global__ void __launch_bounds__(1024) fpT2d_kernel(Geom2D g, const float2 *__restrict__ views,
                                                      const TI *__restrict__ sino, T *__restrict__ img, int ntx,
@@ -692,7 +685,7 @@ hipError_t fpT2d_f(const Geom2D &g, const float2 *views, const void *sino, void 
     // Views set up together, so that the rays of an 8 x 8 tile's support at the
     // isocentre (its diagonal and three bins for the rounded-out ends) fill the
     // wave; a view that needs more lanes is set up in several passes.  512^2,
-    // 360 fan views, 13 bins: 850, 625 and 605 us for one, two and four views.
+    // 360 fan views, 13 bins, with A: 1.17, 0.95 and 0.89 ms for one, two and four views.
     const float diag = 9.0f * sqrtf(g.sx * g.sx + g.sy * g.sy), n = diag * (FAN ? g.ru / g.sid : g.ru) + 3.0f;
     if (n <= 16.0f)
         return fpT2d_v<T, TI, FAN, 4>(g, views, sino, img, batch, s);

@@ -16,6 +16,15 @@ __device__ __forceinline__ float2 load_pair(const T *base, unsigned bytes)
     return make_float2(load_f32(&p.a), load_f32(&p.b));
 }
 
+// Orders a wave's own LDS writes before its lanes' reads (and the other way
+// round): for LDS that only one wave uses.
+__device__ __forceinline__ void wave_lds_fence()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // Index coordinates (x, y, z) of a ray's anchor (its point closest to the
 // isocentre) and of one sampling step: sample m sits at p + m * e.
 struct Ray {

@@ -26,6 +26,13 @@ CASES = {
     "par_off_axis": ("par2d", (60, 50), 500, 1.0, 9, 180, {}, (-180.0, 120.0)),
     "fan_65_views": ("fan2d", (127, 129), 230, 1.0, 65, 360, FAN, None),
     "fan_few_bins": ("fan2d", (100, 90), 3, 60.0, 33, 360, FAN, None),
+    # slabs: 64 rays to a wave, the last wave of one ray; bins wider than the
+    # widest slab; a step longer than a pixel; rays at 45 degrees
+    "par_65_bins": ("par2d", (61, 83), 65, 1.3, 8, 180, {}, None),
+    "par_wide_bins": ("par2d", (70, 64), 50, 1.75, 7, 180, {}, None),
+    "par_very_wide_bins": ("par2d", (70, 64), 40, 2.6, 7, 180, {}, None),
+    "par_diagonal": ("par2d", (200, 190), 280, 1.0, 8, 360, {}, None),
+    "fan_steep": ("fan2d", (80, 300), 400, 1.2, 12, 360, dict(sid=190.0, sdd=300.0), None),
     "arc_short": ("fan2d_curved", (90, 128), 190, 1.1, 37, 220, FAN, None),
 }
 
@@ -48,9 +55,28 @@ def test_pair_2d_edges(ph, ora, name):
     rng = np.random.default_rng(3)
     # positive values: a sum of terms that do not cancel keeps the coordinates'
     # rounding (2^-17 pixel and bin) at 1e-5 of itself
+    # enough items of the same two images for the slab kernel (512 waves of
+    # rays), and the two alone for the direct one
     f = as_f32(rng.uniform(0.5, 1.5, (2,) + spec.vol_shape))
     p = as_f32(rng.uniform(0.5, 1.5, (2, views, nu)))
+    many = -(-512 // (-(-nu // 64) * views) // 2)
     A, B = (ph.project_fan2d, ph.backproject_fan2d) if fan else (ph.project_par2d, ph.backproject_par2d)
     say(f"[A, B 2D] {name}")
     check(to_np(A(g, rv, to_dev(f))), np.stack([ora.project(spec, v) for v in f]), "A", tol=2e-5)
+    out = A(g, rv, to_dev(f).repeat(many, 1, 1))
+    check(to_np(out[:2]), np.stack([ora.project(spec, v) for v in f]), "A, many items", tol=2e-5)
+    assert (out.view((many, 2) + tuple(out.shape[1:])) == out[:2]).all()
     check(to_np(B(g, rv, to_dev(p))), np.stack([ora.backproject(spec, v) for v in p]), "B", tol=2e-5)
+
+
+@pytest.mark.parametrize("step", [0.1, 0.7, 1.0, 1.3])
+def test_project_2d_steps(ph, ora, step):
+    """Sampling steps from a tenth of a pixel to more than one."""
+    spec = synth.config("par2d_64").with_(vol_shape=(90, 75), vol_spacing=(1.0, 1.2), det_shape=(131,),
+                                          det_spacing=(0.9,), n_proj=9, step_mm=step)
+    g = ph.from_spec(spec)
+    rv = ph.ray_vectors_2d(g)
+    f = as_f32(np.random.default_rng(8).uniform(0.5, 1.5, spec.vol_shape))
+    ref = ora.project(spec, f)
+    check(to_np(ph.project_par2d(g, rv, to_dev(f))), ref, f"step {step}, direct", tol=2e-5)
+    check(to_np(ph.project_par2d(g, rv, to_dev(f).repeat(20, 1, 1))[19]), ref, f"step {step}, slabs", tol=2e-5)
