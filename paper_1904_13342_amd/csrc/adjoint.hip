@@ -670,12 +670,15 @@ hipError_t fpT2d_v(const Geom2D &g, const float2 *views, const void *sino, void 
     const long tiles = (long)ntx * nty * batch;
     if (tiles > 0x7fffffffL)
         return hipErrorInvalidConfiguration;
-    // waves per tile: about 32 on every CU, at least two views each
-    int waves = 1;
-    while (waves < 16 && tiles * waves < 8192 && 2 * V * waves <= g.n_proj)
-        waves *= 2;
-    hipLaunchKernelGGL((fpT2d_kernel<T, TI, FAN, V>), dim3((unsigned)tiles), dim3(64 * waves),
-                       64 * waves * sizeof(TileRay), s, g, views, (const TI *)sino, (T *)img, ntx, nty);
+    // waves per tile: about 32 on every CU in all, at least V views each (a
+    // small image's time is one wave's chain of views: 256^2 with 30 views, 15.0
+    // us for four waves of eight views, 13.2 us for eight of four)
+    long waves = (8192 + tiles - 1) / tiles;
+    const long most = (g.n_proj + V - 1) / V;
+    waves = waves < most ? waves : most;
+    waves = waves < 16 ? waves : 16;
+    hipLaunchKernelGGL((fpT2d_kernel<T, TI, FAN, V>), dim3((unsigned)tiles), dim3((unsigned)(64 * waves)),
+                       (size_t)(64 * waves) * sizeof(TileRay), s, g, views, (const TI *)sino, (T *)img, ntx, nty);
     return hipGetLastError();
 }
 

@@ -30,7 +30,8 @@ __device__ __forceinline__ float sample_direct(const T *im, const Geom2D &g, flo
     return fmaf(ty, a1 - a0, a0);
 }
 
-constexpr int UNROLL2D = 4;   // samples (A) or views (B) per lane whose loads are in flight together
+constexpr int A_UNROLL = 2;   // samples per lane of A whose loads are in flight together
+constexpr int B_UNROLL = 4;   // views per wave of B
 
 // Narrow [lo, hi] to the sample range inside the open interval (a, b) of
 // index coordinates.
@@ -49,7 +50,8 @@ __device__ __forceinline__ bool krange(float p, float e, float a, float b, float
 // sums meet in a fixed shuffle tree.  Small problems (few rays, long rays)
 // then still fill the machine.
 //
-// A lane takes four samples at a time.  Where every sample of the wave's four
+// A lane takes two samples at a time (four or eight leave more of a short ray
+// to its checked ends).  Where every sample of the wave's two
 // has its 2 x 2 cell inside the image (all but a ray's ends), the cell is
 // read as two pairs at 32-bit offsets from the image, without bounds checks:
 // 17 vector operations and two loads a sample.  Elsewhere the four pixels
@@ -87,12 +89,12 @@ __global__ void __launch_bounds__(256) fp2d_kernel(Geom2D g, const float2 *__res
                            krange(Y0, eY, ey, (float)(g.ny - 1) - ey, ilo, ihi) &&
                            (size_t)g.nx * g.ny * sizeof(T) <= 0xffffffffu && g.nx < (1 << 24) && g.ny < (1 << 24);
         const int in_lo = cells ? (int)ceilf(ilo) : 1, in_hi = cells ? (int)floorf(ihi) : 0;
-        for (int m = k0 + s; m <= k1; m += UNROLL2D * S) {
-            if (__all(m >= in_lo && m + (UNROLL2D - 1) * S <= in_hi)) {
-                float2 p[UNROLL2D], q[UNROLL2D];
-                float tx[UNROLL2D], ty[UNROLL2D];
+        for (int m = k0 + s; m <= k1; m += A_UNROLL * S) {
+            if (__all(m >= in_lo && m + (A_UNROLL - 1) * S <= in_hi)) {
+                float2 p[A_UNROLL], q[A_UNROLL];
+                float tx[A_UNROLL], ty[A_UNROLL];
 #pragma unroll
-                for (int u = 0; u < UNROLL2D; ++u) {
+                for (int u = 0; u < A_UNROLL; ++u) {
                     const float fm = (float)(m + u * S), X = fmaf(fm, eX, X0), Y = fmaf(fm, eY, Y0);
                     tx[u] = __builtin_amdgcn_fractf(X);
                     ty[u] = __builtin_amdgcn_fractf(Y);
@@ -101,13 +103,13 @@ __global__ void __launch_bounds__(256) fp2d_kernel(Geom2D g, const float2 *__res
                     q[u] = load_pair(im1, off);
                 }
 #pragma unroll
-                for (int u = 0; u < UNROLL2D; ++u) {
+                for (int u = 0; u < A_UNROLL; ++u) {
                     const float a0 = fmaf(tx[u], p[u].y - p[u].x, p[u].x), a1 = fmaf(tx[u], q[u].y - q[u].x, q[u].x);
                     acc += fmaf(ty[u], a1 - a0, a0);
                 }
             } else {
 #pragma unroll
-                for (int u = 0; u < UNROLL2D; ++u) {
+                for (int u = 0; u < A_UNROLL; ++u) {
                     const float fm = (float)(m + u * S);
                     const float v = sample_direct(im, g, fmaf(fm, eX, X0), fmaf(fm, eY, Y0));
                     acc += m + u * S <= k1 ? v : 0.0f;
@@ -401,26 +403,26 @@ __global__ void __launch_bounds__(1024) bp2d_kernel(Geom2D g, const float2 *__re
     const TI *sb = sino + (size_t)b * g.n_proj * g.nu;
     const float x = fmaf((float)min(ix, g.nx - 1), g.sx, g.ox), y = fmaf((float)min(iy, g.ny - 1), g.sy, g.oy);
     float acc = 0.0f;
-    for (int k0 = wave; k0 < g.n_proj; k0 += UNROLL2D * waves) {
-        float fu[UNROLL2D], t[UNROLL2D], wt[UNROLL2D];
+    for (int k0 = wave; k0 < g.n_proj; k0 += B_UNROLL * waves) {
+        float fu[B_UNROLL], t[B_UNROLL], wt[B_UNROLL];
         bool inside = true;
 #pragma unroll
-        for (int u = 0; u < UNROLL2D; ++u) {
+        for (int u = 0; u < B_UNROLL; ++u) {
             const int k = min(k0 + u * waves, g.n_proj - 1);
             point2d<FAN>(g, views[k], x, y, fu[u], t[u], wt[u]);
             inside = inside && fu[u] >= 0.0f && fu[u] < (float)(g.nu - 1);
         }
-        if (__all(inside) && k0 + (UNROLL2D - 1) * waves < g.n_proj) {
-            float2 p[UNROLL2D];
+        if (__all(inside) && k0 + (B_UNROLL - 1) * waves < g.n_proj) {
+            float2 p[B_UNROLL];
 #pragma unroll
-            for (int u = 0; u < UNROLL2D; ++u)
+            for (int u = 0; u < B_UNROLL; ++u)
                 p[u] = load_pair(sb + (size_t)(k0 + u * waves) * g.nu, (unsigned)fu[u] * (unsigned)sizeof(TI));
 #pragma unroll
-            for (int u = 0; u < UNROLL2D; ++u)
+            for (int u = 0; u < B_UNROLL; ++u)
                 acc = fmaf(wt[u], fmaf(t[u], p[u].y - p[u].x, p[u].x), acc);
         } else {
 #pragma unroll
-            for (int u = 0; u < UNROLL2D; ++u) {
+            for (int u = 0; u < B_UNROLL; ++u) {
                 const int k = k0 + u * waves, j = (int)fu[u];
                 const TI *row = sb + (size_t)min(k, g.n_proj - 1) * g.nu;
                 const int j0 = min(max(j, 0), g.nu - 1), j1 = min(max(j + 1, 0), g.nu - 1);
@@ -444,16 +446,15 @@ __global__ void __launch_bounds__(1024) bp2d_kernel(Geom2D g, const float2 *__re
         store_f32(img + ((size_t)b * g.ny + iy) * g.nx + ix, g.dbeta * acc);
 }
 
-// Lanes per ray: up to about 2^21 threads in all (512^2, 360 fan views of 725
-// bins: 312, 318, 365, 414 and 700 us for 16, 8, 4, 2 and 1 lanes; more lanes
-// read more of each cache line while it is there), but at least 32 samples of
+// Lanes per ray: up to about 2^21 threads in all, but at least 16 samples of
 // the image's diagonal each, or setting the rays up outweighs sampling them
-// (256^2, 30 parallel views: 21 us at 64 lanes, 16 us at 16).
+// (256^2, 30 parallel views: 16.2, 13.4, 13.6 and 16.0 us for at least 8, 16,
+// 32 and 64 samples per lane; 64^2, 16 views 7.1, 7.1, 10.7 and 19.3 us).
 inline int lanes_per_ray(const Geom2D &g, long rays)
 {
     const float wx = g.nx * g.sx, wy = g.ny * g.sy, samples = sqrtf(wx * wx + wy * wy) / g.step;
     int S = 1;
-    while (S < 64 && rays * S * 2 <= (1L << 21) && 64.0f * (float)S <= samples)
+    while (S < 64 && rays * S * 2 <= (1L << 21) && 32.0f * (float)S <= samples)
         S *= 2;
     return S;
 }
