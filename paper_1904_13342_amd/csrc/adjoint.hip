@@ -663,6 +663,93 @@ __global__ void __launch_bounds__(1024) bpT2d_kernel(Geom2D g, const float2 *__r
         sino[((size_t)b * g.n_proj + k) * g.nu + j] = a0 + below;
 }
 
+// The same gather from the pixels' side, where a view's bins fit a wave's LDS.
+// A wave takes runs of 64 neighbouring pixels along the axis on which the
+// detector coordinate moves faster, one run after the other, and adds each
+// pixel's two terms to the (1 - t, t) pair of its strip in its own LDS, plainly
+// read, added and written: the coordinate moves by at least 1 / P of a bin per
+// pixel, so the lanes of one residue mod P never share a strip, and P such
+// passes need no atomics (a run that breaks the rule, as a fan's may at the
+// edge, falls back to LDS atomics; within one wave those too come in a fixed
+// order).  Every pixel is evaluated once, where the strips above test two or
+// three candidates for each that they hold.  The waves of a workgroup share a
+// view and meet in LDS in a fixed order.
+constexpr int RUN_COLS = 4;   // runs whose pixels are loaded together
+
+template <typename TI, bool FAN, int P>
+__global__ void __launch_bounds__(1024) bpT2d_run_kernel(Geom2D g, const float2 *__restrict__ views,
+                                                         const TI *__restrict__ img, float *__restrict__ sino)
+{
+    extern __shared__ float2 part[];   // g.nu + 1 strips (-1 .. nu - 1) per wave
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int waves = blockDim.x >> 6, strips = g.nu + 1;
+    const int k = (int)(blockIdx.x % (unsigned)g.n_proj), b = (int)(blockIdx.x / (unsigned)g.n_proj);
+    const float2 c = views[k];
+    const TI *im = img + (size_t)b * g.nx * g.ny;
+    float2 *own = part + wave * strips;
+    for (int n = lane; n < strips; n += 64)
+        own[n] = make_float2(0.0f, 0.0f);
+    wave_lds_fence();
+    // runs along x (rows of the image), or along y
+    const bool along_x = fabsf(c.y) * g.sx >= fabsf(c.x) * g.sy;
+    const int nq = along_x ? g.nx : g.ny, np = along_x ? g.ny : g.nx;
+    const int chunks = (nq + 63) / 64, groups = (np + RUN_COLS - 1) / RUN_COLS;
+    // units of RUN_COLS runs of one chunk; a wave's units are spread so that
+    // the workgroup's waves read the same cache lines when runs go along y
+    for (int u = wave; u < chunks * groups; u += waves) {
+        const int q = u / groups * 64 + lane, p0 = u % groups * RUN_COLS;
+        const int qc = min(q, nq - 1);
+        float val[RUN_COLS];
+#pragma unroll
+        for (int r = 0; r < RUN_COLS; ++r) {
+            const int pc = min(p0 + r, np - 1);
+            val[r] = load_f32(im + (along_x ? (size_t)pc * g.nx + qc : (size_t)qc * g.nx + pc));
+        }
+#pragma unroll
+        for (int r = 0; r < RUN_COLS; ++r) {
+            const int p = p0 + r;
+            if (p >= np)   // uniform
+                break;
+            const float x = fmaf((float)(along_x ? qc : p), g.sx, g.ox), y = fmaf((float)(along_x ? p : qc), g.sy, g.oy);
+            float fu, t, wt;
+            point2d<FAN>(g, c, x, y, fu, t, wt);
+            const float v = FAN ? wt * val[r] : val[r];
+            const float w1 = v * t, w0 = v * (1.0f - t);
+            // strips -1 .. nu - 1; the rest of the lanes, and those past the run, add nothing
+            const bool used = q < nq && fu >= -1.0f && fu < (float)g.nu;
+            const int n = used ? (int)fu + 1 : 0;
+            // neighbours P lanes apart must hold different strips
+            const float ahead = __shfl_down(fu, P);
+            if (__any(used && lane + P < 64 && q + P < nq && fabsf(ahead - fu) < 1.0f)) {
+                if (used) {
+                    unsafeAtomicAdd(&own[n].x, w0);
+                    unsafeAtomicAdd(&own[n].y, w1);
+                }
+                continue;
+            }
+#pragma unroll
+            for (int h = 0; h < P; ++h) {
+                if (used && (P == 1 || lane % P == h)) {
+                    float2 s = own[n];
+                    s.x += w0;
+                    s.y += w1;
+                    own[n] = s;
+                }
+                __builtin_amdgcn_wave_barrier();
+            }
+        }
+    }
+    __syncthreads();
+    for (int j = threadIdx.x; j < g.nu; j += blockDim.x) {
+        float s0 = 0.0f, s1 = 0.0f;
+        for (int w = 0; w < waves; ++w) {
+            s0 += part[w * strips + j + 1].x;
+            s1 += part[w * strips + j].y;
+        }
+        sino[((size_t)b * g.n_proj + k) * g.nu + j] = g.dbeta * (s0 + s1);
+    }
+}
+
 template <typename T, typename TI, bool FAN, int V>
 hipError_t fpT2d_v(const Geom2D &g, const float2 *views, const void *sino, void *img, int batch, hipStream_t s)
 {
@@ -797,10 +884,45 @@ hipError_t launch_project_adjoint_cone(int dtype, const Geom3D &g, const ConeFPV
     }
 }
 
+template <typename TI, int P>
+hipError_t bpT2d_run(bool fan, const Geom2D &g, const float2 *views, const void *img, float *sino, int batch,
+                     int waves, hipStream_t stream)
+{
+    const dim3 grid((unsigned)(g.n_proj * batch)), block(64 * waves);
+    const size_t lds = (size_t)waves * (g.nu + 1) * sizeof(float2);
+    if (fan)
+        hipLaunchKernelGGL((bpT2d_run_kernel<TI, true, P>), grid, block, lds, stream, g, views, (const TI *)img, sino);
+    else
+        hipLaunchKernelGGL((bpT2d_run_kernel<TI, false, P>), grid, block, lds, stream, g, views, (const TI *)img, sino);
+    return hipGetLastError();
+}
+
 template <typename TI>
 hipError_t bpT2d(bool fan, const Geom2D &g, const float2 *views, const void *img, float *sino, int batch,
                  hipStream_t stream)
 {
+    // Runs, where a view per workgroup fills the GPU or the image is small (256^2
+    // parallel, 60, 180 and 2880 views in all: strips 28, 46 and 470 us, runs
+    // 32, 32 and 280; 512^2, 60 and 180: strips 56 and 131, runs 169 and 169;
+    // 128^2 and 64^2: runs no slower at any number) and the pixels of a run move
+    // by at least a quarter of a bin: the faster axis moves by 1 / sqrt(2) of a
+    // spacing on the detector, seen from the far side of the image.
+    const float wx = g.nx * g.sx, wy = g.ny * g.sy;
+    const float rate = 0.7071f * fminf(g.sx, g.sy) * (fan ? g.ru / (g.sid + 0.5f * sqrtf(wx * wx + wy * wy)) : g.ru);
+    const int P = rate >= 1.0f ? 1 : rate >= 0.5f ? 2 : rate >= 0.3334f ? 3 : rate >= 0.25f ? 4 : 0;
+    const long items = (long)g.n_proj * batch;
+    const size_t bins = (size_t)(g.nu + 1) * sizeof(float2);   // LDS per wave; at most 64 KiB per workgroup
+    if (P > 0 && bins <= 65536 && items <= 0x7fffffffL && (items >= 256 || (long)g.nx * g.ny <= 128 * 128)) {
+        int rw = 1;
+        while (rw < 16 && items * rw < 16384 && 2 * rw * bins <= 65536)
+            rw *= 2;
+        switch (P) {
+        case 1: return bpT2d_run<TI, 1>(fan, g, views, img, sino, batch, rw, stream);
+        case 2: return bpT2d_run<TI, 2>(fan, g, views, img, sino, batch, rw, stream);
+        case 3: return bpT2d_run<TI, 3>(fan, g, views, img, sino, batch, rw, stream);
+        default: return bpT2d_run<TI, 4>(fan, g, views, img, sino, batch, rw, stream);
+        }
+    }
     const int groups = (g.nu + 62) / 63;
     const long blocks = (long)groups * g.n_proj * batch;
     if (blocks > 0x7fffffffL)

@@ -68,6 +68,41 @@ def test_backproject_adjoint_2d_edges(ph, ora, name):
 
 
 @pytest.mark.parametrize("name", list(CASES))
+def test_backproject_adjoint_2d_many_items(ph, ora, name):
+    """Enough items that a view's workgroup takes whole runs of pixels
+    (images up to 128^2 do at any number), and an image large enough that few
+    items go by strips."""
+    import numpy as np
+    spec, g, rv, fan = _setup(ph, name)
+    f = as_f32(np.random.default_rng(7).uniform(0.5, 1.5, (2,) + spec.vol_shape))
+    bT = ph.backproject_adjoint_fan2d if fan else ph.backproject_adjoint_par2d
+    many = -(-256 // spec.n_proj)
+    out = bT(g, rv, to_dev(f).repeat(many, 1, 1))
+    say(f"[B^T 2D, {2 * many} items] {name}")
+    check(to_np(out[:2]), np.stack([ora.backproject_adjoint(spec, v) for v in f]), name)
+    assert (out.view((many, 2) + tuple(out.shape[1:])) == out[:2]).all()
+
+
+@pytest.mark.parametrize("kind,du", [("par2d", 0.6), ("par2d", 1.0), ("par2d", 1.9), ("par2d", 2.5), ("par2d", 3.5),
+                                     ("fan2d", 1.1), ("fan2d_curved", 1.9)])
+def test_backproject_adjoint_2d_strips_and_runs(ph, ora, kind, du):
+    """A 140 x 150 image, a few views (strips) and 260 (runs), for bins of a
+    fraction of a pixel to several."""
+    import numpy as np
+    src = dict(sid=400.0, sdd=640.0) if kind != "par2d" else {}
+    fan = kind != "par2d"
+    for views in (12, 260):
+        spec = synth.config("par2d_64").with_(kind=kind, vol_shape=(140, 150), vol_spacing=(1.0, 1.0),
+                                              det_shape=(int(330 / du),), det_spacing=(du,), n_proj=views,
+                                              angular_range=2 * math.pi, **src)
+        g = ph.from_spec(spec)
+        f = as_f32(np.random.default_rng(11).uniform(0.5, 1.5, spec.vol_shape))
+        bT = ph.backproject_adjoint_fan2d if fan else ph.backproject_adjoint_par2d
+        say(f"[B^T 2D] {kind} bins of {du}, {views} views")
+        check(to_np(bT(g, ph.ray_vectors_2d(g), to_dev(f))), ora.backproject_adjoint(spec, f), "B^T")
+
+
+@pytest.mark.parametrize("name", list(CASES))
 def test_project_adjoint_2d_edges(ph, ora, name):
     import numpy as np
     spec, g, rv, fan = _setup(ph, name)
