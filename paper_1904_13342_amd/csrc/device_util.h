@@ -162,7 +162,7 @@ __device__ __forceinline__ float atan_small(float z)
 // atan_small of the slope, taken from the pi / 4 or pi / 2 direction beyond
 // tan(pi / 8) and tan(3 pi / 8).  The back-projector and its transpose both
 // use this, so they see the same coordinates.
-template <bool FAN>
+template <bool FAN, int FORM = 0>
 __device__ __forceinline__ void point2d(const Geom2D &g, float2 c, float x, float y, float &fu, float &t, float &wt)
 {
     const float xu = fmaf(y, c.x, -(x * c.y));
@@ -170,21 +170,25 @@ __device__ __forceinline__ void point2d(const Geom2D &g, float2 c, float x, floa
     wt = 1.0f;
     if (FAN) {
         const float w = fmaf(x, c.x, fmaf(y, c.y, g.sid));
-        if (!g.curved) {
+        if (FORM == 1 || (FORM == 0 && !g.curved)) {
             const float rw = rcp_nr(w), q0 = xu * rw, sw = g.sid * rw;
             q = fmaf(fmaf(-q0, w, xu), rw, q0);   // xu / w
             wt = sw * sw;
         } else {
             wt = g.sid * g.sid * rcp_nr(fmaf(w, w, xu * xu));
             const float a = fabsf(xu);
-            float num = a, den = w;
-            if (a > 0.41421357f * w) {
-                const bool steep = a > 2.4142135f * w;
-                num = steep ? -w : a - w;
-                den = steep ? a : a + w;
-                off = copysignf(steep ? 1.57079633f : 0.78539816f, xu);
+            if (FORM == 0 && __any(a > 0.41421357f * w)) {
+                float num = a, den = w;
+                if (a > 0.41421357f * w) {
+                    const bool steep = a > 2.4142135f * w;
+                    num = steep ? -w : a - w;
+                    den = steep ? a : a + w;
+                    off = copysignf(steep ? 1.57079633f : 0.78539816f, xu);
+                }
+                q = copysignf(1.0f, xu) * atan_small(div_nr(num, den));
+            } else {   // the same value: every step is odd in xu
+                q = atan_small(div_nr(xu, w));
             }
-            q = copysignf(1.0f, xu) * atan_small(div_nr(num, den));
         }
     }
     const float lo = FAN ? (q + off) * g.ru_lo : q * g.ru_lo;

@@ -1,7 +1,8 @@
 // 2D parallel- and fan-beam forward projection (ray-driven, a few lanes per
 // detector bin) and back-projection (voxel-driven, a few waves per 8 x 8 pixels),
 // Sec. II.B.2.  The images of the 2D workloads (at most 512 x 512 FP32,
-// 1 MiB) stay resident in L2, so both kernels read global memory directly.
+// 1 MiB) stay resident in L2; what neighbouring rays or pixels share, A in slabs
+// and B in segments stage once more in LDS.
 #include "device_util.h"
 
 namespace ph {
@@ -389,6 +390,9 @@ __global__ void __launch_bounds__(1024) fp2d_slab_kernel(Geom2D g, const float2 
 // where both bins of all four lie on the detector for the whole wave, each
 // pair is one load, otherwise two masked ones.  (With the lanes of a wave on 4
 // views of 16 pixels: 174 against 112 us for 8 x 256^2 and 360 parallel views.)
+// Taken for single items of fan views, bound by some 38 vector operations for
+// each sample's coordinate (512^2, 360 arc views: 89 us, 1.1 a clock on every
+// CU), and for bins too fine to stage, below.
 template <typename T, typename TI, bool FAN>
 __global__ void __launch_bounds__(1024) bp2d_kernel(Geom2D g, const float2 *__restrict__ views,
                                                     const TI *__restrict__ sino, T *__restrict__ img, int ntx, int nty)
@@ -444,6 +448,172 @@ __global__ void __launch_bounds__(1024) bp2d_kernel(Geom2D g, const float2 *__re
     }
     if (ix < g.nx && iy < g.ny)
         store_f32(img + ((size_t)b * g.ny + iy) * g.nx + ix, g.dbeta * acc);
+}
+
+// B in tiles of 16 x 16 pixels, four to a lane, for NB items of a batch at once.
+// A wave takes a few views at a time: its lanes project the tile's four
+// corners in each of them (the projection of a convex tile in front of the
+// source is extreme at a corner) and stage the W bins from one below the
+// lowest, zero outside the detector, in the wave's own LDS, the items of a bin
+// side by side.  A pixel's coordinate is then found once for all items, and a
+// sample is one read of a pair, with no bounds checks.  The next views' bins are
+// loaded meanwhile.  A view whose corners span more bins than are staged, or lie
+// so far out that FP32 bins round, is read from memory.  The waves of a
+// workgroup share a tile and meet in LDS in a fixed order.  Reading pairs from
+// memory cost about 25 clocks of a CU for each wave's sample; staged, it is 15
+// vector operations, of which an item's own are three (8 x 256^2, 360 parallel
+// views: 122 us from memory, 88 staged one item at a time, 61 and 45 two and
+// four).
+constexpr int SB_BINS = 512;   // views times bins of a chunk
+
+template <typename T, typename TI, bool FAN, int NB, int W>
+__global__ void __launch_bounds__(1024) bp2d_seg_kernel(Geom2D g, const float2 *__restrict__ views,
+                                                        const TI *__restrict__ sino, T *__restrict__ img, int ntx,
+                                                        int nty, int batch)
+{
+    typedef float Items __attribute__((ext_vector_type(NB)));
+    constexpr int LOADS = SB_BINS / 64, V = SB_BINS / W;   // V views to a chunk, at most one lane to a corner
+    // SB_BINS of each wave, at the end its pixels' sums
+    extern __shared__ __align__(16) char seg_lds[];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int waves = blockDim.x >> 6;
+    const unsigned tile = blockIdx.x;
+    const int x0 = 16 * (int)(tile % (unsigned)ntx), y0 = 16 * (int)((tile / (unsigned)ntx) % (unsigned)nty);
+    const int b0 = NB * (int)(tile / ((unsigned)ntx * (unsigned)nty));
+    const size_t item = (size_t)g.n_proj * g.nu;
+    Items *seg = (Items *)seg_lds + wave * SB_BINS;
+    float px[2], py[2];
+#pragma unroll
+    for (int a = 0; a < 2; ++a) {
+        px[a] = fmaf((float)min(x0 + 8 * a + (lane & 7), g.nx - 1), g.sx, g.ox);
+        py[a] = fmaf((float)min(y0 + 8 * a + (lane >> 3), g.ny - 1), g.sy, g.oy);
+    }
+    // lane 4 v + c holds view v's corner c
+    const float qx = fmaf((float)((lane & 1) ? min(x0 + 15, g.nx - 1) : x0), g.sx, g.ox);
+    const float qy = fmaf((float)((lane & 2) ? min(y0 + 15, g.ny - 1) : y0), g.sy, g.oy);
+    float2 cl, cl_next;   // view lane / 4, and its first staged bin
+    int lo, lo_next;
+    unsigned long long ok, ok_next, small, small_next;   // bit 4 v: view v is staged; its fan angles are small
+    Items val[LOADS];
+    auto fetch = [&](int k0) {
+        const float2 c = cl_next = views[min(k0 + (lane >> 2), g.n_proj - 1)];
+        float fu, t, wt;
+        point2d<FAN>(g, c, qx, qy, fu, t, wt);
+        const float w = FAN ? fmaf(qx, c.x, fmaf(qy, c.y, g.sid)) : 1.0f;
+        bool in = fabsf(fu) < 262144.0f;
+        float mn = fu, mx = fu;
+#pragma unroll
+        for (int o = 1; o < 4; o <<= 1) {
+            mn = fminf(mn, __shfl_xor(mn, o));
+            mx = fmaxf(mx, __shfl_xor(mx, o));
+        }
+        in = in && mx - mn <= (float)(W - 4);   // one bin to each side, and the pair's second
+        ok_next = __ballot(in);
+        ok_next &= ok_next >> 1;
+        ok_next &= ok_next >> 2;
+        // below point2d's own bound by more than a rounding
+        small_next = __ballot(fabsf(fmaf(qy, c.x, -(qx * c.y))) < 0.414f * w);
+        small_next &= small_next >> 1;
+        small_next &= small_next >> 2;
+        lo_next = in ? (int)mn - 1 : 0;
+#pragma unroll
+        for (int i = 0; i < LOADS; ++i) {
+            const int v = (64 * i + lane) / W;
+            const int j = __shfl(lo_next, 4 * v) + lane % W, jc = min(max(j, 0), g.nu - 1);
+            const TI *p = sino + (size_t)min(k0 + v, g.n_proj - 1) * g.nu + jc;
+#pragma unroll
+            for (int n = 0; n < NB; ++n) {
+                const float q = load_f32(p + (size_t)min(b0 + n, batch - 1) * item);
+                val[i][n] = j == jc ? q : 0.0f;
+            }
+        }
+    };
+    Items acc[4];
+#pragma unroll
+    for (int a = 0; a < 4; ++a)
+        acc[a] = 0.0f;
+    int k0 = wave * V;
+    if (k0 < g.n_proj)
+        fetch(k0);
+    for (; k0 < g.n_proj; k0 += V * waves) {
+        wave_lds_fence();   // the previous views have been read
+#pragma unroll
+        for (int i = 0; i < LOADS; ++i)
+            seg[64 * i + lane] = val[i];
+        wave_lds_fence();
+        cl = cl_next;
+        lo = lo_next;
+        ok = ok_next;
+        small = small_next;
+        if (k0 + V * waves < g.n_proj)
+            fetch(k0 + V * waves);
+        const int nv = min(V, g.n_proj - k0);
+        for (int v = 0; v < nv; ++v) {
+            const float2 c = make_float2(lane_value(cl.x, 4 * v), lane_value(cl.y, 4 * v));
+            float fu[4], t[4], wt[4];
+            if (FAN && !g.curved) {
+#pragma unroll
+                for (int a = 0; a < 4; ++a)
+                    point2d<FAN, 1>(g, c, px[a & 1], py[a >> 1], fu[a], t[a], wt[a]);
+            } else if (FAN && ((small >> (4 * v)) & 1)) {
+#pragma unroll
+                for (int a = 0; a < 4; ++a)
+                    point2d<FAN, 2>(g, c, px[a & 1], py[a >> 1], fu[a], t[a], wt[a]);
+            } else {
+#pragma unroll
+                for (int a = 0; a < 4; ++a)
+                    point2d<FAN>(g, c, px[a & 1], py[a >> 1], fu[a], t[a], wt[a]);
+            }
+            if ((ok >> (4 * v)) & 1) {
+                const int first = v * W - __builtin_amdgcn_readlane(lo, 4 * v);
+#pragma unroll
+                for (int a = 0; a < 4; ++a) {
+                    const Items *p = seg + ((int)fu[a] + first);
+                    const Items p0 = p[0], p1 = p[1];
+#pragma unroll
+                    for (int n = 0; n < NB; ++n)
+                        acc[a][n] = fmaf(wt[a], fmaf(t[a], p1[n] - p0[n], p0[n]), acc[a][n]);
+                }
+            } else {
+                const TI *row = sino + (size_t)(k0 + v) * g.nu;
+#pragma unroll
+                for (int a = 0; a < 4; ++a) {
+                    const int j = (int)fu[a];
+                    const int j0 = min(max(j, 0), g.nu - 1), j1 = min(max(j + 1, 0), g.nu - 1);
+#pragma unroll
+                    for (int n = 0; n < NB; ++n) {
+                        const TI *q = row + (size_t)min(b0 + n, batch - 1) * item;
+                        float p0 = load_f32(q + j0), p1 = load_f32(q + j1);
+                        p0 = j0 == j ? p0 : 0.0f;
+                        p1 = j1 == j + 1 ? p1 : 0.0f;
+                        acc[a][n] = fmaf(wt[a], fmaf(t[a], p1 - p0, p0), acc[a][n]);
+                    }
+                }
+            }
+        }
+    }
+    if (waves > 1) {
+        wave_lds_fence();
+#pragma unroll
+        for (int a = 0; a < 4; ++a)
+            seg[64 * a + lane] = acc[a];
+        __syncthreads();
+        if (wave > 0)
+            return;
+        for (int w = 1; w < waves; ++w)
+#pragma unroll
+            for (int a = 0; a < 4; ++a)
+                acc[a] += seg[w * SB_BINS + 64 * a + lane];
+    }
+#pragma unroll
+    for (int a = 0; a < 4; ++a) {
+        const int ix = x0 + 8 * (a & 1) + (lane & 7), iy = y0 + 8 * (a >> 1) + (lane >> 3);
+        if (ix < g.nx && iy < g.ny)
+#pragma unroll
+            for (int n = 0; n < NB; ++n)
+                if (b0 + n < batch)
+                    store_f32(img + ((size_t)(b0 + n) * g.ny + iy) * g.nx + ix, g.dbeta * acc[a][n]);
+    }
 }
 
 // Lanes per ray: up to about 2^21 threads in all, but at least 16 samples of
@@ -522,9 +692,60 @@ hipError_t fp2d(bool fan, const Geom2D &g, const float2 *views, const void *img,
     return fan ? fp2d_f<T, true>(g, views, img, sino, batch, s) : fp2d_f<T, false>(g, views, img, sino, batch, s);
 }
 
+template <typename T, typename TI, bool FAN, int NB, int W>
+hipError_t bp2d_seg(const Geom2D &g, const float2 *views, const void *sino, void *img, int batch, hipStream_t s)
+{
+    const int ntx = (g.nx + 15) / 16, nty = (g.ny + 15) / 16;
+    const long tiles = (long)ntx * nty * ((batch + NB - 1) / NB);
+    if (tiles > 0x7fffffffL)
+        return hipErrorInvalidConfiguration;
+    // waves per tile: about 32 on every CU in all (8 x 256^2, 360 parallel views
+    // one item at a time, in the step of learning the filter: 438, 416 and 418
+    // us for 4096, 8192 and 16384), a chunk of views each
+    int waves = 1;
+    while (waves < 8 && tiles * waves < 8192 && (2 * waves - 1) * (SB_BINS / W) < g.n_proj)
+        waves *= 2;
+    hipLaunchKernelGGL((bp2d_seg_kernel<T, TI, FAN, NB, W>), dim3((unsigned)tiles), dim3(64 * waves),
+                       (size_t)waves * SB_BINS * NB * sizeof(float), s, g, views, (const TI *)sino, (T *)img, ntx, nty,
+                       batch);
+    return hipGetLastError();
+}
+
+template <typename T, typename TI, bool FAN, int NB>
+hipError_t bp2d_seg_w(float span, const Geom2D &g, const float2 *views, const void *sino, void *img, int batch,
+                      hipStream_t s)
+{
+    return span <= 28.0f ? bp2d_seg<T, TI, FAN, NB, 32>(g, views, sino, img, batch, s)
+                         : bp2d_seg<T, TI, FAN, NB, 64>(g, views, sino, img, batch, s);
+}
+
 template <typename T, typename TI, bool FAN>
 hipError_t bp2d_f(const Geom2D &g, const float2 *views, const void *sino, void *img, int batch, hipStream_t s)
 {
+    // From staged bins where those of a 16 x 16 tile, at most its diagonal seen
+    // from the near side of the image, fit 64 with the margins.  Items of a
+    // batch go together as long as 256 workgroups are left (180 fan views of
+    // 128^2: 20, 22 us for one and two together of 2 items, with the filter).
+    // Parallel views gain from the staging alone (512^2, 360 views, with the
+    // filter: 74 and 60 us), fan views, bound by the arithmetic of their
+    // coordinates, only where two items or more share it (512^2, 360 arc views
+    // of one, two and five items: 103, 189 and 418 us from memory, 118, 123
+    // and 247 staged).
+    const float wx = g.nx * g.sx, wy = g.ny * g.sy, near = g.sid - 0.5f * sqrtf(wx * wx + wy * wy);
+    const float diag = 15.0f * sqrtf(g.sx * g.sx + g.sy * g.sy);
+    const float span = !FAN ? diag * g.ru : near > 0.0f ? diag * g.ru / near : 3.0e38f;
+    const long pieces = (long)((g.nx + 15) / 16) * ((g.ny + 15) / 16);
+    int nb = 1;
+    while (nb < 4 && nb < batch && pieces * ((batch + 2 * nb - 1) / (2 * nb)) >= 256)
+        nb *= 2;
+    if (span <= 60.0f) {
+        if (nb == 4)
+            return bp2d_seg_w<T, TI, FAN, 4>(span, g, views, sino, img, batch, s);
+        if (nb == 2)
+            return bp2d_seg_w<T, TI, FAN, 2>(span, g, views, sino, img, batch, s);
+        if constexpr (!FAN)
+            return bp2d_seg_w<T, TI, FAN, 1>(span, g, views, sino, img, batch, s);
+    }
     const int ntx = (g.nx + 7) / 8, nty = (g.ny + 7) / 8;
     const long tiles = (long)ntx * nty * batch;
     if (tiles > 0x7fffffffL)

@@ -80,3 +80,36 @@ def test_project_2d_steps(ph, ora, step):
     ref = ora.project(spec, f)
     check(to_np(ph.project_par2d(g, rv, to_dev(f))), ref, f"step {step}, direct", tol=2e-5)
     check(to_np(ph.project_par2d(g, rv, to_dev(f).repeat(20, 1, 1))[19]), ref, f"step {step}, slabs", tol=2e-5)
+
+
+# kind, (ny, nx), nu, du, views, range, source, origin, items: one item and
+# items in groups of two and four with one left over, by number of 16 x 16
+# tiles; 32 and 64 bins to a view, and more than fit; tiles, views and waves
+# with remainders; tiles off the detector
+SEGMENTS = {
+    "par_one": ("par2d", (45, 33), 61, 1.0, 17, 180, {}, None, 1),
+    "par_64_bins": ("par2d", (45, 33), 240, 0.4, 33, 180, {}, None, 1),
+    "par_too_fine": ("par2d", (30, 33), 200, 0.3, 5, 180, {}, None, 2),
+    "par_groups_of_2": ("par2d", (130, 144), 150, 1.0, 31, 180, {}, None, 5),
+    "par_groups_of_4": ("par2d", (257, 270), 300, 1.0, 7, 180, {}, (-140.0, -90.0), 5),
+    "flat_groups_of_2": ("fan2d", (130, 144), 210, 1.7, 31, 360, FAN, None, 5),
+    "flat_64_bins": ("fan2d", (257, 270), 300, 0.9, 7, 360, FAN, None, 3),
+    "arc_groups_of_4": ("fan2d_curved", (257, 270), 400, 1.9, 7, 360, FAN, None, 5),
+    "arc_wide_fan": ("fan2d_curved", (130, 300), 300, 2.6, 19, 360, dict(sid=210.0, sdd=300.0), None, 4),
+    "arc_off_axis": ("fan2d_curved", (130, 300), 300, 2.6, 19, 360, dict(sid=260.0, sdd=420.0), (-60.0, -110.0), 4),
+}
+
+
+@pytest.mark.parametrize("name", list(SEGMENTS))
+def test_backproject_2d_segments(ph, ora, name):
+    kind, shape, nu, du, views, turn, src, origin, items = SEGMENTS[name]
+    spec = synth.config("par2d_64").with_(kind=kind, vol_shape=shape, vol_spacing=(1.0, 1.0), det_shape=(nu,),
+                                          det_spacing=(du,), n_proj=views, angular_range=turn * math.pi / 180,
+                                          vol_origin=origin, **src)
+    g = ph.from_spec(spec)
+    p = as_f32(np.random.default_rng(5).uniform(0.5, 1.5, (items, views, nu)))
+    B = ph.backproject_fan2d if kind != "par2d" else ph.backproject_par2d
+    say(f"[B 2D segments] {name}")
+    out = to_np(B(g, ph.ray_vectors_2d(g), to_dev(p)))
+    for n in {0, items // 2, items - 1}:
+        check(out[n], ora.backproject(spec, p[n]), f"item {n}", tol=2e-5)
