@@ -663,32 +663,59 @@ __global__ void __launch_bounds__(1024) bpT2d_kernel(Geom2D g, const float2 *__r
         sino[((size_t)b * g.n_proj + k) * g.nu + j] = a0 + below;
 }
 
+// The value of the next or previous lane of the wave (DPP wavefront shifts by
+// one), `end` in the last or first one.
+__device__ __forceinline__ int next_lane(int x, int end)
+{
+    return __builtin_amdgcn_update_dpp(end, x, 0x130, 0xF, 0xF, false);
+}
+__device__ __forceinline__ float next_lane(float x, float end)
+{
+    return __int_as_float(next_lane(__float_as_int(x), __float_as_int(end)));
+}
+__device__ __forceinline__ int prev_lane(int x, int end)
+{
+    return __builtin_amdgcn_update_dpp(end, x, 0x138, 0xF, 0xF, false);
+}
+
 // The same gather from the pixels' side, where a view's bins fit a wave's LDS.
 // A wave takes runs of 64 neighbouring pixels along the axis on which the
 // detector coordinate moves faster, one run after the other, and adds each
 // pixel's two terms to the (1 - t, t) pair of its strip in its own LDS, plainly
-// read, added and written: the coordinate moves by at least 1 / P of a bin per
-// pixel, so the lanes of one residue mod P never share a strip, and P such
-// passes need no atomics (a run that breaks the rule, as a fan's may at the
-// edge, falls back to LDS atomics; within one wave those too come in a fixed
-// order).  Every pixel is evaluated once, where the strips above test two or
-// three candidates for each that they hold.  The waves of a workgroup share a
-// view and meet in LDS in a fixed order.
-constexpr int RUN_COLS = 4;   // runs whose pixels are loaded together
+// read, added and written, without atomics: the coordinate moves by at least
+// 1 / P of a bin per pixel, so no strip holds pixels P lanes apart.  For P = 2
+// the first of two neighbours in one strip adds the other's terms to its own;
+// beyond, the lanes of one residue mod P go together, in P passes.  (A run that
+// breaks the rule, as a fan's may at the edge, falls back to LDS atomics;
+// within one wave those too come in a fixed order.)  Every pixel is evaluated
+// once, where the strips above test two or three candidates for each that they
+// hold, and once for NB items of a batch.  The waves of a workgroup share a view
+// and meet in LDS in a fixed order.
+//
+// Runs along y read a column, 64 cache lines for a wave; RUN_COLS neighbouring
+// ones are read by wide loads, so that each line is touched twice and not once
+// a run.  8 x 256^2, 360 parallel views: 252 us with four loads of a pixel
+// each, 211 with one of four, 200 with two for eight runs and 155 with two items
+// together, then bound by about 35 vector operations for each run and item.
+constexpr int RUN_COLS = 8;          // runs whose pixels are loaded together
+constexpr size_t RUN_LDS = 65536;    // LDS of a workgroup, at most
 
-template <typename TI, bool FAN, int P>
+template <typename TI, bool FAN, int P, int NB>
 __global__ void __launch_bounds__(1024) bpT2d_run_kernel(Geom2D g, const float2 *__restrict__ views,
-                                                         const TI *__restrict__ img, float *__restrict__ sino)
+                                                         const TI *__restrict__ img, float *__restrict__ sino,
+                                                         int batch)
 {
-    extern __shared__ float2 part[];   // g.nu + 1 strips (-1 .. nu - 1) per wave
+    typedef float Pairs __attribute__((ext_vector_type(2 * NB)));   // (w0, w1) of each item
+    extern __shared__ __align__(32) char run_lds[];   // g.nu + 1 strips (-1 .. nu - 1) per wave
+    Pairs *part = (Pairs *)run_lds;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int waves = blockDim.x >> 6, strips = g.nu + 1;
-    const int k = (int)(blockIdx.x % (unsigned)g.n_proj), b = (int)(blockIdx.x / (unsigned)g.n_proj);
+    const int k = (int)(blockIdx.x % (unsigned)g.n_proj), b0 = NB * (int)(blockIdx.x / (unsigned)g.n_proj);
     const float2 c = views[k];
-    const TI *im = img + (size_t)b * g.nx * g.ny;
-    float2 *own = part + wave * strips;
+    const size_t pixels = (size_t)g.nx * g.ny;
+    Pairs *own = part + wave * strips;
     for (int n = lane; n < strips; n += 64)
-        own[n] = make_float2(0.0f, 0.0f);
+        own[n] = 0.0f;
     wave_lds_fence();
     // runs along x (rows of the image), or along y
     const bool along_x = fabsf(c.y) * g.sx >= fabsf(c.x) * g.sy;
@@ -699,11 +726,23 @@ __global__ void __launch_bounds__(1024) bpT2d_run_kernel(Geom2D g, const float2 
     for (int u = wave; u < chunks * groups; u += waves) {
         const int q = u / groups * 64 + lane, p0 = u % groups * RUN_COLS;
         const int qc = min(q, nq - 1);
-        float val[RUN_COLS];
+        float val[NB][RUN_COLS];
 #pragma unroll
-        for (int r = 0; r < RUN_COLS; ++r) {
-            const int pc = min(p0 + r, np - 1);
-            val[r] = load_f32(im + (along_x ? (size_t)pc * g.nx + qc : (size_t)qc * g.nx + pc));
+        for (int i = 0; i < NB; ++i) {
+            const TI *im = img + (size_t)min(b0 + i, batch - 1) * pixels;
+            if (!along_x && p0 + RUN_COLS <= np) {
+                TI row[RUN_COLS];   // wide loads: the lanes lie on 64 cache lines
+                __builtin_memcpy(row, im + ((size_t)qc * g.nx + p0), sizeof row);
+#pragma unroll
+                for (int r = 0; r < RUN_COLS; ++r)
+                    val[i][r] = load_f32(&row[r]);
+            } else {
+#pragma unroll
+                for (int r = 0; r < RUN_COLS; ++r) {
+                    const int pc = min(p0 + r, np - 1);
+                    val[i][r] = load_f32(im + (along_x ? (size_t)pc * g.nx + qc : (size_t)qc * g.nx + pc));
+                }
+            }
         }
 #pragma unroll
         for (int r = 0; r < RUN_COLS; ++r) {
@@ -713,40 +752,67 @@ __global__ void __launch_bounds__(1024) bpT2d_run_kernel(Geom2D g, const float2 
             const float x = fmaf((float)(along_x ? qc : p), g.sx, g.ox), y = fmaf((float)(along_x ? p : qc), g.sy, g.oy);
             float fu, t, wt;
             point2d<FAN>(g, c, x, y, fu, t, wt);
-            const float v = FAN ? wt * val[r] : val[r];
-            const float w1 = v * t, w0 = v * (1.0f - t);
+            Pairs w;
+#pragma unroll
+            for (int i = 0; i < NB; ++i) {
+                const float v = FAN ? wt * val[i][r] : val[i][r];
+                w[2 * i] = v * (1.0f - t);
+                w[2 * i + 1] = v * t;
+            }
             // strips -1 .. nu - 1; the rest of the lanes, and those past the run, add nothing
             const bool used = q < nq && fu >= -1.0f && fu < (float)g.nu;
-            const int n = used ? (int)fu + 1 : 0;
-            // neighbours P lanes apart must hold different strips
-            const float ahead = __shfl_down(fu, P);
-            if (__any(used && lane + P < 64 && q + P < nq && fabsf(ahead - fu) < 1.0f)) {
+            const int n = used ? (int)fu + 1 : -1;
+            // the strips of the next lane and the one after it, or P lanes on
+            const int next = next_lane(n, -2), far = P == 1 ? next : P == 2 ? next_lane(next, -2) : __shfl_down(n, P);
+            if (__any(used && far == n && (P <= 2 || lane + P < 64))) {
                 if (used) {
-                    unsafeAtomicAdd(&own[n].x, w0);
-                    unsafeAtomicAdd(&own[n].y, w1);
+#pragma unroll
+                    for (int i = 0; i < 2 * NB; ++i)
+                        unsafeAtomicAdd((float *)(own + n) + i, w[i]);
                 }
                 continue;
             }
+            if constexpr (P <= 2) {
+                bool first = used;   // holds its strip's sum
+                if constexpr (P == 2) {
 #pragma unroll
-            for (int h = 0; h < P; ++h) {
-                if (used && (P == 1 || lane % P == h)) {
-                    float2 s = own[n];
-                    s.x += w0;
-                    s.y += w1;
-                    own[n] = s;
+                    for (int i = 0; i < 2 * NB; ++i) {
+                        const float o = next_lane(w[i], 0.0f);
+                        w[i] += next == n ? o : 0.0f;
+                    }
+                    first = used && prev_lane(n, -2) != n;
                 }
-                __builtin_amdgcn_wave_barrier();
+                if (first)
+                    own[n] += w;
+            } else {
+#pragma unroll
+                for (int h = 0; h < P; ++h) {
+                    if (used && lane % P == h)
+                        own[n] += w;
+                    __builtin_amdgcn_wave_barrier();
+                }
             }
+            __builtin_amdgcn_wave_barrier();
         }
     }
     __syncthreads();
     for (int j = threadIdx.x; j < g.nu; j += blockDim.x) {
-        float s0 = 0.0f, s1 = 0.0f;
+        float s0[NB], s1[NB];
+#pragma unroll
+        for (int i = 0; i < NB; ++i)
+            s0[i] = s1[i] = 0.0f;
         for (int w = 0; w < waves; ++w) {
-            s0 += part[w * strips + j + 1].x;
-            s1 += part[w * strips + j].y;
+            const Pairs above = part[w * strips + j + 1], below = part[w * strips + j];
+#pragma unroll
+            for (int i = 0; i < NB; ++i) {
+                s0[i] += above[2 * i];
+                s1[i] += below[2 * i + 1];
+            }
         }
-        sino[((size_t)b * g.n_proj + k) * g.nu + j] = g.dbeta * (s0 + s1);
+#pragma unroll
+        for (int i = 0; i < NB; ++i)
+            if (b0 + i < batch)
+                sino[((size_t)(b0 + i) * g.n_proj + k) * g.nu + j] = g.dbeta * (s0[i] + s1[i]);
     }
 }
 
@@ -884,43 +950,63 @@ hipError_t launch_project_adjoint_cone(int dtype, const Geom3D &g, const ConeFPV
     }
 }
 
-template <typename TI, int P>
+template <typename TI, int P, int NB>
 hipError_t bpT2d_run(bool fan, const Geom2D &g, const float2 *views, const void *img, float *sino, int batch,
-                     int waves, hipStream_t stream)
+                     hipStream_t stream)
 {
-    const dim3 grid((unsigned)(g.n_proj * batch)), block(64 * waves);
-    const size_t lds = (size_t)waves * (g.nu + 1) * sizeof(float2);
+    const long groups = (long)g.n_proj * ((batch + NB - 1) / NB);
+    const size_t bins = (size_t)(g.nu + 1) * NB * sizeof(float2);   // LDS per wave
+    int waves = 1;
+    while (waves < 16 && groups * waves < 16384 && 2 * waves * bins <= RUN_LDS)
+        waves *= 2;
+    const dim3 grid((unsigned)groups), block(64 * waves);
+    const size_t lds = (size_t)waves * bins;
     if (fan)
-        hipLaunchKernelGGL((bpT2d_run_kernel<TI, true, P>), grid, block, lds, stream, g, views, (const TI *)img, sino);
+        hipLaunchKernelGGL((bpT2d_run_kernel<TI, true, P, NB>), grid, block, lds, stream, g, views, (const TI *)img,
+                           sino, batch);
     else
-        hipLaunchKernelGGL((bpT2d_run_kernel<TI, false, P>), grid, block, lds, stream, g, views, (const TI *)img, sino);
+        hipLaunchKernelGGL((bpT2d_run_kernel<TI, false, P, NB>), grid, block, lds, stream, g, views, (const TI *)img,
+                           sino, batch);
     return hipGetLastError();
+}
+
+template <typename TI, int P>
+hipError_t bpT2d_run_p(int nb, bool fan, const Geom2D &g, const float2 *views, const void *img, float *sino, int batch,
+                       hipStream_t stream)
+{
+    return nb == 2 ? bpT2d_run<TI, P, 2>(fan, g, views, img, sino, batch, stream)
+                   : bpT2d_run<TI, P, 1>(fan, g, views, img, sino, batch, stream);
 }
 
 template <typename TI>
 hipError_t bpT2d(bool fan, const Geom2D &g, const float2 *views, const void *img, float *sino, int batch,
                  hipStream_t stream)
 {
-    // Runs, where a view per workgroup fills the GPU or the image is small (256^2
-    // parallel, 60, 180 and 2880 views in all: strips 28, 46 and 470 us, runs
-    // 32, 32 and 280; 512^2, 60 and 180: strips 56 and 131, runs 169 and 169;
-    // 128^2 and 64^2: runs no slower at any number) and the pixels of a run move
-    // by at least a quarter of a bin: the faster axis moves by 1 / sqrt(2) of a
-    // spacing on the detector, seen from the far side of the image.
+    // Runs, where a view per workgroup fills the GPU or the image is small
+    // (strips and runs, us: 256^2, 60, 120 and 180 parallel views 29 and 28, 30
+    // and 29, 46 and 28, fan views 25 and 34, 39 and 34, 50 and 34; 512^2, 180,
+    // 256 and 360 parallel views 131 and 153, 139 and 154, 245 and 196, arc views
+    // 219 and 246, 261 and 246, 385 and 294; 128^2 and 64^2: runs no slower at
+    // any number) and the pixels of a run move by at least a quarter of a bin:
+    // the faster axis moves by 1 / sqrt(2) of a spacing on the detector, seen
+    // from the far side of the image.
     const float wx = g.nx * g.sx, wy = g.ny * g.sy;
     const float rate = 0.7071f * fminf(g.sx, g.sy) * (fan ? g.ru / (g.sid + 0.5f * sqrtf(wx * wx + wy * wy)) : g.ru);
     const int P = rate >= 1.0f ? 1 : rate >= 0.5f ? 2 : rate >= 0.3334f ? 3 : rate >= 0.25f ? 4 : 0;
     const long items = (long)g.n_proj * batch;
-    const size_t bins = (size_t)(g.nu + 1) * sizeof(float2);   // LDS per wave; at most 64 KiB per workgroup
-    if (P > 0 && bins <= 65536 && items <= 0x7fffffffL && (items >= 256 || (long)g.nx * g.ny <= 128 * 128)) {
-        int rw = 1;
-        while (rw < 16 && items * rw < 16384 && 2 * rw * bins <= 65536)
-            rw *= 2;
+    const size_t bins = (size_t)(g.nu + 1) * sizeof(float2);   // LDS per wave and item
+    // Two items of a batch together, where eight waves of a workgroup still find
+    // LDS and the chip is filled (parallel, 256^2: 180 views of 2 and 5 items and
+    // 360 of 8: 43, 76 and 200 us alone, 52, 75 and 155 by twos; 512^2, 360 fan
+    // views of 1020 bins, four waves to a workgroup: 382 and 452).
+    const int nb = batch > 1 && 16 * bins <= RUN_LDS && (long)g.n_proj * ((batch + 1) / 2) >= 512 ? 2 : 1;
+    const long pixels = (long)g.nx * g.ny, least = pixels <= 128 * 128 ? 1 : pixels <= 256 * 256 ? 96 : 256;
+    if (P > 0 && bins <= RUN_LDS && items <= 0x7fffffffL && items >= least) {
         switch (P) {
-        case 1: return bpT2d_run<TI, 1>(fan, g, views, img, sino, batch, rw, stream);
-        case 2: return bpT2d_run<TI, 2>(fan, g, views, img, sino, batch, rw, stream);
-        case 3: return bpT2d_run<TI, 3>(fan, g, views, img, sino, batch, rw, stream);
-        default: return bpT2d_run<TI, 4>(fan, g, views, img, sino, batch, rw, stream);
+        case 1: return bpT2d_run_p<TI, 1>(nb, fan, g, views, img, sino, batch, stream);
+        case 2: return bpT2d_run_p<TI, 2>(nb, fan, g, views, img, sino, batch, stream);
+        case 3: return bpT2d_run_p<TI, 3>(nb, fan, g, views, img, sino, batch, stream);
+        default: return bpT2d_run_p<TI, 4>(nb, fan, g, views, img, sino, batch, stream);
         }
     }
     const int groups = (g.nu + 62) / 63;

@@ -83,6 +83,26 @@ def test_backproject_adjoint_2d_many_items(ph, ora, name):
     assert (out.view((many, 2) + tuple(out.shape[1:])) == out[:2]).all()
 
 
+@pytest.mark.parametrize("name", list(CASES))
+def test_backproject_adjoint_2d_item_pairs(ph, ora, name):
+    """An odd number of items, enough that runs take them two at a time."""
+    import numpy as np
+    import torch
+    spec, g, rv, fan = _setup(ph, name)
+    f = as_f32(np.random.default_rng(9).uniform(0.5, 1.5, (3,) + spec.vol_shape))
+    bT = ph.backproject_adjoint_fan2d if fan else ph.backproject_adjoint_par2d
+    pairs = -(-512 // spec.n_proj) + 1
+    x = torch.cat([to_dev(f[:2]).repeat(pairs, 1, 1), to_dev(f[2:])])
+    out = bT(g, rv, x)
+    say(f"[B^T 2D, {2 * pairs + 1} items] {name}")
+    check(to_np(out[[0, 1, -1]]), np.stack([ora.backproject_adjoint(spec, v) for v in f]), name)
+    assert (out[:-1].view((pairs, 2) + tuple(out.shape[1:])) == out[:2]).all()
+    assert (bT(g, rv, x) == out).all()
+    # half storage: the sums are FP32, so pairs and single items differ by one rounding at most
+    half, one = bT(g, rv, x.half())[:1].float(), bT(g, rv, x[:1].half()).float()
+    assert float((half - one).abs().max()) <= 2.0 ** -10 * float(one.abs().max())
+
+
 @pytest.mark.parametrize("kind,du", [("par2d", 0.6), ("par2d", 1.0), ("par2d", 1.9), ("par2d", 2.5), ("par2d", 3.5),
                                      ("fan2d", 1.1), ("fan2d_curved", 1.9)])
 def test_backproject_adjoint_2d_strips_and_runs(ph, ora, kind, du):
