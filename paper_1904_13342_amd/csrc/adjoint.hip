@@ -22,20 +22,24 @@ namespace {
 
 // --------------------------------------------------------------- A^T, 2D
 
-// A wave owns a tile of 8 x 8 pixels and takes one view at a time.  The rays
-// that can cross the tile (the bins of its footprint, a few dozen) are set up
-// once for all its pixels, a ray per lane and up to four views at once, in
-// double precision and exactly as the projector sets them up, and put in LDS
-// with the reciprocals of their steps; then every lane gathers over the two or
-// three rays that cross its own pixel's support, clipping each to it.  Setting the ray up in every
-// pixel instead is what the time went to: 3.19 ms for 512^2 and 360 fan views
-// of 725 bins, against 0.61 ms (0.80 ms setting up one view at a time); 256^2
-// with 30 parallel views of 363 bins went from 46 to 16 us.  VALU-bound.  The W waves of a workgroup share a tile, wave w taking views
-// w, w + W, ..., and meet in LDS in a fixed order.
-struct TileRay {
+// A wave owns a tile of 8 x 8 pixels, of up to eight items of a batch, and takes
+// one view at a time.  The rays that can cross the tile (the bins of its
+// footprint, a few dozen) are set up once for all its pixels, a ray per lane and
+// up to four views at once, in double precision and exactly as the projector
+// sets them up, and put in LDS with the reciprocals of their steps and their
+// values; then every lane gathers over the two or three rays that cross its own
+// pixel's support, clipping each to it.  Setting the ray up in every pixel
+// instead is what the time went to: 3.19 ms for 512^2 and 360 fan views of 725
+// bins, against 0.59 ms (0.80 ms setting up one view at a time); 256^2 with 30
+// parallel views of 363 bins went from 46 to 16 us.  VALU-bound, and the weights
+// are the same for every item of a batch: another item costs one operation a
+// ray.  The W waves of a workgroup share a tile, wave w taking views w, w + W,
+// ..., and meet in LDS in a fixed order.
+template <int NB>
+struct __align__(16) TileRay {
     float X0, Y0, eX, eY;   // sample m sits at (X0 + m eX, Y0 + m eY)
-    float rX, rY, g;        // 1 / eX, 1 / eY (finite), the ray's value
-    float pad;
+    float rX, rY;           // 1 / eX, 1 / eY (finite)
+    float g[NB];            // the ray's value in each item
 };
 
 __device__ __forceinline__ float step_rcp(float e)
@@ -53,19 +57,20 @@ __device__ __forceinline__ float hat(float d)
     return r;
 }
 
-template <typename T, typename TI, bool FAN, int V>
+template <typename T, typename TI, bool FAN, int V, int NB>
 __global__ void __launch_bounds__(1024) fpT2d_kernel(Geom2D g, const float2 *__restrict__ views,
                                                      const TI *__restrict__ sino, T *__restrict__ img, int ntx,
-                                                     int nty)
+                                                     int nty, int batch)
 {
     constexpr int L = 64 / V;   // lanes (and rays) per view
-    extern __shared__ TileRay s_rays[];   // 64 per wave
+    extern __shared__ __align__(16) char at_lds[];   // 64 rays per wave
+    TileRay<NB> *s_rays = (TileRay<NB> *)at_lds;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int waves = blockDim.x >> 6;
-    TileRay *rays = s_rays + wave * 64;
+    TileRay<NB> *rays = s_rays + wave * 64;
     const unsigned tile = blockIdx.x;
     const int tx = (int)(tile % (unsigned)ntx), ty = (int)((tile / (unsigned)ntx) % (unsigned)nty);
-    const int b = (int)(tile / ((unsigned)ntx * (unsigned)nty));
+    const int b0 = NB * (int)(tile / ((unsigned)ntx * (unsigned)nty));
     const int ix = tx * 8 + (lane & 7), iy = ty * 8 + (lane >> 3);
     const float fx = (float)ix, fy = (float)iy;
     const float x = fmaf(fx, g.sx, g.ox), y = fmaf(fy, g.sy, g.oy);
@@ -73,8 +78,11 @@ __global__ void __launch_bounds__(1024) fpT2d_kernel(Geom2D g, const float2 *__r
     const float qx = fmaf((float)((lane & 1) ? min(tx * 8 + 8, g.nx) : tx * 8 - 1), g.sx, g.ox);
     const float qy = fmaf((float)((lane & 2) ? min(ty * 8 + 8, g.ny) : ty * 8 - 1), g.sy, g.oy);
     const float margin = fmaf(1e-6f, (float)g.nu, 0.02f);   // rounding of the coordinates (bins)
-    const TI *sb = sino + (size_t)b * g.n_proj * g.nu;
-    float acc = 0.0f;
+    const size_t item = (size_t)g.n_proj * g.nu;
+    float acc[NB];
+#pragma unroll
+    for (int n = 0; n < NB; ++n)
+        acc[n] = 0.0f;
     for (int k0 = wave * V; k0 < g.n_proj; k0 += waves * V) {
         // the tile's bins in this lane's view
         const int kv = min(k0 + lane / L, g.n_proj - 1);
@@ -90,11 +98,13 @@ __global__ void __launch_bounds__(1024) fpT2d_kernel(Geom2D g, const float2 *__r
         for (int c0 = 0; __any(j_lo + c0 <= j_hi); c0 += L) {
             const int jl = j_lo + c0 + lane % L;
             if (jl <= j_hi) {
-                TileRay r;
+                TileRay<NB> r;
                 make_ray_2d<FAN>(g, cl, jl, r.X0, r.Y0, r.eX, r.eY);
                 r.rX = step_rcp(r.eX);
                 r.rY = step_rcp(r.eY);
-                r.g = load_f32(sb + (size_t)kv * g.nu + jl);
+#pragma unroll
+                for (int n = 0; n < NB; ++n)
+                    r.g[n] = load_f32(sino + min(b0 + n, batch - 1) * item + (size_t)kv * g.nu + jl);
                 rays[lane] = r;
             }
             wave_lds_fence();
@@ -119,7 +129,7 @@ __global__ void __launch_bounds__(1024) fpT2d_kernel(Geom2D g, const float2 *__r
                 h = fmaf(h, g.ru, margin);
                 const int ja = (int)ceilf(fmaxf(fu + (t - h), (float)jv)), jb = (int)floorf(fminf(fu + (t + h), (float)je));
                 for (int j = ja; j <= jb; ++j) {
-                    const TileRay r = rays[v * L + j - jv];
+                    const TileRay<NB> r = rays[v * L + j - jv];
                     // the samples inside the support; the clip only picks the
                     // range to visit (hardware reciprocals, widened), the
                     // weights decide every sample
@@ -135,7 +145,9 @@ __global__ void __launch_bounds__(1024) fpT2d_kernel(Geom2D g, const float2 *__r
                         const float wy = hat(fmaf((float)m, r.eY, r.Y0) - fy);
                         w = fmaf(wx, wy, w);
                     }
-                    acc = fmaf(r.g, w, acc);
+#pragma unroll
+                    for (int n = 0; n < NB; ++n)
+                        acc[n] = fmaf(r.g[n], w, acc[n]);
                 }
             }
             wave_lds_fence();
@@ -143,16 +155,23 @@ __global__ void __launch_bounds__(1024) fpT2d_kernel(Geom2D g, const float2 *__r
     }
     if (waves > 1) {
         __syncthreads();
-        float *part = (float *)s_rays;
-        part[threadIdx.x] = acc;
+        float *part = (float *)at_lds;
+#pragma unroll
+        for (int n = 0; n < NB; ++n)
+            part[n * blockDim.x + threadIdx.x] = acc[n];
         __syncthreads();
         if (wave > 0)
             return;
         for (int w = 1; w < waves; ++w)
-            acc += part[w * 64 + lane];
+#pragma unroll
+            for (int n = 0; n < NB; ++n)
+                acc[n] += part[n * blockDim.x + w * 64 + lane];
     }
     if (ix < g.nx && iy < g.ny)
-        store_f32(img + ((size_t)b * g.ny + iy) * g.nx + ix, g.step * acc);
+#pragma unroll
+        for (int n = 0; n < NB; ++n)
+            if (b0 + n < batch)
+                store_f32(img + ((size_t)(b0 + n) * g.ny + iy) * g.nx + ix, g.step * acc[n]);
 }
 
 // --------------------------------------------------------------- A^T, 3D
@@ -816,11 +835,11 @@ __global__ void __launch_bounds__(1024) bpT2d_run_kernel(Geom2D g, const float2 
     }
 }
 
-template <typename T, typename TI, bool FAN, int V>
-hipError_t fpT2d_v(const Geom2D &g, const float2 *views, const void *sino, void *img, int batch, hipStream_t s)
+template <typename T, typename TI, bool FAN, int V, int NB>
+hipError_t fpT2d_n(const Geom2D &g, const float2 *views, const void *sino, void *img, int batch, hipStream_t s)
 {
     const int ntx = (g.nx + 7) / 8, nty = (g.ny + 7) / 8;
-    const long tiles = (long)ntx * nty * batch;
+    const long tiles = (long)ntx * nty * ((batch + NB - 1) / NB);
     if (tiles > 0x7fffffffL)
         return hipErrorInvalidConfiguration;
     // waves per tile: about 32 on every CU in all, at least V views each (a
@@ -830,9 +849,25 @@ hipError_t fpT2d_v(const Geom2D &g, const float2 *views, const void *sino, void 
     const long most = (g.n_proj + V - 1) / V;
     waves = waves < most ? waves : most;
     waves = waves < 16 ? waves : 16;
-    hipLaunchKernelGGL((fpT2d_kernel<T, TI, FAN, V>), dim3((unsigned)tiles), dim3((unsigned)(64 * waves)),
-                       (size_t)(64 * waves) * sizeof(TileRay), s, g, views, (const TI *)sino, (T *)img, ntx, nty);
+    hipLaunchKernelGGL((fpT2d_kernel<T, TI, FAN, V, NB>), dim3((unsigned)tiles), dim3((unsigned)(64 * waves)),
+                       (size_t)(64 * waves) * sizeof(TileRay<NB>), s, g, views, (const TI *)sino, (T *)img, ntx, nty,
+                       batch);
     return hipGetLastError();
+}
+
+template <typename T, typename TI, bool FAN, int V>
+hipError_t fpT2d_v(const Geom2D &g, const float2 *views, const void *sino, void *img, int batch, hipStream_t s)
+{
+    // up to eight items of a batch share the rays and weights (512^2, 360 fan
+    // views of 1020 bins, two and five items: 1526 and 3439 us one at a time, 828
+    // and 2201 by twos, 1581 five by fours, 1046 in one; 64^2, 90 parallel views of
+    // five: 18, 12, 13 and 14 us)
+    if (batch > 4)
+        return fpT2d_n<T, TI, FAN, V, 8>(g, views, sino, img, batch, s);
+    if (batch > 2)
+        return fpT2d_n<T, TI, FAN, V, 4>(g, views, sino, img, batch, s);
+    return batch == 2 ? fpT2d_n<T, TI, FAN, V, 2>(g, views, sino, img, batch, s)
+                      : fpT2d_n<T, TI, FAN, V, 1>(g, views, sino, img, batch, s);
 }
 
 template <typename T, typename TI, bool FAN>

@@ -133,3 +133,16 @@ def test_project_adjoint_2d_edges(ph, ora, name):
     say(f"[A^T 2D] {name}")
     check(to_np(out), np.stack([ora.project_adjoint(spec, v) for v in p]), name, tol=TOL_AT)
     assert (aT(g, rv, to_dev(p)) == out).all()
+
+
+@pytest.mark.parametrize("items", [1, 2, 4, 5, 8, 9])
+@pytest.mark.parametrize("name", ["par_63", "par_127_fine", "arc_190"])
+def test_project_adjoint_2d_item_groups(ph, ora, name, items):
+    """Groups of up to eight items with the last one part empty."""
+    import numpy as np
+    spec, g, rv, fan = _setup(ph, name)
+    p = as_f32(np.random.default_rng(13).standard_normal((items, spec.n_proj) + spec.det_shape))
+    aT = ph.project_adjoint_fan2d if fan else ph.project_adjoint_par2d
+    out = aT(g, rv, to_dev(p))
+    say(f"[A^T 2D, {items} items] {name}")
+    check(to_np(out), np.stack([ora.project_adjoint(spec, v) for v in p]), name, tol=TOL_AT)
