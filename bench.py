@@ -44,16 +44,16 @@ OPS_PER_SAMPLE = 26.0      # forward projection: 3 coordinates, 3 floor/fract, 7
 COPY_BYTES = 1 << 30
 COPY_FETCH_KIB, COPY_WRITE_KIB = 524315.0, 1048576.0
 MEASURED_TRAFFIC = {
-    "fp_cone": {"fetch_kib": 6.47788e+07, "write_kib": 1.24095e+06,
-             "sources": ('cone_fp.hip', 'device_util.h'), "sha256_16": "3689f3d998d3b903"},
-    "bp_cone": {"fetch_kib": 8.80846e+06, "write_kib": 524288,
-             "sources": ('cone_bp.hip', 'device_util.h'), "sha256_16": "e1f54f92b2136414"},
-    "weight_filter": {"fetch_kib": 563800, "write_kib": 1.10592e+06,
+    "fp_cone": {"fetch_kib": 6.03206e+07, "write_kib": 1.23984e+06,
+             "sources": ('cone_fp.hip', 'device_util.h'), "sha256_16": "808e4cbb11aadcc2"},
+    "bp_cone": {"fetch_kib": 9.02833e+06, "write_kib": 524288,
+             "sources": ('cone_bp.hip', 'device_util.h'), "sha256_16": "3e9a44094c708c39"},
+    "weight_filter": {"fetch_kib": 563476, "write_kib": 1.10592e+06,
                    "sources": ('filter.hip', 'fft.h'), "sha256_16": "89a6c98d7d5f61cc"},
-    "fpT_cone": {"fetch_kib": 8.37076e+06, "write_kib": 524288,
-              "sources": ('adjoint.hip', 'device_util.h'), "sha256_16": "d6d2b86b350f2a7c"},
-    "bpT_cone": {"fetch_kib": 2.75112e+06, "write_kib": 2.27029e+07,
-              "sources": ('cone_bp.hip', 'device_util.h'), "sha256_16": "e1f54f92b2136414"},
+    "fpT_cone": {"fetch_kib": 1.02448e+07, "write_kib": 524288,
+              "sources": ('adjoint.hip', 'device_util.h'), "sha256_16": "682c708c236ba2ff"},
+    "bpT_cone": {"fetch_kib": 2.74625e+06, "write_kib": 2.27029e+07,
+              "sources": ('cone_bp.hip', 'device_util.h'), "sha256_16": "3e9a44094c708c39"},
 }
 
 

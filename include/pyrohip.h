@@ -157,13 +157,15 @@ int ph_backproject_cone3d(const ph_geom3d *g, const float *mats, const void *pro
  *
  * ph_project_adjoint_*: A^T, volume_x = step * sum_r g_r sum_k Lambda(X_rk - x)
  * over the same sample positions X_rk as ph_project_* (Lambda the bi/trilinear
- * hat function).  Gather, no atomics; any storage dtype.
+ * hat function).  No global atomics, and sums in an order fixed by the sizes
+ * (2D) or exact in integers (3D): the same bits on every run; any storage dtype.
  *   sino/proj : device input, same layout as the projector's output
  *   img/vol   : device output, same layout as the projector's input
  * ph_backproject_adjoint_*: B^T, projection_(k,i,j) = dbeta * sum_x f(x)
  * w_k(x) Lambda(j - su_k(x)) Lambda(i - sv_k(x)) with w_k = 1 (parallel) or
- * (SID/w)^2.  Scatter with float atomics: FP32 storage here (other dtypes ->
- * PH_ERR_UNSUPPORTED; the _ws variants below take them); summation order,
+ * (SID/w)^2.  FP32 storage here (other dtypes -> PH_ERR_UNSUPPORTED; the _ws
+ * variants below take them).  2D gathers per bin, the same bits on every run;
+ * 3D adds its bricks' footprints with float atomics, so its summation order,
  * hence the last bits, may vary from run to run.
  *   img/vol   : device FP32 input; sino/proj : device FP32 output */
 int ph_project_adjoint_par2d(const ph_geom2d *g, const float *ray_vecs, const void *sino, void *img, int batch,
@@ -189,7 +191,7 @@ size_t ph_project_adjoint_workspace_bytes_3d(const ph_geom3d *g, int batch);
 int ph_project_adjoint_ws_cone3d(const ph_geom3d *g, const float *mats, const void *proj, void *vol, void *ws,
                                  size_t ws_bytes, int batch, ph_dtype dtype, void *stream);
 
-/* B^T with any storage type (extension 1): the scatter accumulates in FP32,
+/* B^T with any storage type (extension 1): the sums are FP32,
  * in the output itself for FP32 and otherwise in the workspace `ws` of
  * ph_backproject_adjoint_workspace_bytes_*() bytes (0 for FP32, where ws may
  * be NULL), which is then rounded to the storage type (nearest even). */

@@ -171,10 +171,12 @@ int make_geom2d(const ph_geom2d *g, bool fan, Geom2D *o)
     o->n_proj = g->n_proj;
     o->sid = fan ? g->sid : 0.0f;
     o->sdd = fan ? g->sdd : 0.0f;
-    const double ru = (fan ? (double)g->sdd : 1.0) / (double)g->det_spacing;
-    o->ru = (float)ru;
-    o->ru_lo = (float)(ru - (double)o->ru);
+    o->rdu = 1.0f / g->det_spacing;
+    o->ru = fan ? g->sdd / g->det_spacing : o->rdu;
     o->curved = fan && g->fan_detector == 1 ? 1 : 0;
+    o->ru_lo = o->curved && g->det_shape <= 256 ? (float)((double)g->sdd / g->det_spacing - o->ru) : 0.0f;
+    if (o->curved && g->det_shape <= 256 && o->ru_lo == 0.0f)
+        o->ru_lo = 1e-30f;   // an exact scale: the fraction alone
     o->step = (float)default_step(g->step_mm, std::fmin(g->vol_spacing[0], g->vol_spacing[1]));
     o->step_sx = (double)o->step / g->vol_spacing[1];
     o->step_sy = (double)o->step / g->vol_spacing[0];
@@ -847,8 +849,8 @@ int fbp2d(const ph_geom2d *g, bool fan, const float *rv, const void *sino, void 
     return to_status(launch_backproject_2d(dtype, fan, t.G, t.views, q, true, img, batch, (hipStream_t)stream));
 }
 
-// B^T accumulates with float atomics: FP32 output directly, half-precision
-// output through an FP32 workspace that is then rounded to the storage type.
+// B^T sums in FP32: FP32 output directly, half-precision output through an FP32
+// workspace that is then rounded to the storage type.
 int adjoint2d(const ph_geom2d *g, bool fan, bool of_projector, const float *rv, const void *in, void *out,
               int batch, int dtype, void *stream, void *ws = nullptr, size_t ws_bytes = 0, bool ws_call = false)
 {

@@ -617,7 +617,7 @@ __device__ __forceinline__ void strip_walk(const Geom2D &g, float2 c, const TI *
                 const int q = in ? q0[r] + n : 0, p = in ? pb + r * stride : 0;
                 const int ix = AX == 0 ? q : p, iy = AX == 0 ? p : q;
                 float fu, t, wt;
-                point2d<FAN>(g, c, fmaf((float)ix, g.sx, g.ox), fmaf((float)iy, g.sy, g.oy), fu, t, wt);
+                point2d<FAN, FORM_ATAN2>(g, c, fmaf((float)ix, g.sx, g.ox), fmaf((float)iy, g.sy, g.oy), fu, t, wt);
                 const float v = g.dbeta * wt * (in && fu == jf ? val[r] : 0.0f);
                 a0 = fmaf(v, 1.0f - t, a0);
                 a1 = fmaf(v, t, a1);
@@ -714,7 +714,7 @@ __device__ __forceinline__ int prev_lane(int x, int end)
 // Runs along y read a column, 64 cache lines for a wave; RUN_COLS neighbouring
 // ones are read by wide loads, so that each line is touched twice and not once
 // a run.  8 x 256^2, 360 parallel views: 252 us with four loads of a pixel
-// each, 211 with one of four, 200 with two for eight runs and 155 with two items
+// each, 211 with one of four, 200 with two for eight runs and 150 with two items
 // together, then bound by about 35 vector operations for each run and item.
 constexpr int RUN_COLS = 8;          // runs whose pixels are loaded together
 constexpr size_t RUN_LDS = 65536;    // LDS of a workgroup, at most
@@ -770,7 +770,7 @@ __global__ void __launch_bounds__(1024) bpT2d_run_kernel(Geom2D g, const float2 
                 break;
             const float x = fmaf((float)(along_x ? qc : p), g.sx, g.ox), y = fmaf((float)(along_x ? p : qc), g.sy, g.oy);
             float fu, t, wt;
-            point2d<FAN>(g, c, x, y, fu, t, wt);
+            point2d<FAN, FORM_ATAN2>(g, c, x, y, fu, t, wt);
             Pairs w;
 #pragma unroll
             for (int i = 0; i < NB; ++i) {
@@ -1021,7 +1021,8 @@ hipError_t bpT2d(bool fan, const Geom2D &g, const float2 *views, const void *img
     // (strips and runs, us: 256^2, 60, 120 and 180 parallel views 29 and 28, 30
     // and 29, 46 and 28, fan views 25 and 34, 39 and 34, 50 and 34; 512^2, 180,
     // 256 and 360 parallel views 131 and 153, 139 and 154, 245 and 196, arc views
-    // 219 and 246, 261 and 246, 385 and 294; 128^2 and 64^2: runs no slower at
+    // 219 and 246, 261 and 246, 385 and 294, with atan2f now 278 by strips, 274
+    // and 337 by runs; 128^2 and 64^2: runs no slower at
     // any number) and the pixels of a run move by at least a quarter of a bin:
     // the faster axis moves by 1 / sqrt(2) of a spacing on the detector, seen
     // from the far side of the image.

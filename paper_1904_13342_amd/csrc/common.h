@@ -43,7 +43,8 @@ struct Geom2D {
     double step_sx, step_sy;  // ray sampling step / spacing
     float sx, sy;
     float du, cu;          // detector spacing, (nu-1)/2
-    float ru, ru_lo;       // bins per mm (parallel: 1/du) or per unit of slope or fan angle (sdd/du), in two floats
+    float ru, rdu;         // bins per mm (parallel) or per unit of slope or fan angle (sdd/du), and 1/du
+    float ru_lo;           // arcs of up to 256 bins: what ru leaves of sdd/du, else 0
     float sid, sdd;
     float step;            // ray sampling step (mm)
     float dbeta;           // range / n_proj
@@ -117,8 +118,8 @@ hipError_t launch_backproject_cone(int dtype, const Geom3D &g, const ConeBPView 
 // use per device); PH_ERR_HIP-style failure returns a HIP error.
 hipError_t static_scratch(void **ptr, size_t *bytes);
 
-// Exact transposes.  A^T: any storage type (gather, written once).  B^T:
-// FP32 in and out (scatter with float atomics into a zero-filled output).
+// Exact transposes.  A^T: any storage type, every element written once.  B^T:
+// FP32 out; 2D gathers, 3D adds with float atomics into an output it clears.
 hipError_t launch_project_adjoint_2d(int dtype, bool fan, const Geom2D &g, const float2 *views, const void *sino,
                                      void *img, int batch, hipStream_t stream);
 // scratch: project_adjoint_scratch() bytes for the partial sums of a small

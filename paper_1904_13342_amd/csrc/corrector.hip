@@ -192,9 +192,11 @@ hipError_t launch_mse(const float *x, const float *ref, const float *mask, size_
             return e;
     }
     // the workgroups' FP64 atomics on the one loss take their turns at about 13
-    // ns each: with a loss, no more workgroups than hide the loads (524288
-    // elements: 27 us with 2048 of them)
-    const size_t blocks = (n + 255) / 256, most = loss ? 512 : 4096;
+    // ns each: with a loss, few workgroups where they would outlast the loads
+    // (512, 1024, 2048 and 4096: 524288 elements 10, 16, 28 and 28 us; 2^25 159,
+    // 103, 89 and 99; 2^28 1242, 772, 603 and 685)
+    const size_t blocks = (n + 255) / 256, fair = n / 8192;
+    const size_t most = !loss ? 4096 : fair < 512 ? 512 : fair < 2048 ? fair : 2048;
     hipLaunchKernelGGL(mse_kernel, dim3((unsigned)(blocks < most ? blocks : most)), dim3(256), 0, s, x, ref, mask, n,
                        1.0f / (float)n, grad, loss);
     return hipGetLastError();

@@ -154,30 +154,47 @@ __device__ __forceinline__ float atan_small(float z)
 // orthogonal projection, weight 1.  Fan beams: central projection onto the
 // flat detector with weight (SID / w)^2, w the depth along the central ray; on
 // the equiangular detector the bin of the point's fan angle, with weight
-// (SID / L)^2, L the distance from the source.  All in FP32.  Two roundings
-// that a detector of a thousand bins would feel are kept out: the scale to
-// bins (ru) is held in two floats, and the fraction is formed from the
-// centred coordinate by one FMA, not by subtracting the bin from a rounded
-// sum (so it may leave [0, 1) by an ulp of the coordinate).  The fan angle is
+// (SID / L)^2, L the distance from the source.  All in FP32.  The fan angle is
 // atan_small of the slope, taken from the pi / 4 or pi / 2 direction beyond
-// tan(pi / 8) and tan(3 pi / 8).  The back-projector and its transpose both
-// use this, so they see the same coordinates.
-template <bool FAN, int FORM = 0>
+// tan(pi / 8) and tan(3 pi / 8); where no lane of the wave is beyond, that is
+// left out (the same value: every step is odd in xu).  On arcs of few bins
+// (ru_lo) the scale to bins is held in two floats and the fraction is formed
+// from the centred coordinate, since there the rounding of their sum would be
+// the largest error; on longer ones that of x and y on the ray's normal is as
+// large, and the three operations are saved.  FORM: FORM_ANY, or
+// what the caller knows of the detector, so that the code has no branch for it:
+// flat, or an arc, of few bins or not, whose slopes are below tan(pi / 8) or any.  FORM_ATAN2
+// takes the angle on longer arcs from atan2f: B^T of rough data moves with the last
+// bits of a coordinate (2e-5 of itself at 1000 bins), and these are the ones its
+// results have had.  Otherwise the back-projector and its transpose see the same
+// coordinates.
+constexpr int FORM_ANY = 0, FORM_FLAT = 1, FORM_FINE_ARC = 2, FORM_ARC = 4, FORM_SMALL = 8, FORM_ATAN2 = 16;
+
+template <bool FAN, int FORM = FORM_ANY>
 __device__ __forceinline__ void point2d(const Geom2D &g, float2 c, float x, float y, float &fu, float &t, float &wt)
 {
     const float xu = fmaf(y, c.x, -(x * c.y));
-    float q = xu, off = 0.0f;   // offset, slope or fan angle: q + off
+    float s;   // detector coordinate in bins
     wt = 1.0f;
-    if (FAN) {
+    if (!FAN) {
+        s = fmaf(xu, g.ru, g.cu);
+    } else {
         const float w = fmaf(x, c.x, fmaf(y, c.y, g.sid));
-        if (FORM == 1 || (FORM == 0 && !g.curved)) {
-            const float rw = rcp_nr(w), q0 = xu * rw, sw = g.sid * rw;
-            q = fmaf(fmaf(-q0, w, xu), rw, q0);   // xu / w
+        if (FORM == FORM_FLAT || ((FORM == FORM_ANY || FORM == FORM_ATAN2) && !g.curved)) {
+            const float rw = rcp_nr(w), sw = g.sid * rw;
+            s = fmaf(g.sdd * xu * rw, g.rdu, g.cu);
             wt = sw * sw;
         } else {
             wt = g.sid * g.sid * rcp_nr(fmaf(w, w, xu * xu));
+            if (FORM == FORM_ATAN2 && g.ru_lo == 0.0f) {   // uniform
+                s = fmaf(atan2f(xu, w), g.ru, g.cu);
+                fu = floorf(s);
+                t = s - fu;
+                return;
+            }
             const float a = fabsf(xu);
-            if (FORM == 0 && __any(a > 0.41421357f * w)) {
+            float q, off = 0.0f;   // fan angle: q + off
+            if (!(FORM & FORM_SMALL) && __any(a > 0.41421357f * w)) {
                 float num = a, den = w;
                 if (a > 0.41421357f * w) {
                     const bool steep = a > 2.4142135f * w;
@@ -186,16 +203,20 @@ __device__ __forceinline__ void point2d(const Geom2D &g, float2 c, float x, floa
                     off = copysignf(steep ? 1.57079633f : 0.78539816f, xu);
                 }
                 q = copysignf(1.0f, xu) * atan_small(div_nr(num, den));
-            } else {   // the same value: every step is odd in xu
+            } else {
                 q = atan_small(div_nr(xu, w));
             }
+            if ((FORM & FORM_FINE_ARC) || ((FORM == FORM_ANY || FORM == FORM_ATAN2) && g.ru_lo != 0.0f)) {   // uniform
+                const float lo = (q + off) * g.ru_lo;
+                fu = floorf(fmaf(q, g.ru, fmaf(off, g.ru, g.cu) + lo));
+                t = fmaf(q, g.ru, fmaf(off, g.ru, g.cu - fu)) + lo;
+                return;
+            }
+            s = fmaf(q + off, g.ru, g.cu);
         }
     }
-    const float lo = FAN ? (q + off) * g.ru_lo : q * g.ru_lo;
-    const float base = FAN ? fmaf(off, g.ru, g.cu) : g.cu;
-    fu = floorf(fmaf(q, g.ru, base + lo));
-    const float back = FAN ? fmaf(off, g.ru, g.cu - fu) : g.cu - fu;
-    t = fmaf(q, g.ru, back) + lo;
+    fu = floorf(s);
+    t = s - fu;
 }
 
 // Narrow [lo, hi] to the parameters t with p + t e inside the open interval

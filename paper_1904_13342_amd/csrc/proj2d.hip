@@ -34,6 +34,11 @@ __device__ __forceinline__ float sample_direct(const T *im, const Geom2D &g, flo
 constexpr int A_UNROLL = 2;   // samples per lane of A whose loads are in flight together
 constexpr int B_UNROLL = 4;   // views per wave of B
 
+template <int F>
+struct Form {   // a form of point2d as an argument
+    static constexpr int value = F;
+};
+
 // Narrow [lo, hi] to the sample range inside the open interval (a, b) of
 // index coordinates.
 __device__ __forceinline__ bool krange(float p, float e, float a, float b, float &lo, float &hi)
@@ -311,14 +316,14 @@ __device__ __forceinline__ float slab_walk_2d(const Geom2D &g, const T *im, floa
                 const float a0 = fmaf(tx, p01 - p00, p00), a1 = fmaf(tx, p11 - p10, p10);
                 return fmaf(ty, a1 - a0, a0);
             };
+            // the slab's samples are summed first, so that no long sum is rounded at every sample
             const float fend = (float)m_end;
-            float fm = (float)m;
-            for (; fm + 1.0f < fend; fm += 2.0f) {
-                acc += sample(fm);
-                acc += sample(fm + 1.0f);
-            }
+            float fm = (float)m, sum = 0.0f;
+            for (; fm + 1.0f < fend; fm += 2.0f)
+                sum += sample(fm) + sample(fm + 1.0f);
             if (fm < fend)
-                acc += sample(fm);
+                sum += sample(fm);
+            acc += sum;
         } else {
             for (int q = m; q < m_end; ++q)
                 acc += sample_direct(im, g, fmaf((float)q, eX, X0), fmaf((float)q, eY, Y0));
@@ -391,7 +396,7 @@ __global__ void __launch_bounds__(1024) fp2d_slab_kernel(Geom2D g, const float2 
 // pair is one load, otherwise two masked ones.  (With the lanes of a wave on 4
 // views of 16 pixels: 174 against 112 us for 8 x 256^2 and 360 parallel views.)
 // Taken for single items of fan views, bound by some 38 vector operations for
-// each sample's coordinate (512^2, 360 arc views: 89 us, 1.1 a clock on every
+// each sample's coordinate (512^2, 360 arc views: 81 us, 1.1 a clock on every
 // CU), and for bins too fine to stage, below.
 template <typename T, typename TI, bool FAN>
 __global__ void __launch_bounds__(1024) bp2d_kernel(Geom2D g, const float2 *__restrict__ views,
@@ -410,12 +415,20 @@ __global__ void __launch_bounds__(1024) bp2d_kernel(Geom2D g, const float2 *__re
     for (int k0 = wave; k0 < g.n_proj; k0 += B_UNROLL * waves) {
         float fu[B_UNROLL], t[B_UNROLL], wt[B_UNROLL];
         bool inside = true;
+        auto points = [&](auto form) {
 #pragma unroll
-        for (int u = 0; u < B_UNROLL; ++u) {
-            const int k = min(k0 + u * waves, g.n_proj - 1);
-            point2d<FAN>(g, views[k], x, y, fu[u], t[u], wt[u]);
-            inside = inside && fu[u] >= 0.0f && fu[u] < (float)(g.nu - 1);
-        }
+            for (int u = 0; u < B_UNROLL; ++u) {
+                const int k = min(k0 + u * waves, g.n_proj - 1);
+                point2d<FAN, decltype(form)::value>(g, views[k], x, y, fu[u], t[u], wt[u]);
+                inside = inside && fu[u] >= 0.0f && fu[u] < (float)(g.nu - 1);
+            }
+        };
+        if (!FAN || !g.curved)
+            points(Form<FORM_FLAT>());
+        else if (g.ru_lo != 0.0f)
+            points(Form<FORM_FINE_ARC>());
+        else
+            points(Form<FORM_ARC>());
         if (__all(inside) && k0 + (B_UNROLL - 1) * waves < g.n_proj) {
             float2 p[B_UNROLL];
 #pragma unroll
@@ -551,19 +564,19 @@ __global__ void __launch_bounds__(1024) bp2d_seg_kernel(Geom2D g, const float2 *
         for (int v = 0; v < nv; ++v) {
             const float2 c = make_float2(lane_value(cl.x, 4 * v), lane_value(cl.y, 4 * v));
             float fu[4], t[4], wt[4];
-            if (FAN && !g.curved) {
+            auto points = [&](auto form) {
 #pragma unroll
                 for (int a = 0; a < 4; ++a)
-                    point2d<FAN, 1>(g, c, px[a & 1], py[a >> 1], fu[a], t[a], wt[a]);
-            } else if (FAN && ((small >> (4 * v)) & 1)) {
-#pragma unroll
-                for (int a = 0; a < 4; ++a)
-                    point2d<FAN, 2>(g, c, px[a & 1], py[a >> 1], fu[a], t[a], wt[a]);
-            } else {
-#pragma unroll
-                for (int a = 0; a < 4; ++a)
-                    point2d<FAN>(g, c, px[a & 1], py[a >> 1], fu[a], t[a], wt[a]);
-            }
+                    point2d<FAN, decltype(form)::value>(g, c, px[a & 1], py[a >> 1], fu[a], t[a], wt[a]);
+            };
+            if (!FAN || !g.curved)
+                points(Form<FORM_FLAT>());
+            else if (!((small >> (4 * v)) & 1))
+                points(Form<FORM_ANY>());
+            else if (g.ru_lo != 0.0f)
+                points(Form<FORM_FINE_ARC | FORM_SMALL>());
+            else
+                points(Form<FORM_ARC | FORM_SMALL>());
             if ((ok >> (4 * v)) & 1) {
                 const int first = v * W - __builtin_amdgcn_readlane(lo, 4 * v);
 #pragma unroll
@@ -730,7 +743,8 @@ hipError_t bp2d_f(const Geom2D &g, const float2 *views, const void *sino, void *
     // filter: 74 and 60 us), fan views, bound by the arithmetic of their
     // coordinates, only where two items or more share it (512^2, 360 arc views
     // of one, two and five items: 103, 189 and 418 us from memory, 118, 123
-    // and 247 staged).
+    // and 247 staged; since the coordinate's forms are told apart 96 for one
+    // and 114 for two).
     const float wx = g.nx * g.sx, wy = g.ny * g.sy, near = g.sid - 0.5f * sqrtf(wx * wx + wy * wy);
     const float diag = 15.0f * sqrtf(g.sx * g.sx + g.sy * g.sy);
     const float span = !FAN ? diag * g.ru : near > 0.0f ? diag * g.ru / near : 3.0e38f;
