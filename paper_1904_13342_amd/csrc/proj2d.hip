@@ -4,6 +4,7 @@
 // 1 MiB) stay resident in L2; what neighbouring rays or pixels share, A in slabs
 // and B in segments stage once more in LDS.
 #include "device_util.h"
+#include "ranges.h"
 
 namespace ph {
 namespace {
@@ -39,18 +40,6 @@ struct Form {   // a form of point2d as an argument
     static constexpr int value = F;
 };
 
-// Narrow [lo, hi] to the sample range inside the open interval (a, b) of
-// index coordinates.
-__device__ __forceinline__ bool krange(float p, float e, float a, float b, float &lo, float &hi)
-{
-    if (fabsf(e) < 1e-30f)
-        return p > a && p < b;
-    const float r = 1.0f / e, t1 = (a - p) * r, t2 = (b - p) * r;
-    lo = fmaxf(lo, fminf(t1, t2));
-    hi = fminf(hi, fmaxf(t1, t2));
-    return true;
-}
-
 // S lanes share one ray (S a power of two, at most 64: the lanes of a ray lie
 // in one wave); lane s takes samples k0 + s, k0 + s + S, ... and the partial
 // sums meet in a fixed shuffle tree.  Small problems (few rays, long rays)
@@ -85,16 +74,8 @@ __global__ void __launch_bounds__(256) fp2d_kernel(Geom2D g, const float2 *__res
     float acc = 0.0f;
     if (krange(X0, eX, -1.0f, (float)g.nx, lo, hi) && krange(Y0, eY, -1.0f, (float)g.ny, lo, hi) && lo < hi) {
         const int k0 = (int)floorf(lo) - 1, k1 = (int)ceilf(hi) + 1;
-        // samples in_lo .. in_hi have their cells inside the image; the margin
-        // covers the rounding of the clip and of the coordinates (relative 2^-22
-        // of the anchor and of the image size), and 32-bit byte offsets must
-        // reach the whole image
-        const float ex = fmaf(1e-6f, (float)g.nx + fabsf(X0), 0.02f), ey = fmaf(1e-6f, (float)g.ny + fabsf(Y0), 0.02f);
-        float ilo = -1.0e9f, ihi = 1.0e9f;
-        const bool cells = krange(X0, eX, ex, (float)(g.nx - 1) - ex, ilo, ihi) &&
-                           krange(Y0, eY, ey, (float)(g.ny - 1) - ey, ilo, ihi) &&
-                           (size_t)g.nx * g.ny * sizeof(T) <= 0xffffffffu && g.nx < (1 << 24) && g.ny < (1 << 24);
-        const int in_lo = cells ? (int)ceilf(ilo) : 1, in_hi = cells ? (int)floorf(ihi) : 0;
+        int in_lo, in_hi;   // samples whose cells lie inside the image
+        cell_range(X0, Y0, eX, eY, g.nx, g.ny, sizeof(T), in_lo, in_hi);
         for (int m = k0 + s; m <= k1; m += A_UNROLL * S) {
             if (__all(m >= in_lo && m + (A_UNROLL - 1) * S <= in_hi)) {
                 float2 p[A_UNROLL], q[A_UNROLL];

@@ -1,0 +1,8 @@
+// The kernels' host-and-device range arithmetic behind a C interface, for
+// test_ranges.py: compiled for the host alone.
+#include "../paper_1904_13342_amd/csrc/ranges.h"
+
+extern "C" void cell_range_of(float X0, float Y0, float eX, float eY, int nx, int ny, int elem, int *first, int *last)
+{
+    ph::cell_range(X0, Y0, eX, eY, nx, ny, (size_t)elem, *first, *last);
+}

@@ -113,3 +113,22 @@ def test_backproject_2d_segments(ph, ora, name):
     out = to_np(B(g, ph.ray_vectors_2d(g), to_dev(p)))
     for n in {0, items // 2, items - 1}:
         check(out[n], ora.backproject(spec, p[n]), f"item {n}", tol=2e-5)
+
+
+@pytest.mark.parametrize("shape", [(1, 1), (1, 70), (70, 1), (2, 70), (70, 2), (3, 70)])
+@pytest.mark.parametrize("kind,du", [("par2d", 1.0), ("par2d", 2.0), ("fan2d", 2.0), ("fan2d_curved", 3.0)])
+def test_project_2d_thin_images(ph, ora, kind, du, shape):
+    """Images of one to three rows or columns, rays along them through their
+    centres (odd bins, views a quarter turn apart): no 2 x 2 cell lies inside
+    the thinnest, and the two items differ, so a read past one would show."""
+    spec = synth.config("par2d_64").with_(kind=kind, vol_shape=shape, vol_spacing=(1.0, 1.0), det_shape=(81,),
+                                          det_spacing=(du,), n_proj=8, angular_range=2 * math.pi,
+                                          **({} if kind == "par2d" else FAN))
+    g = ph.from_spec(spec)
+    rv = ph.ray_vectors_2d(g)
+    f = as_f32(np.random.default_rng(2).uniform(0.5, 1.5, (2,) + shape) * np.array([1.0, 100.0])[:, None, None])
+    A = ph.project_par2d if kind == "par2d" else ph.project_fan2d
+    say(f"[A 2D] {kind} {shape} bins of {du}")
+    out = to_np(A(g, rv, to_dev(f)))
+    for n in range(2):
+        check(out[n], ora.project(spec, f[n]), f"item {n}", tol=2e-5)
