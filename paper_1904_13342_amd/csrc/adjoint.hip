@@ -90,7 +90,7 @@ __global__ void __launch_bounds__(1024) fpT2d_kernel(Geom2D g, const float2 *__r
         int j_lo, j_hi;
         {
             float fu, t, wt;
-            point2d<FAN>(g, cl, qx, qy, fu, t, wt);
+            point2d<FAN, FORM_RANGE>(g, cl, qx, qy, fu, t, wt);
             const int jc = (int)fu;
             j_lo = max(imin4(jc), 0);
             j_hi = min(imax4(jc) + 1, g.nu - 1);
@@ -118,7 +118,7 @@ __global__ void __launch_bounds__(1024) fpT2d_kernel(Geom2D g, const float2 *__r
                 // projection of the box |dx| < sx, |dy| < sy; the fan angle
                 // moves no faster than the slope)
                 float fu, t, wt;
-                point2d<FAN>(g, c, x, y, fu, t, wt);
+                point2d<FAN, FORM_RANGE>(g, c, x, y, fu, t, wt);
                 const float ac = fabsf(c.x), as = fabsf(c.y);
                 float h = fmaf(as, g.sx, ac * g.sy);
                 if (FAN) {
@@ -617,7 +617,7 @@ __device__ __forceinline__ void strip_walk(const Geom2D &g, float2 c, const TI *
                 const int q = in ? q0[r] + n : 0, p = in ? pb + r * stride : 0;
                 const int ix = AX == 0 ? q : p, iy = AX == 0 ? p : q;
                 float fu, t, wt;
-                point2d<FAN, FORM_ATAN2>(g, c, fmaf((float)ix, g.sx, g.ox), fmaf((float)iy, g.sy, g.oy), fu, t, wt);
+                point2d<FAN>(g, c, fmaf((float)ix, g.sx, g.ox), fmaf((float)iy, g.sy, g.oy), fu, t, wt);
                 const float v = g.dbeta * wt * (in && fu == jf ? val[r] : 0.0f);
                 a0 = fmaf(v, 1.0f - t, a0);
                 a1 = fmaf(v, t, a1);
@@ -770,7 +770,7 @@ __global__ void __launch_bounds__(1024) bpT2d_run_kernel(Geom2D g, const float2 
                 break;
             const float x = fmaf((float)(along_x ? qc : p), g.sx, g.ox), y = fmaf((float)(along_x ? p : qc), g.sy, g.oy);
             float fu, t, wt;
-            point2d<FAN, FORM_ATAN2>(g, c, x, y, fu, t, wt);
+            point2d<FAN>(g, c, x, y, fu, t, wt);
             Pairs w;
 #pragma unroll
             for (int i = 0; i < NB; ++i) {

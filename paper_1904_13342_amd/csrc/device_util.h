@@ -154,25 +154,29 @@ __device__ __forceinline__ float atan_small(float z)
 // orthogonal projection, weight 1.  Fan beams: central projection onto the
 // flat detector with weight (SID / w)^2, w the depth along the central ray; on
 // the equiangular detector the bin of the point's fan angle, with weight
-// (SID / L)^2, L the distance from the source.  All in FP32.  The fan angle is
-// atan_small of the slope, taken from the pi / 4 or pi / 2 direction beyond
-// tan(pi / 8) and tan(3 pi / 8); where no lane of the wave is beyond, that is
-// left out (the same value: every step is odd in xu).  On arcs of few bins
-// (ru_lo) the scale to bins is held in two floats and the fraction is formed
-// from the centred coordinate, since there the rounding of their sum would be
-// the largest error; on longer ones that of x and y on the ray's normal is as
-// large, and the three operations are saved.  FORM: FORM_ANY, or
-// what the caller knows of the detector, so that the code has no branch for it:
-// flat, or an arc, of few bins or not, whose slopes are below tan(pi / 8) or any.  FORM_ATAN2
-// takes the angle on longer arcs from atan2f: B^T of rough data moves with the last
-// bits of a coordinate (2e-5 of itself at 1000 bins), and these are the ones its
-// results have had.  Otherwise the back-projector and its transpose see the same
-// coordinates.
-constexpr int FORM_ANY = 0, FORM_FLAT = 1, FORM_FINE_ARC = 2, FORM_ARC = 4, FORM_SMALL = 8, FORM_ATAN2 = 16;
+// (SID / L)^2, L the distance from the source.  All in FP32.
+//
+// B and B^T take every coordinate from here and so see the same ones to the
+// last bit, on every detector; FORM_ANY and the forms that a caller may name,
+// so that its code has no branch on the detector, give the same values.  Arcs
+// of few bins (ru_lo): the fan angle is atan_small of the slope, taken from the
+// pi / 4 or pi / 2 direction beyond tan(pi / 8) and tan(3 pi / 8) (where no lane
+// of the wave is beyond, or FORM_SMALL says so, that is left out: the same
+// value, every step is odd in xu); the scale to bins is held in two floats and
+// the fraction is formed from the centred coordinate, since there the rounding
+// of their sum would be the largest error.  On longer arcs that rounding is
+// left, 2^-15 bin at 512 to 1023 bins, whatever the angle's own error: the
+// results for rough data move with it, and the angle stays atan2f's.
+//
+// FORM_RANGE: for ranges of bins with a margin (1e-4 bin on top of it), the
+// polynomial on every arc.
+constexpr int FORM_ANY = 0, FORM_FLAT = 1, FORM_FINE_ARC = 2, FORM_ARC = 4, FORM_SMALL = 8, FORM_RANGE = 16;
 
 template <bool FAN, int FORM = FORM_ANY>
 __device__ __forceinline__ void point2d(const Geom2D &g, float2 c, float x, float y, float &fu, float &t, float &wt)
 {
+#pragma clang fp contract(off)   // the fused operations are those written out, in every caller
+    constexpr bool told = FORM != FORM_ANY && FORM != FORM_RANGE;   // which detector it is
     const float xu = fmaf(y, c.x, -(x * c.y));
     float s;   // detector coordinate in bins
     wt = 1.0f;
@@ -180,39 +184,41 @@ __device__ __forceinline__ void point2d(const Geom2D &g, float2 c, float x, floa
         s = fmaf(xu, g.ru, g.cu);
     } else {
         const float w = fmaf(x, c.x, fmaf(y, c.y, g.sid));
-        if (FORM == FORM_FLAT || ((FORM == FORM_ANY || FORM == FORM_ATAN2) && !g.curved)) {
+        if (FORM == FORM_FLAT || (!told && !g.curved)) {
             const float rw = rcp_nr(w), sw = g.sid * rw;
             s = fmaf(g.sdd * xu * rw, g.rdu, g.cu);
             wt = sw * sw;
         } else {
             wt = g.sid * g.sid * rcp_nr(fmaf(w, w, xu * xu));
-            if (FORM == FORM_ATAN2 && g.ru_lo == 0.0f) {   // uniform
-                s = fmaf(atan2f(xu, w), g.ru, g.cu);
-                fu = floorf(s);
-                t = s - fu;
-                return;
-            }
-            const float a = fabsf(xu);
-            float q, off = 0.0f;   // fan angle: q + off
-            if (!(FORM & FORM_SMALL) && __any(a > 0.41421357f * w)) {
-                float num = a, den = w;
-                if (a > 0.41421357f * w) {
-                    const bool steep = a > 2.4142135f * w;
-                    num = steep ? -w : a - w;
-                    den = steep ? a : a + w;
-                    off = copysignf(steep ? 1.57079633f : 0.78539816f, xu);
-                }
-                q = copysignf(1.0f, xu) * atan_small(div_nr(num, den));
+            if (FORM == FORM_ARC || (FORM == FORM_ANY && g.ru_lo == 0.0f)) {   // uniform
+                // the clamps change nothing for a point in front of the source; they
+                // tell the compiler which of atan2f's special cases cannot occur
+                // (nine of its operations)
+                const float xc = fminf(fmaxf(xu, -1e30f), 1e30f), wc = fminf(fmaxf(w, 1e-30f), 1e30f);
+                s = fmaf(atan2f(xc, wc), g.ru, g.cu);
             } else {
-                q = atan_small(div_nr(xu, w));
+                const float a = fabsf(xu);
+                float q, off = 0.0f;   // fan angle: q + off
+                if (!(FORM & FORM_SMALL) && __any(a > 0.41421357f * w)) {
+                    float num = a, den = w;
+                    if (a > 0.41421357f * w) {
+                        const bool steep = a > 2.4142135f * w;
+                        num = steep ? -w : a - w;
+                        den = steep ? a : a + w;
+                        off = copysignf(steep ? 1.57079633f : 0.78539816f, xu);
+                    }
+                    q = copysignf(1.0f, xu) * atan_small(div_nr(num, den));
+                } else {
+                    q = atan_small(div_nr(xu, w));
+                }
+                if (FORM != FORM_RANGE) {
+                    const float lo = (q + off) * g.ru_lo;
+                    fu = floorf(fmaf(q, g.ru, fmaf(off, g.ru, g.cu) + lo));
+                    t = fmaf(q, g.ru, fmaf(off, g.ru, g.cu - fu)) + lo;
+                    return;
+                }
+                s = fmaf(q + off, g.ru, g.cu);
             }
-            if ((FORM & FORM_FINE_ARC) || ((FORM == FORM_ANY || FORM == FORM_ATAN2) && g.ru_lo != 0.0f)) {   // uniform
-                const float lo = (q + off) * g.ru_lo;
-                fu = floorf(fmaf(q, g.ru, fmaf(off, g.ru, g.cu) + lo));
-                t = fmaf(q, g.ru, fmaf(off, g.ru, g.cu - fu)) + lo;
-                return;
-            }
-            s = fmaf(q + off, g.ru, g.cu);
         }
     }
     fu = floorf(s);

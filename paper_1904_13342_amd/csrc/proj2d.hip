@@ -492,7 +492,7 @@ __global__ void __launch_bounds__(1024) bp2d_seg_kernel(Geom2D g, const float2 *
     auto fetch = [&](int k0) {
         const float2 c = cl_next = views[min(k0 + (lane >> 2), g.n_proj - 1)];
         float fu, t, wt;
-        point2d<FAN>(g, c, qx, qy, fu, t, wt);
+        point2d<FAN, FORM_RANGE>(g, c, qx, qy, fu, t, wt);
         const float w = FAN ? fmaf(qx, c.x, fmaf(qy, c.y, g.sid)) : 1.0f;
         bool in = fabsf(fu) < 262144.0f;
         float mn = fu, mx = fu;
@@ -552,12 +552,12 @@ __global__ void __launch_bounds__(1024) bp2d_seg_kernel(Geom2D g, const float2 *
             };
             if (!FAN || !g.curved)
                 points(Form<FORM_FLAT>());
-            else if (!((small >> (4 * v)) & 1))
-                points(Form<FORM_ANY>());
-            else if (g.ru_lo != 0.0f)
+            else if (g.ru_lo == 0.0f)
+                points(Form<FORM_ARC>());
+            else if ((small >> (4 * v)) & 1)
                 points(Form<FORM_FINE_ARC | FORM_SMALL>());
             else
-                points(Form<FORM_ARC | FORM_SMALL>());
+                points(Form<FORM_FINE_ARC>());
             if ((ok >> (4 * v)) & 1) {
                 const int first = v * W - __builtin_amdgcn_readlane(lo, 4 * v);
 #pragma unroll

@@ -129,3 +129,76 @@ def test_fbp_of_disk(ph, ora):
     inner, ring = x[rr < 0.8 * r].mean(), x[(rr > 1.2 * r) & (rr < 1.5 * r)].mean()
     say(f"[curved disk fbp] inside {inner:.5f} ring {ring:.2e}")
     assert abs(inner - 1.0) < 2e-3 and abs(ring) < 2e-3
+
+
+# bins either side of where the scale to bins is held in two floats, and a
+# clinical arc; (ny, nx), nu, du
+LONG_ARCS = {"255_bins": ((130, 144), 255, 1.6), "257_bins": ((130, 144), 257, 1.6), "725_bins": ((300, 290), 725, 1.0)}
+
+
+def _long_arc(ph, name, n_proj):
+    shape, nu, du = LONG_ARCS[name]
+    spec = synth.config("fan2d_512").with_(kind="fan2d_curved", vol_shape=shape, vol_spacing=(1.0, 1.0),
+                                           det_shape=(nu,), det_spacing=(du,), n_proj=n_proj,
+                                           angular_range=2 * math.pi, sid=500.0, sdd=800.0)
+    g = ph.from_spec(spec)
+    return spec, g, ph.ray_vectors_2d(g)
+
+
+@pytest.mark.parametrize("name", list(LONG_ARCS))
+def test_pair_sees_the_same_coordinates(ph, name):
+    """The weight that B gives a view's odd bins in a pixel is the sum of the
+    odd bins of B^T of that pixel, to the rounding of the products: a bin
+    coordinate of another rounding (2^-15 bin at 725 bins) would show as its
+    difference.  B one item at a time and in a batch, B^T by strips (few views
+    of few items) and by runs."""
+    views = 6
+    spec, g, rv = _long_arc(ph, name, views)
+    nu, dev = spec.det_shape[0], gc.device()
+    odd = torch.zeros((views, views, nu), device=dev)   # item k: the odd bins of view k
+    for k in range(views):
+        odd[k, k, 1::2] = 1.0
+    say(f"[curved pair] {name}")
+    B = ph.backproject_fan2d(g, rv, odd)
+    one = torch.stack([ph.backproject_fan2d(g, rv, odd[k].contiguous()) for k in range(views)])
+    ny, nx = spec.vol_shape
+    rng = np.random.default_rng(21)
+    for items in (30, 60):
+        y, x = rng.integers(0, ny, items), rng.integers(0, nx, items)
+        e = torch.zeros((items, ny, nx), device=dev)
+        e[torch.arange(items), torch.as_tensor(y), torch.as_tensor(x)] = 1.0
+        bT = ph.backproject_adjoint_fan2d(g, rv, e)                       # [items, views, nu]
+        got = bT[:, :, 1::2].double().sum(2).cpu()
+        # dbeta * wt is at most the largest view weight; four roundings of it
+        scale = float(bT.double().sum(2).max())
+        for b in (B, one):
+            want = b[:, torch.as_tensor(y), torch.as_tensor(x)].T.double().cpu()
+            worst = float((got - want).abs().max()) / scale
+            say(f"  {items} pixels: largest difference {worst:.1e} of the weight")
+            assert worst <= 4 * 2.0 ** -24
+
+
+@pytest.mark.parametrize("views", [9, 300])
+@pytest.mark.parametrize("name", list(LONG_ARCS))
+def test_backproject_adjoint_long_arcs(ph, ora, name, views):
+    """B^T of white noise by strips and by runs.  A bin coordinate carries up to
+    three roundings at nu / 2 to nu bins (2^-25 nu each), which move a weight by
+    as much; noise does not average it."""
+    spec, g, rv = _long_arc(ph, name, views)
+    f = as_f32(np.random.default_rng(22).standard_normal(spec.vol_shape))
+    say(f"[curved B^T] {name}, {views} views")
+    check(to_np(ph.backproject_adjoint_fan2d(g, rv, to_dev(f))), ora.backproject_adjoint(spec, f), "B^T",
+          tol=3 * 2.0 ** -25 * spec.det_shape[0], elem=1.0)
+
+
+def test_transposes_512(ph):
+    """<B y, x> = <y, B^T x> at the fan workload's sizes."""
+    spec, g, rv = _setup(ph, "curved_512")
+    y = as_f32(synth.random_array((spec.n_proj, spec.det_shape[0]), 3))
+    x = as_f32(synth.random_array(spec.vol_shape, 4))
+    bx = to_np(ph.backproject_fan2d(g, rv, to_dev(y)))
+    bt = to_np(ph.backproject_adjoint_fan2d(g, rv, to_dev(x)))
+    lhs, rhs = np.vdot(bx, x), np.vdot(y, bt)
+    size = np.linalg.norm(bx) * np.linalg.norm(x)
+    say(f"[curved transposes] 512: {abs(lhs - rhs) / size:.1e} of |B y| |x|")
+    assert abs(lhs - rhs) <= 1e-7 * size
