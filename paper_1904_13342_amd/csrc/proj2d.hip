@@ -126,6 +126,7 @@ __global__ void __launch_bounds__(256) fp2d_kernel(Geom2D g, const float2 *__res
 // lane slots per sample, VALU-bound).
 constexpr int SL_D = 7;          // planes a slab advances
 constexpr int SL_P = SL_D + 1;   // planes it holds
+constexpr size_t SL_LDS = 65536;   // LDS of a workgroup, at most
 
 __device__ __forceinline__ int floor_int(float x)
 {
@@ -643,12 +644,15 @@ hipError_t fp2d_slab(const Geom2D &g, const float2 *views, const void *img, void
         return hipErrorInvalidConfiguration;
     // waves per 64 rays: about 64 on every CU in all (512^2, 360 fan views: 283,
     // 192, 161 and 160 us for 4096, 8192, 16384 and 32768 waves), at least
-    // three slabs each
+    // three slabs each, and two workgroups or more to a CU's LDS (the widest
+    // slabs, 512^2 and 60, 120 and 170 fan views: 52, 88 and 120 us for the 16
+    // waves of one workgroup, 45, 72 and 90 for at most eight)
+    constexpr size_t slab = (size_t)SL_P * SW * sizeof(float);   // LDS of a wave
     int waves = 1;
-    while (waves < 16 && blocks * waves < 16384 && 2 * waves * 3 * SL_D <= (g.nx < g.ny ? g.nx : g.ny))
+    while (waves < 16 && blocks * waves < 16384 && 2 * waves * 3 * SL_D <= (g.nx < g.ny ? g.nx : g.ny) &&
+           2 * waves * slab <= SL_LDS)
         waves *= 2;
-    hipLaunchKernelGGL((fp2d_slab_kernel<T, FAN, SW>), dim3((unsigned)blocks), dim3(64 * waves),
-                       (size_t)waves * SL_P * SW * sizeof(float), s, g, views, (const T *)img, (T *)sino, groups);
+    hipLaunchKernelGGL((fp2d_slab_kernel<T, FAN, SW>), dim3((unsigned)blocks), dim3(64 * waves), waves * slab, s, g, views, (const T *)img, (T *)sino, groups);
     return hipGetLastError();
 }
 

@@ -132,3 +132,15 @@ def test_project_2d_thin_images(ph, ora, kind, du, shape):
     out = to_np(A(g, rv, to_dev(f)))
     for n in range(2):
         check(out[n], ora.project(spec, f[n]), f"item {n}", tol=2e-5)
+
+
+@pytest.mark.parametrize("nu,du,views", [(345, 1.4, 90), (345, 1.4, 300), (250, 1.9, 140)])
+def test_project_2d_wide_slabs(ph, ora, nu, du, views):
+    """The widest slabs with as many waves to a workgroup as its share of the
+    LDS holds, and bins just too wide for them."""
+    spec = synth.config("par2d_64").with_(vol_shape=(341, 345), vol_spacing=(1.0, 1.0), det_shape=(nu,),
+                                          det_spacing=(du,), n_proj=views, angular_range=math.pi)
+    g = ph.from_spec(spec)
+    f = as_f32(np.random.default_rng(12).uniform(0.5, 1.5, spec.vol_shape))
+    say(f"[A 2D] {nu} bins of {du}, {views} views")
+    check(to_np(ph.project_par2d(g, ph.ray_vectors_2d(g), to_dev(f))), ora.project(spec, f), "A", tol=2e-5)
