@@ -667,7 +667,12 @@ hipError_t fp2d_f(const Geom2D &g, const float2 *views, const void *img, void *s
     const float wx = g.nx * g.sx, wy = g.ny * g.sy;
     const float far = FAN ? (g.sid + 0.5f * sqrtf(wx * wx + wy * wy)) / g.ru : g.du;
     const float span = 63.0f * 1.4143f * far / fminf(g.sx, g.sy) + SL_D + 5.0f;
-    if ((long)((g.nu + 63) / 64) * g.n_proj * batch >= 512 && g.step <= fminf(g.sx, g.sy)) {
+    // A wave with few rays walks its slabs all the same: at least half of the
+    // lanes have one (256^2 and 40000 rays of 1, 9, 25, 33, 45, 65 and 96 bins: 51
+    // us direct at all, in slabs 626, 88, 44, 36, 32, 41 and 40; 700^2: 87 direct,
+    // 1700, 220, 140, 108, 91, 122 and 119).
+    const long groups = (g.nu + 63) / 64;
+    if (groups * g.n_proj * batch >= 512 && 2L * g.nu > 64 * groups && g.step <= fminf(g.sx, g.sy)) {
         if (span <= 104.0f)
             return fp2d_slab<T, FAN, 104>(g, views, img, sino, batch, s);
         if (span <= 168.0f)
