@@ -279,7 +279,7 @@ __device__ __forceinline__ float slab_walk_2d(const Geom2D &g, const T *im, floa
         int m_end = m;
         if (m <= ke && in_slab(m)) {
             const float bound = (float)(up ? x.a0 + SL_D : x.a0);
-            m_end = min(m + max((int)ceilf((bound - fmaf((float)m, eA, PA)) * rEA), 1), ke + 1);
+            m_end = sample_beyond(m, ke, bound, fmaf((float)m, eA, PA), rEA);
 #pragma clang loop unroll(disable) vectorize(disable) interleave(disable)
             while (m_end > m + 1 && !in_slab(m_end - 1))
                 --m_end;

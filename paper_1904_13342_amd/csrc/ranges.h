@@ -38,4 +38,12 @@ __host__ __device__ __forceinline__ void cell_range(float X0, float Y0, float eX
     last = cells ? (int)floorf(hi) : 0;
 }
 
+// First guess at the sample after m, at coordinate at, that lies beyond bound,
+// for rays that advance by 1 / rate; between m + 1 and last + 1 (compared as
+// floats: a ray that hardly advances never gets there).  last - m < 2^24.
+__host__ __device__ __forceinline__ int sample_beyond(int m, int last, float bound, float at, float rate)
+{
+    return m + (int)fmaxf(fminf(ceilf((bound - at) * rate), (float)(last + 1 - m)), 1.0f);
+}
+
 }  // namespace ph

@@ -6,3 +6,8 @@ extern "C" void cell_range_of(float X0, float Y0, float eX, float eY, int nx, in
 {
     ph::cell_range(X0, Y0, eX, eY, nx, ny, (size_t)elem, *first, *last);
 }
+
+extern "C" int sample_beyond_of(int m, int last, float bound, float at, float rate)
+{
+    return ph::sample_beyond(m, last, bound, at, rate);
+}

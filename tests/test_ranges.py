@@ -21,6 +21,8 @@ def ranges(tmp_path_factory):
     f, i = ctypes.c_float, ctypes.c_int
     L.cell_range_of.argtypes = [f, f, f, f, i, i, i, ctypes.POINTER(i), ctypes.POINTER(i)]
     L.cell_range_of.restype = None
+    L.sample_beyond_of.argtypes = [i, i, f, f, f]
+    L.sample_beyond_of.restype = i
     return L
 
 
@@ -63,3 +65,18 @@ def test_unchecked_samples_lie_inside(ranges, shape):
         assert X.min() >= 0 and Y.min() >= 0 and X.max() < nx - 1 and Y.max() < ny - 1, (ray, first, last)
         seen += 1
     assert seen == 0 if min(shape) < 2 else seen > 0
+
+
+@pytest.mark.parametrize("m,last", [(0, 0), (5, 700), (-300, 4), (1 << 22, (1 << 22) + 90), (-(1 << 22), 1 << 22)])
+@pytest.mark.parametrize("step", [0.5, 1.0, 1e-3, 3e-9, 1e-12, 1e-19])
+def test_sample_beyond_stays_in_range(ranges, m, last, step):
+    """The guess at where a ray leaves a slab lies in m + 1 .. last + 1, so that
+    the search from it takes a bounded number of steps, however slowly the ray
+    advances."""
+    for sign in (1.0, -1.0):
+        rate = float(np.float32(1.0) / np.float32(sign * step))
+        for gap in (0.0, 0.25, 6.9, -1e-3):
+            n = ranges.sample_beyond_of(m, last, 100.0 + sign * gap, 100.0, rate)
+            assert m + 1 <= n <= max(last, m) + 1
+            if gap > 0 and gap / step < 1e6:
+                assert abs(min(m + gap / step, last + 1) - n) <= 1 + 1e-5 * gap / step
