@@ -16,6 +16,7 @@
 // footprint covers it (FP32 output); the 3D B^T sits beside the back-projector
 // it mirrors.
 #include "device_util.h"
+#include "ranges.h"
 
 namespace ph {
 namespace {
@@ -211,10 +212,10 @@ __global__ void __launch_bounds__(1024) fpT2d_kernel(Geom2D g, const float2 *__r
 // ms against 63 for 256 threads and 640 rays, and 4.4 against 5.1 ms at 128^3.
 //
 // Sample ranges come from a clip with hardware reciprocals (relative error
-// ~1e-7 of a few thousand steps), widened by 0.01 step: every sample inside
-// the support box is visited, and a visited sample lies at most 0.01 step
-// outside it, so its cell is one of floor coordinates x0 - 2 .. x0 + 16 and
-// its corners reach x0 + 17.  Cells of the halo (x0 - 2, x0 - 1, x0 + 16 and
+// ~1e-7 of a few thousand steps), widened by 0.01 step or half a voxel: every
+// sample inside the support box is visited, and a visited sample lies less than
+// a voxel outside it, so its cell is one of floor coordinates x0 - 2 .. x0 + 16
+// and its corners reach x0 + 17.  Cells of the halo (x0 - 2, x0 - 1, x0 + 16 and
 // x0 + 17 on any axis) are never read, since the neighbouring bricks own those
 // voxels, so they need no clearing, and the first and the last share a column
 // (of the row before), a row and a plane.  Rows and planes have odd pitches:
@@ -231,7 +232,6 @@ constexpr int AT_RAYS = 1024;                  // footprint pixels per pass (ray
 constexpr int AT_Z = AT_B * AT_B * AT_B / AT_T;   // voxels per thread (a piece of a z-column)
 constexpr int AT_PER_THREAD = (AT_RAYS + AT_T - 1) / AT_T;
 constexpr int AT_BINS = 256;                   // sample-count bins of the ray sort
-constexpr float AT_EPS = 0.01f;                // clip widening (steps)
 constexpr float AT_FIX = 1073741824.0f;        // 2^30
 
 template <typename T, typename TI>
@@ -327,20 +327,22 @@ __global__ void __launch_bounds__(AT_T, 4) fpT_cone_kernel(Geom3D g, const ConeF
                 if (gv == 0.0f)
                     continue;
                 const Ray r = make_cone_ray(g, fv, j, i);
+                const float re_max =
+                    __builtin_amdgcn_rcpf(fmaxf(fabsf(r.e[0]), fmaxf(fabsf(r.e[1]), fabsf(r.e[2]))));
+                const float eps = clip_margin(re_max);
                 float lo = -3.0e38f, hi = 3.0e38f;
                 if (!clip_line_rcp(r.p[0], r.e[0], sx0, sx1, lo, hi) ||
                     !clip_line_rcp(r.p[1], r.e[1], sy0, sy1, lo, hi) ||
-                    !clip_line_rcp(r.p[2], r.e[2], sz0, sz1, lo, hi) || !(lo < hi + 2.0f * AT_EPS))
+                    !clip_line_rcp(r.p[2], r.e[2], sz0, sz1, lo, hi) || !(lo < hi + 2.0f * eps))
                     continue;
-                const int m0 = (int)ceilf(lo - AT_EPS), m1 = (int)floorf(hi + AT_EPS);
+                const int m0 = (int)ceilf(lo - eps), m1 = (int)floorf(hi + eps);
                 if (m1 < m0)
                     continue;
                 cnt[u] = m1 - m0 + 1;
                 ra[u] = make_float4(r.p[0] + RAY_BIAS, r.p[1] + RAY_BIAS, r.p[2] + RAY_BIAS, gv);
                 rb[u] = make_float4(r.e[0], r.e[1], r.e[2], __int_as_float(m0));
-                const float emax = fmaxf(fabsf(r.e[0]), fmaxf(fabsf(r.e[1]), fabsf(r.e[2])));
                 // 1 / e_max + 1, rounded up by a relative 1e-5 (the hardware reciprocal is within 1 ulp)
-                lb = fmaf(fabsf(gv), fmaf(__builtin_amdgcn_rcpf(emax), 1.00001f, 1.00001f), lb);
+                lb = fmaf(fabsf(gv), fmaf(re_max, 1.00001f, 1.00001f), lb);
                 atomicAdd(&hist[min(cnt[u], AT_BINS - 1)], 1);
             }
 #pragma unroll

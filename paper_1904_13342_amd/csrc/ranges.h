@@ -46,4 +46,10 @@ __host__ __device__ __forceinline__ int sample_beyond(int m, int last, float bou
     return m + (int)fmaxf(fminf(ceilf((bound - at) * rate), (float)(last + 1 - m)), 1.0f);
 }
 
+// How far beyond its clip (in steps) a ray is visited in the 3D A^T: 0.01 step,
+// which covers the rounding of the clip, but at most half a voxel, so that no
+// sample visited lies a voxel outside the box it was clipped to.  re_max = 1 /
+// (largest increment of an index per step).
+__host__ __device__ __forceinline__ float clip_margin(float re_max) { return fminf(0.01f, 0.5f * re_max); }
+
 }  // namespace ph

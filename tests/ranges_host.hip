@@ -11,3 +11,5 @@ extern "C" int sample_beyond_of(int m, int last, float bound, float at, float ra
 {
     return ph::sample_beyond(m, last, bound, at, rate);
 }
+
+extern "C" float clip_margin_of(float re_max) { return ph::clip_margin(re_max); }

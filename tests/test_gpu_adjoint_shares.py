@@ -107,3 +107,16 @@ def test_backproject_adjoint_shares(ph, ora, views, batch):
     say(f"[B^T shares] {views} views, batch {batch}")
     check(to_np(ph.backproject_adjoint_cone3d(g, ph.projection_matrices_3d(g), to_dev(f))),
           np.stack([ora.backproject_adjoint(spec, v) for v in f]), "B^T")
+
+
+@pytest.mark.parametrize("step", [40.0, 99.0, 150.0, 400.0])
+def test_project_adjoint_long_steps(ph, ora, step):
+    """Sampling steps of many voxels: few rays have a sample in a brick, and the
+    margin of their clip must not reach past the accumulator's halo."""
+    spec = synth.config("cone3d_crop32").with_(vol_shape=(33, 40, 50), vol_spacing=(1.0, 1.0, 1.0), det_shape=(60, 70),
+                                               det_spacing=(1.5, 1.5), n_proj=24, sid=300.0, sdd=500.0, step_mm=step)
+    g = ph.from_spec(spec)
+    p = as_f32(np.random.default_rng(4).uniform(0.5, 1.5, (24, 60, 70)))
+    say(f"[A^T] step {step}")
+    check(to_np(ph.project_adjoint_cone3d(g, ph.projection_matrices_3d(g), to_dev(p))), ora.project_adjoint(spec, p),
+          "A^T")

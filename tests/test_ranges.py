@@ -23,6 +23,8 @@ def ranges(tmp_path_factory):
     L.cell_range_of.restype = None
     L.sample_beyond_of.argtypes = [i, i, f, f, f]
     L.sample_beyond_of.restype = i
+    L.clip_margin_of.argtypes = [f]
+    L.clip_margin_of.restype = f
     return L
 
 
@@ -80,3 +82,12 @@ def test_sample_beyond_stays_in_range(ranges, m, last, step):
             assert m + 1 <= n <= max(last, m) + 1
             if gap > 0 and gap / step < 1e6:
                 assert abs(min(m + gap / step, last + 1) - n) <= 1 + 1e-5 * gap / step
+
+
+@pytest.mark.parametrize("e_max", [1e-3, 0.3, 0.5, 1.0, 49.0, 51.0, 99.0, 101.0, 150.0, 1e4])
+def test_clip_margin_is_less_than_a_voxel(ranges, e_max):
+    """The accumulator's halo is one voxel beyond the clip box, whatever the
+    sampling step; within it the margin is 0.01 step or half a voxel."""
+    margin = ranges.clip_margin_of(1.0 / e_max)
+    assert margin * e_max <= 0.5 * (1 + 1e-6)
+    assert margin == pytest.approx(min(0.01, 0.5 / e_max))
