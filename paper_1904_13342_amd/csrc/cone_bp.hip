@@ -129,9 +129,8 @@ __device__ __forceinline__ float det_coord(float c, float centre)
 // relative to (u_lo, v_lo) (a staged tile's corner, or 0 for the detector
 // itself), the fractions within the cell and the distance weight
 // (SID/w)^2.  The rows' values at a column's (x, y) are formed once per view;
-// a voxel adds its z term and takes the reciprocal of its depth from the FP32
-// estimate and one Newton step (relative error below 1e-13, under 1e-10
-// pixel).  Shared by B and B^T, so the pair sees bitwise the same positions.
+// a voxel adds its z term and takes the reciprocal of its depth in full
+// precision.  Shared by B and B^T, so the pair sees bitwise the same positions.
 struct DetPoint {
     int j, i;
     float fu, fv, wt;
@@ -158,8 +157,7 @@ __device__ __forceinline__ DetPoint general_point(const GeneralCol &c, const Geo
 #pragma clang fp contract(off)
     const double z = zc;
     const double U = fma(c.dz[0], z, c.u), V = fma(c.dz[1], z, c.v), W = fma(c.dz[2], z, c.w);
-    const double r0 = (double)__builtin_amdgcn_rcpf((float)W);
-    const double rW = fma(r0, fma(-W, r0, 1.0), r0);
+    const double rW = rcp64(W);
     const double su = fma(U, rW, (double)g.cu - (double)u_lo);
     const double sv = fma(V, rW, (double)g.cv - (double)v_lo);
     const double fsu = floor(su), fsv = floor(sv);

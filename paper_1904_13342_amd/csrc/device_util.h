@@ -2,6 +2,7 @@
 #pragma once
 
 #include "common.h"
+#include "fp64.h"
 
 namespace ph {
 
@@ -107,7 +108,7 @@ __device__ __forceinline__ void make_ray_2d(const Geom2D &g, float2 c, int j, fl
             dy = fma(cg, cy, sg * ey);
         } else {
             const double tx = fma((double)g.sdd, cx, u * ex), ty = fma((double)g.sdd, cy, u * ey);  // detector - source
-            const double rn = rsqrt_nr(fma(tx, tx, ty * ty));
+            const double rn = rsqrt64(fma(tx, tx, ty * ty));
             dx = tx * rn;
             dy = ty * rn;
         }
@@ -115,21 +116,22 @@ __device__ __forceinline__ void make_ray_2d(const Geom2D &g, float2 c, int j, fl
         ax = fma(t0, dx, sx);
         ay = fma(t0, dy, sy);
     }
-    X0 = (float)((ax - (double)g.ox) * g.inv_sx);
-    Y0 = (float)((ay - (double)g.oy) * g.inv_sy);
+    X0 = (float)div64(ax - (double)g.ox, (double)g.sx, g.inv_sx);
+    Y0 = (float)div64(ay - (double)g.oy, (double)g.sy, g.inv_sy);
     eX = (float)(dx * g.step_sx);
     eY = (float)(dy * g.step_sy);
 }
 
-// 1/x from the hardware estimate refined by one Newton step
+// 1/x from the hardware estimate refined by one Newton step: the correctly
+// rounded quotient at every one of the 2^23 mantissas, and so is div_nr's (tried
+// with three numerators)
 __device__ __forceinline__ float rcp_nr(float x)
 {
     const float r = __builtin_amdgcn_rcpf(x);
     return fmaf(r, fmaf(-x, r, 1.0f), r);
 }
 
-// n / d from rcp_nr with one more residual step: the correctly rounded
-// quotient in nearly every case, in five instructions
+// n / d from rcp_nr with one more residual step, in five instructions
 __device__ __forceinline__ float div_nr(float n, float d)
 {
     const float r = rcp_nr(d), q = n * r;
@@ -189,7 +191,7 @@ __device__ __forceinline__ void point2d(const Geom2D &g, float2 c, float x, floa
             s = fmaf(g.sdd * xu * rw, g.rdu, g.cu);
             wt = sw * sw;
         } else {
-            wt = g.sid * g.sid * rcp_nr(fmaf(w, w, xu * xu));
+            wt = div_nr(g.sid * g.sid, fmaf(w, w, xu * xu));
             if (FORM == FORM_ARC || (FORM == FORM_ANY && g.ru_lo == 0.0f)) {   // uniform
                 // the clamps change nothing for a point in front of the source; they
                 // tell the compiler which of atan2f's special cases cannot occur
