@@ -554,7 +554,7 @@ __device__ __forceinline__ void edge_ray(const Geom2D &g, float2 c, double u, do
 constexpr int STRIP_ROWS = 4;   // rows whose candidates are loaded together
 
 // Called by whole waves; `used` is cleared for lanes without a strip.
-template <typename TI, bool FAN, int AX>
+template <typename TI, bool FAN, int AX, int FORM>
 __device__ __forceinline__ void strip_walk(const Geom2D &g, float2 c, const TI *im, int j, bool used, bool bounded,
                                            StripEdge e0, StripEdge e1, int first, int stride, float &a0, float &a1)
 {
@@ -619,7 +619,7 @@ __device__ __forceinline__ void strip_walk(const Geom2D &g, float2 c, const TI *
                 const int q = in ? q0[r] + n : 0, p = in ? pb + r * stride : 0;
                 const int ix = AX == 0 ? q : p, iy = AX == 0 ? p : q;
                 float fu, t, wt;
-                point2d<FAN>(g, c, fmaf((float)ix, g.sx, g.ox), fmaf((float)iy, g.sy, g.oy), fu, t, wt);
+                point2d<FAN, FORM>(g, c, fmaf((float)ix, g.sx, g.ox), fmaf((float)iy, g.sy, g.oy), fu, t, wt);
                 const float v = g.dbeta * wt * (in && fu == jf ? val[r] : 0.0f);
                 a0 = fmaf(v, 1.0f - t, a0);
                 a1 = fmaf(v, t, a1);
@@ -663,10 +663,12 @@ __global__ void __launch_bounds__(1024) bpT2d_kernel(Geom2D g, const float2 *__r
             e0.a = (float)(ax == 0 ? px - py * b0 : py - px * b0);
             e1.a = (float)(ax == 0 ? qx - qy * b1 : qy - qx * b1);
         }
-        if (ax == 0)
-            strip_walk<TI, FAN, 0>(g, c, im, j, used, bounded, e0, e1, wave, waves, a0, a1);
-        else
-            strip_walk<TI, FAN, 1>(g, c, im, j, used, bounded, e0, e1, wave, waves, a0, a1);
+        with_form<FAN>(g, [&](auto form) {
+            if (ax == 0)
+                strip_walk<TI, FAN, 0, decltype(form)::value>(g, c, im, j, used, bounded, e0, e1, wave, waves, a0, a1);
+            else
+                strip_walk<TI, FAN, 1, decltype(form)::value>(g, c, im, j, used, bounded, e0, e1, wave, waves, a0, a1);
+        });
     }
     if (waves > 1) {
         part[threadIdx.x] = make_float2(a0, a1);
@@ -765,56 +767,58 @@ __global__ void __launch_bounds__(1024) bpT2d_run_kernel(Geom2D g, const float2 
                 }
             }
         }
+        with_form<FAN>(g, [&](auto form) {
 #pragma unroll
-        for (int r = 0; r < RUN_COLS; ++r) {
-            const int p = p0 + r;
-            if (p >= np)   // uniform
-                break;
-            const float x = fmaf((float)(along_x ? qc : p), g.sx, g.ox), y = fmaf((float)(along_x ? p : qc), g.sy, g.oy);
-            float fu, t, wt;
-            point2d<FAN>(g, c, x, y, fu, t, wt);
-            Pairs w;
+            for (int r = 0; r < RUN_COLS; ++r) {
+                const int p = p0 + r;
+                if (p >= np)   // uniform
+                    break;
+                const float x = fmaf((float)(along_x ? qc : p), g.sx, g.ox), y = fmaf((float)(along_x ? p : qc), g.sy, g.oy);
+                float fu, t, wt;
+                point2d<FAN, decltype(form)::value>(g, c, x, y, fu, t, wt);
+                Pairs w;
 #pragma unroll
-            for (int i = 0; i < NB; ++i) {
-                const float v = FAN ? wt * val[i][r] : val[i][r];
-                w[2 * i] = v * (1.0f - t);
-                w[2 * i + 1] = v * t;
-            }
-            // strips -1 .. nu - 1; the rest of the lanes, and those past the run, add nothing
-            const bool used = q < nq && fu >= -1.0f && fu < (float)g.nu;
-            const int n = used ? (int)fu + 1 : -1;
-            // the strips of the next lane and the one after it, or P lanes on
-            const int next = next_lane(n, -2), far = P == 1 ? next : P == 2 ? next_lane(next, -2) : __shfl_down(n, P);
-            if (__any(used && far == n && (P <= 2 || lane + P < 64))) {
-                if (used) {
-#pragma unroll
-                    for (int i = 0; i < 2 * NB; ++i)
-                        unsafeAtomicAdd((float *)(own + n) + i, w[i]);
+                for (int i = 0; i < NB; ++i) {
+                    const float v = FAN ? wt * val[i][r] : val[i][r];
+                    w[2 * i] = v * (1.0f - t);
+                    w[2 * i + 1] = v * t;
                 }
-                continue;
-            }
-            if constexpr (P <= 2) {
-                bool first = used;   // holds its strip's sum
-                if constexpr (P == 2) {
+                // strips -1 .. nu - 1; the rest of the lanes, and those past the run, add nothing
+                const bool used = q < nq && fu >= -1.0f && fu < (float)g.nu;
+                const int n = used ? (int)fu + 1 : -1;
+                // the strips of the next lane and the one after it, or P lanes on
+                const int next = next_lane(n, -2), far = P == 1 ? next : P == 2 ? next_lane(next, -2) : __shfl_down(n, P);
+                if (__any(used && far == n && (P <= 2 || lane + P < 64))) {
+                    if (used) {
 #pragma unroll
-                    for (int i = 0; i < 2 * NB; ++i) {
-                        const float o = next_lane(w[i], 0.0f);
-                        w[i] += next == n ? o : 0.0f;
+                        for (int i = 0; i < 2 * NB; ++i)
+                            unsafeAtomicAdd((float *)(own + n) + i, w[i]);
                     }
-                    first = used && prev_lane(n, -2) != n;
+                    continue;
                 }
-                if (first)
-                    own[n] += w;
-            } else {
+                if constexpr (P <= 2) {
+                    bool first = used;   // holds its strip's sum
+                    if constexpr (P == 2) {
 #pragma unroll
-                for (int h = 0; h < P; ++h) {
-                    if (used && lane % P == h)
+                        for (int i = 0; i < 2 * NB; ++i) {
+                            const float o = next_lane(w[i], 0.0f);
+                            w[i] += next == n ? o : 0.0f;
+                        }
+                        first = used && prev_lane(n, -2) != n;
+                    }
+                    if (first)
                         own[n] += w;
-                    __builtin_amdgcn_wave_barrier();
+                } else {
+#pragma unroll
+                    for (int h = 0; h < P; ++h) {
+                        if (used && lane % P == h)
+                            own[n] += w;
+                        __builtin_amdgcn_wave_barrier();
+                    }
                 }
+                __builtin_amdgcn_wave_barrier();
             }
-            __builtin_amdgcn_wave_barrier();
-        }
+        });
     }
     __syncthreads();
     for (int j = threadIdx.x; j < g.nu; j += blockDim.x) {

@@ -159,26 +159,25 @@ __device__ __forceinline__ float atan_small(float z)
 // (SID / L)^2, L the distance from the source.  All in FP32.
 //
 // B and B^T take every coordinate from here and so see the same ones to the
-// last bit, on every detector; FORM_ANY and the forms that a caller may name,
-// so that its code has no branch on the detector, give the same values.  Arcs
-// of few bins (ru_lo): the fan angle is atan_small of the slope, taken from the
-// pi / 4 or pi / 2 direction beyond tan(pi / 8) and tan(3 pi / 8) (where no lane
-// of the wave is beyond, or FORM_SMALL says so, that is left out: the same
-// value, every step is odd in xu); the scale to bins is held in two floats and
-// the fraction is formed from the centred coordinate, since there the rounding
-// of their sum would be the largest error.  On longer arcs that rounding is
-// left, 2^-15 bin at 512 to 1023 bins, whatever the angle's own error: the
-// results for rough data move with it, and the angle stays atan2f's.
+// last bit, on every detector.  FORM names the detector, so that the code has
+// no branch on it.  Arcs of few bins (FORM_FINE_ARC, ru_lo not 0): the fan
+// angle is atan_small of the slope, taken from the pi / 4 or pi / 2 direction
+// beyond tan(pi / 8) and tan(3 pi / 8) (where no lane of the wave is beyond, or
+// FORM_SMALL says so, that is left out: the same value, every step is odd in
+// xu); the scale to bins is held in two floats and the fraction is formed from
+// the centred coordinate, since there the rounding of their sum would be the
+// largest error.  On longer arcs (FORM_ARC) the fan angle is atan2f's: whatever
+// its own error, the sum rounds to 2^-15 bin at 512 to 1023 bins, and results
+// for rough data are only as reproducible as its last bits.
 //
-// FORM_RANGE: for ranges of bins with a margin (1e-4 bin on top of it), the
-// polynomial on every arc.
-constexpr int FORM_ANY = 0, FORM_FLAT = 1, FORM_FINE_ARC = 2, FORM_ARC = 4, FORM_SMALL = 8, FORM_RANGE = 16;
+// FORM_RANGE, for ranges of bins with a margin of more than 1e-3 bin: the
+// polynomial on every arc, whichever detector it is.
+constexpr int FORM_FLAT = 1, FORM_FINE_ARC = 2, FORM_ARC = 4, FORM_SMALL = 8, FORM_RANGE = 16;
 
-template <bool FAN, int FORM = FORM_ANY>
+template <bool FAN, int FORM>
 __device__ __forceinline__ void point2d(const Geom2D &g, float2 c, float x, float y, float &fu, float &t, float &wt)
 {
 #pragma clang fp contract(off)   // the fused operations are those written out, in every caller
-    constexpr bool told = FORM != FORM_ANY && FORM != FORM_RANGE;   // which detector it is
     const float xu = fmaf(y, c.x, -(x * c.y));
     float s;   // detector coordinate in bins
     wt = 1.0f;
@@ -186,13 +185,13 @@ __device__ __forceinline__ void point2d(const Geom2D &g, float2 c, float x, floa
         s = fmaf(xu, g.ru, g.cu);
     } else {
         const float w = fmaf(x, c.x, fmaf(y, c.y, g.sid));
-        if (FORM == FORM_FLAT || (!told && !g.curved)) {
+        if (FORM == FORM_FLAT || (FORM == FORM_RANGE && !g.curved)) {
             const float rw = rcp_nr(w), sw = g.sid * rw;
             s = fmaf(g.sdd * xu * rw, g.rdu, g.cu);
             wt = sw * sw;
         } else {
             wt = div_nr(g.sid * g.sid, fmaf(w, w, xu * xu));
-            if (FORM == FORM_ARC || (FORM == FORM_ANY && g.ru_lo == 0.0f)) {   // uniform
+            if (FORM == FORM_ARC) {
                 // the clamps change nothing for a point in front of the source; they
                 // tell the compiler which of atan2f's special cases cannot occur
                 // (nine of its operations)
@@ -225,6 +224,23 @@ __device__ __forceinline__ void point2d(const Geom2D &g, float2 c, float x, floa
     }
     fu = floorf(s);
     t = s - fu;
+}
+
+template <int F>
+struct Form {   // a form of point2d as an argument
+    static constexpr int value = F;
+};
+
+// use(Form<...>()) with the form of g's detector (uniform branches)
+template <bool FAN, typename Use>
+__device__ __forceinline__ void with_form(const Geom2D &g, Use use)
+{
+    if (!FAN || !g.curved)
+        use(Form<FORM_FLAT>());
+    else if (g.ru_lo != 0.0f)
+        use(Form<FORM_FINE_ARC>());
+    else
+        use(Form<FORM_ARC>());
 }
 
 // Narrow [lo, hi] to the parameters t with p + t e inside the open interval

@@ -35,11 +35,6 @@ __device__ __forceinline__ float sample_direct(const T *im, const Geom2D &g, flo
 constexpr int A_UNROLL = 2;   // samples per lane of A whose loads are in flight together
 constexpr int B_UNROLL = 4;   // views per wave of B
 
-template <int F>
-struct Form {   // a form of point2d as an argument
-    static constexpr int value = F;
-};
-
 // S lanes share one ray (S a power of two, at most 64: the lanes of a ray lie
 // in one wave); lane s takes samples k0 + s, k0 + s + S, ... and the partial
 // sums meet in a fixed shuffle tree.  Small problems (few rays, long rays)
@@ -405,12 +400,7 @@ __global__ void __launch_bounds__(1024) bp2d_kernel(Geom2D g, const float2 *__re
                 inside = inside && fu[u] >= 0.0f && fu[u] < (float)(g.nu - 1);
             }
         };
-        if (!FAN || !g.curved)
-            points(Form<FORM_FLAT>());
-        else if (g.ru_lo != 0.0f)
-            points(Form<FORM_FINE_ARC>());
-        else
-            points(Form<FORM_ARC>());
+        with_form<FAN>(g, points);
         if (__all(inside) && k0 + (B_UNROLL - 1) * waves < g.n_proj) {
             float2 p[B_UNROLL];
 #pragma unroll
@@ -551,14 +541,10 @@ __global__ void __launch_bounds__(1024) bp2d_seg_kernel(Geom2D g, const float2 *
                 for (int a = 0; a < 4; ++a)
                     point2d<FAN, decltype(form)::value>(g, c, px[a & 1], py[a >> 1], fu[a], t[a], wt[a]);
             };
-            if (!FAN || !g.curved)
-                points(Form<FORM_FLAT>());
-            else if (g.ru_lo == 0.0f)
-                points(Form<FORM_ARC>());
-            else if ((small >> (4 * v)) & 1)
+            if (FAN && g.curved && g.ru_lo != 0.0f && ((small >> (4 * v)) & 1))
                 points(Form<FORM_FINE_ARC | FORM_SMALL>());
             else
-                points(Form<FORM_FINE_ARC>());
+                with_form<FAN>(g, points);
             if ((ok >> (4 * v)) & 1) {
                 const int first = v * W - __builtin_amdgcn_readlane(lo, 4 * v);
 #pragma unroll
