@@ -201,13 +201,29 @@ def project_adjoint_fan2d(g, ray_vecs, sino, out=None):
     return _unary("ph_project_adjoint_fan2d", g, ray_vecs, sino, _sino_tail(g), _vol_tail(g), out)
 
 
-def project_adjoint_cone3d(g, mats, proj, out=None):
+def project_adjoint_workspace_bytes(g, batch=1):
+    """Bytes of project_adjoint_cone3d's workspace (0 for a volume that needs none)."""
+    return int(lib().ph_project_adjoint_workspace_bytes_3d(ctypes.byref(g), int(batch)))
+
+
+def project_adjoint_cone3d(g, mats, proj, out=None, ws=None):
+    """A^T of project_cone3d.  A small volume's views are taken in shares whose
+    partial sums meet in a workspace; with ``out`` and ``ws`` (a uint8 tensor of
+    project_adjoint_workspace_bytes(g, batch) bytes) the call allocates nothing,
+    and where there is no memory for one all views are taken in one share."""
     batch = _dev(proj, "input", _sino_tail(g))
-    nbytes = int(lib().ph_project_adjoint_workspace_bytes_3d(ctypes.byref(g), batch))
-    if nbytes == 0:
+    nbytes = project_adjoint_workspace_bytes(g, batch)
+    if ws is not None:
+        if not isinstance(ws, torch.Tensor) or ws.dtype != torch.uint8 or ws.device != proj.device or \
+                not ws.is_contiguous():
+            raise ValueError(f"ws must be a contiguous uint8 tensor on {proj.device}")
+    elif nbytes > 0:
+        try:
+            ws = torch.empty(nbytes, dtype=torch.uint8, device=proj.device)
+        except torch.OutOfMemoryError:
+            pass
+    if nbytes == 0 or ws is None:
         return _unary("ph_project_adjoint_cone3d", g, mats, proj, _sino_tail(g), _vol_tail(g), out)
-    # a small volume: its views are taken in shares whose partial sums meet in a workspace
-    ws = torch.empty(nbytes, dtype=torch.uint8, device=proj.device)
     return _unary("ph_project_adjoint_ws_cone3d", g, mats, proj, _sino_tail(g), _vol_tail(g), out, ws)
 
 
@@ -538,7 +554,7 @@ __all__ = [
     "project_adjoint_par2d", "project_adjoint_fan2d", "project_adjoint_cone3d", "backproject_adjoint_par2d",
     "backproject_adjoint_fan2d", "backproject_adjoint_cone3d",
     "weight_filter_2d", "weight_filter_3d", "workspace_bytes_2d", "workspace_bytes_3d", "fdk_workspace_bytes",
-    "fbp_par2d",
+    "project_adjoint_workspace_bytes", "fbp_par2d",
     "fbp_fan2d", "fdk_cone3d", "fdk_cone3d_static", "filter_response", "filter_response_equiangular", "tv", "tv_workspace_bytes",
     "tv_iterate", "mse_grad",
     "corrector_grad_3d", "corrector_grad_2d", "adam_step", "version",

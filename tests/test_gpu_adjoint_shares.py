@@ -120,3 +120,36 @@ def test_project_adjoint_long_steps(ph, ora, step):
     say(f"[A^T] step {step}")
     check(to_np(ph.project_adjoint_cone3d(g, ph.projection_matrices_3d(g), to_dev(p))), ora.project_adjoint(spec, p),
           "A^T")
+
+
+def test_project_adjoint_workspace_of_the_caller(ph, monkeypatch):
+    """With out= and ws= nothing is allocated; without memory for a workspace
+    the views are taken in one share."""
+    spec = synth.config("cone3d_crop32").with_(vol_shape=(20, 20, 20), vol_spacing=(1.0, 1.0, 1.0), det_shape=(40, 44),
+                                               det_spacing=(1.2, 1.2), n_proj=40, sid=300.0, sdd=500.0)
+    g = ph.from_spec(spec)
+    mats = ph.projection_matrices_3d(g)
+    p = torch.rand((2, 40, 40, 44), device=gc.device())
+    ref = ph.project_adjoint_cone3d(g, mats, p)
+    nbytes = ph.project_adjoint_workspace_bytes(g, 2)
+    assert nbytes > 0
+    out, ws = torch.empty_like(ref), torch.empty(nbytes, dtype=torch.uint8, device=p.device)
+    before = torch.cuda.memory_stats()["allocation.all.allocated"]
+    assert ph.project_adjoint_cone3d(g, mats, p, out, ws) is out
+    assert torch.cuda.memory_stats()["allocation.all.allocated"] == before
+    assert (out == ref).all()
+    with pytest.raises(ph._lib.PyroHipError):
+        ph.project_adjoint_cone3d(g, mats, p, out, ws[:nbytes - 1])
+    for bad in (ws.float(), ws.cpu(), ws[::2]):
+        with pytest.raises(ValueError):
+            ph.project_adjoint_cone3d(g, mats, p, out, bad)
+    empty = torch.empty
+
+    def none_left(*shape, **kw):
+        if kw.get("dtype") == torch.uint8:
+            raise torch.OutOfMemoryError("no memory")
+        return empty(*shape, **kw)
+
+    monkeypatch.setattr(torch, "empty", none_left)
+    one = ph.project_adjoint_cone3d(g, mats, p)
+    assert (one - ref).abs().max() <= 2.0 ** -23 * ref.abs().max()
