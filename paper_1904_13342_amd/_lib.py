@@ -55,7 +55,7 @@ class TvParams(ctypes.Structure):
 
 
 _P = ctypes.c_void_p
-_FP = ctypes.c_void_p   # host float arrays: an address, or a ctypes pointer to floats
+_FP = ctypes.POINTER(ctypes.c_float)
 _I = ctypes.c_int
 _SZ = ctypes.c_size_t
 _G2 = ctypes.POINTER(Geom2D)

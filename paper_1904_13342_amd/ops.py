@@ -80,7 +80,8 @@ def from_spec(spec):
 
 
 def _fptr(a):
-    return a.ctypes.data
+    """The first float of an array, which ctypes passes by reference (the caller keeps the array)."""
+    return ctypes.c_float.from_address(a.ctypes.data)
 
 
 def ray_vectors_2d(g):

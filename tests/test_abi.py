@@ -323,3 +323,12 @@ def test_binding_checks_tensor_shapes(ph):
         ph.project_par2d(g, rv, torch.zeros(64, 64))          # host tensor
     with pytest.raises(ValueError):
         ph.project_par2d(g, rv[:10], torch.zeros(64, 64))     # wrong trajectory length
+
+
+def test_host_arrays_are_typed(ph, L):
+    """A host array of anything but floats is refused before the call."""
+    spec = synth.config("par2d_64")
+    g = ph.from_spec(spec)
+    for bad in ((ctypes.c_double * (2 * spec.n_proj))(), (ctypes.c_int * (2 * spec.n_proj))(), 4096):
+        with pytest.raises(ctypes.ArgumentError):
+            L.ph_project_par2d(ctypes.byref(g), bad, None, None, 1, 0, None)
