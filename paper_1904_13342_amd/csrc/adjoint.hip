@@ -63,7 +63,7 @@ __device__ __forceinline__ float hat(float d)
 template <typename T, typename TI, bool FAN, int V, int NB>
 __global__ void __launch_bounds__(1024) fpT2d_kernel(Geom2D g, const float2 *__restrict__ views,
                                                      const TI *__restrict__ sino, T *__restrict__ img, int ntx,
-                                                     int nty, int batch)
+                                                     int nty, int batch, unsigned tile0)
 {
     constexpr int L = 64 / V;   // lanes (and rays) per view
     extern __shared__ __align__(16) char at_lds[];   // 64 rays per wave
@@ -71,7 +71,7 @@ __global__ void __launch_bounds__(1024) fpT2d_kernel(Geom2D g, const float2 *__r
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int waves = blockDim.x >> 6;
     TileRay<NB> *rays = s_rays + wave * 64;
-    const unsigned tile = blockIdx.x;
+    const unsigned tile = tile0 + blockIdx.x;
     const int tx = (int)(tile % (unsigned)ntx), ty = (int)((tile / (unsigned)ntx) % (unsigned)nty);
     const int b0 = NB * (int)(tile / ((unsigned)ntx * (unsigned)nty));
     const int ix = tx * 8 + (lane & 7), iy = ty * 8 + (lane >> 3);
@@ -246,7 +246,8 @@ template <typename T, typename TI>
 __global__ void __launch_bounds__(AT_T, 4) fpT_cone_kernel(Geom3D g, const ConeFPView *__restrict__ fviews,
                                                         const ConeBPView *__restrict__ bviews,
                                                         const TI *__restrict__ proj, T *__restrict__ vol,
-                                                        double *__restrict__ part, int nbx, int nby, int nbz)
+                                                        double *__restrict__ part, int nbx, int nby, int nbz,
+                                                        unsigned brick0)
 {
     __shared__ int acc[AT_CELLS];
     __shared__ float4 s_ra[AT_RAYS];   // biased anchor X, Y, Z and the ray's value
@@ -258,8 +259,9 @@ __global__ void __launch_bounds__(AT_T, 4) fpT_cone_kernel(Geom3D g, const ConeF
     __shared__ int s_nhit;
     __shared__ int s_next;   // next 64-ray task of the walk
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int bxi = (int)(blockIdx.x % (unsigned)nbx), byi = (int)((blockIdx.x / (unsigned)nbx) % (unsigned)nby);
-    const int bzb = (int)(blockIdx.x / (unsigned)(nbx * nby));
+    const unsigned brick = brick0 + blockIdx.x;
+    const int bxi = (int)(brick % (unsigned)nbx), byi = (int)((brick / (unsigned)nbx) % (unsigned)nby);
+    const int bzb = (int)(brick / (unsigned)(nbx * nby));
     const int bzi = bzb % nbz, b = bzb / nbz;
     const int x0 = bxi * AT_B, y0 = byi * AT_B, z0 = bzi * AT_B;
     for (int n = tid; n < AT_CELLS; n += AT_T)
@@ -638,12 +640,14 @@ __device__ __forceinline__ void strip_walk(const Geom2D &g, float2 c, const TI *
 
 template <typename TI, bool FAN>
 __global__ void __launch_bounds__(1024) bpT2d_kernel(Geom2D g, const float2 *__restrict__ views,
-                                                     const TI *__restrict__ img, float *__restrict__ sino, int groups)
+                                                     const TI *__restrict__ img, float *__restrict__ sino, int groups,
+                                                     unsigned block0)
 {
     extern __shared__ float2 part[];   // one entry per thread, for more than one wave
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, waves = blockDim.x >> 6;
-    const int grp = (int)(blockIdx.x % (unsigned)groups);
-    const long kb = blockIdx.x / (unsigned)groups;   // view of an item
+    const unsigned block = block0 + blockIdx.x;
+    const int grp = (int)(block % (unsigned)groups);
+    const long kb = block / (unsigned)groups;   // view of an item
     const int k = (int)(kb % g.n_proj), b = (int)(kb / g.n_proj);
     const int j = grp * 63 - 1 + lane;   // this lane's strip
     const float2 c = views[k];
@@ -736,14 +740,15 @@ constexpr size_t RUN_LDS = 65536;    // LDS of a workgroup, at most
 template <typename TI, bool FAN, int P, int NB>
 __global__ void __launch_bounds__(1024) bpT2d_run_kernel(Geom2D g, const float2 *__restrict__ views,
                                                          const TI *__restrict__ img, float *__restrict__ sino,
-                                                         int batch)
+                                                         int batch, unsigned block0)
 {
     typedef float Pairs __attribute__((ext_vector_type(2 * NB)));   // (w0, w1) of each item
     extern __shared__ __align__(32) char run_lds[];   // g.nu + 1 strips (-1 .. nu - 1) per wave
     Pairs *part = (Pairs *)run_lds;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int waves = blockDim.x >> 6, strips = g.nu + 1;
-    const int k = (int)(blockIdx.x % (unsigned)g.n_proj), b0 = NB * (int)(blockIdx.x / (unsigned)g.n_proj);
+    const unsigned block = block0 + blockIdx.x;
+    const int k = (int)(block % (unsigned)g.n_proj), b0 = NB * (int)(block / (unsigned)g.n_proj);
     const float2 c = views[k];
     const size_t pixels = (size_t)g.nx * g.ny;
     Pairs *own = part + wave * strips;
@@ -864,8 +869,6 @@ hipError_t fpT2d_n(const Geom2D &g, const float2 *views, const void *sino, void 
 {
     const int ntx = (g.nx + 7) / 8, nty = (g.ny + 7) / 8;
     const long tiles = (long)ntx * nty * ((batch + NB - 1) / NB);
-    if (tiles > 0x7fffffffL)
-        return hipErrorInvalidConfiguration;
     // waves per tile: about 32 on every CU in all, at least V views each (a
     // small image's time is one wave's chain of views: 256^2 with 30 views, 15.0
     // us for four waves of eight views, 13.2 us for eight of four)
@@ -873,10 +876,11 @@ hipError_t fpT2d_n(const Geom2D &g, const float2 *views, const void *sino, void 
     const long most = (g.n_proj + V - 1) / V;
     waves = waves < most ? waves : most;
     waves = waves < 16 ? waves : 16;
-    hipLaunchKernelGGL((fpT2d_kernel<T, TI, FAN, V, NB>), dim3((unsigned)tiles), dim3((unsigned)(64 * waves)),
-                       (size_t)(64 * waves) * sizeof(TileRay<NB>), s, g, views, (const TI *)sino, (T *)img, ntx, nty,
-                       batch);
-    return hipGetLastError();
+    const int threads = (int)(64 * waves);
+    return launch_in_pieces(tiles, threads, [&](unsigned first, dim3 grid) {
+        hipLaunchKernelGGL((fpT2d_kernel<T, TI, FAN, V, NB>), grid, dim3(threads), threads * sizeof(TileRay<NB>), s, g,
+                           views, (const TI *)sino, (T *)img, ntx, nty, batch, first);
+    });
 }
 
 template <typename T, typename TI, bool FAN, int V>
@@ -923,11 +927,12 @@ hipError_t fpT_cone(const Geom3D &g, const ConeFPView *fviews, const ConeBPView 
 {
     const int nbx = (g.nx + AT_B - 1) / AT_B, nby = (g.ny + AT_B - 1) / AT_B, nbz = (g.nz + AT_B - 1) / AT_B;
     const long blocks = (long)nbx * nby * nbz * batch;
-    if (blocks > 0x7fffffffL)
-        return hipErrorInvalidConfiguration;
-    hipLaunchKernelGGL((fpT_cone_kernel<T, T>), dim3((unsigned)blocks, (unsigned)shares), dim3(AT_T), 0, s, g, fviews,
-                       bviews, (const T *)proj, (T *)vol, shares > 1 ? part : nullptr, nbx, nby, nbz);
-    hipError_t e = hipGetLastError();
+    // (shares only where there are few bricks: one piece)
+    const hipError_t e = launch_in_pieces(blocks, AT_T, [&](unsigned first, dim3 grid) {
+        grid.y = (unsigned)shares;
+        hipLaunchKernelGGL((fpT_cone_kernel<T, T>), grid, dim3(AT_T), 0, s, g, fviews, bviews, (const T *)proj, (T *)vol,
+                           shares > 1 ? part : nullptr, nbx, nby, nbz, first);
+    });
     if (e != hipSuccess || shares == 1)
         return e;
     hipLaunchKernelGGL(fpT_cone_sum_kernel<T>, dim3((unsigned)blocks * (AT_B * AT_B * AT_B / 256)), dim3(256), 0, s, g,
@@ -1018,15 +1023,16 @@ hipError_t bpT2d_run(bool fan, const Geom2D &g, const float2 *views, const void 
     int waves = 1;
     while (waves < 16 && groups * waves < 16384 && 2 * waves * bins <= RUN_LDS)
         waves *= 2;
-    const dim3 grid((unsigned)groups), block(64 * waves);
+    const dim3 block(64 * waves);
     const size_t lds = (size_t)waves * bins;
-    if (fan)
-        hipLaunchKernelGGL((bpT2d_run_kernel<TI, true, P, NB>), grid, block, lds, stream, g, views, (const TI *)img,
-                           sino, batch);
-    else
-        hipLaunchKernelGGL((bpT2d_run_kernel<TI, false, P, NB>), grid, block, lds, stream, g, views, (const TI *)img,
-                           sino, batch);
-    return hipGetLastError();
+    return launch_in_pieces(groups, 64 * waves, [&](unsigned first, dim3 grid) {
+        if (fan)
+            hipLaunchKernelGGL((bpT2d_run_kernel<TI, true, P, NB>), grid, block, lds, stream, g, views, (const TI *)img,
+                               sino, batch, first);
+        else
+            hipLaunchKernelGGL((bpT2d_run_kernel<TI, false, P, NB>), grid, block, lds, stream, g, views,
+                               (const TI *)img, sino, batch, first);
+    });
 }
 
 template <typename TI, int P>
@@ -1061,7 +1067,7 @@ hipError_t bpT2d(bool fan, const Geom2D &g, const float2 *views, const void *img
     // views of 1020 bins, four waves to a workgroup: 382 and 452).
     const int nb = batch > 1 && 16 * bins <= RUN_LDS && (long)g.n_proj * ((batch + 1) / 2) >= 512 ? 2 : 1;
     const long pixels = (long)g.nx * g.ny, least = pixels <= 128 * 128 ? 1 : pixels <= 256 * 256 ? 96 : 256;
-    if (P > 0 && bins <= RUN_LDS && items <= 0x7fffffffL && items >= least) {
+    if (P > 0 && bins <= RUN_LDS && items >= least) {
         switch (P) {
         case 1: return bpT2d_run_p<TI, 1>(nb, fan, g, views, img, sino, batch, stream);
         case 2: return bpT2d_run_p<TI, 2>(nb, fan, g, views, img, sino, batch, stream);
@@ -1071,22 +1077,21 @@ hipError_t bpT2d(bool fan, const Geom2D &g, const float2 *views, const void *img
     }
     const int groups = (g.nu + 62) / 63;
     const long blocks = (long)groups * g.n_proj * batch;
-    if (blocks > 0x7fffffffL)
-        return hipErrorInvalidConfiguration;
     // waves per workgroup: enough for about 16 waves on every CU, at least
     // eight rows each
     int waves = 1;
     while (waves < 16 && blocks * waves < 4096 && waves * 16 <= (g.nx < g.ny ? g.nx : g.ny))
         waves *= 2;
-    const dim3 grid((unsigned)blocks), block(64 * waves);
+    const dim3 block(64 * waves);
     const size_t lds = waves > 1 ? 64 * waves * sizeof(float2) : 0;
-    if (fan)
-        hipLaunchKernelGGL((bpT2d_kernel<TI, true>), grid, block, lds, stream, g, views, (const TI *)img, sino,
-                           groups);
-    else
-        hipLaunchKernelGGL((bpT2d_kernel<TI, false>), grid, block, lds, stream, g, views, (const TI *)img, sino,
-                           groups);
-    return hipGetLastError();
+    return launch_in_pieces(blocks, 64 * waves, [&](unsigned first, dim3 grid) {
+        if (fan)
+            hipLaunchKernelGGL((bpT2d_kernel<TI, true>), grid, block, lds, stream, g, views, (const TI *)img, sino,
+                               groups, first);
+        else
+            hipLaunchKernelGGL((bpT2d_kernel<TI, false>), grid, block, lds, stream, g, views, (const TI *)img, sino,
+                               groups, first);
+    });
 }
 
 hipError_t launch_backproject_adjoint_2d(int in_dtype, bool fan, const Geom2D &g, const float2 *views,

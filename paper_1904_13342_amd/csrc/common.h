@@ -98,6 +98,24 @@ struct ConeFPView {
 // ------------------------------------------------------------------ launchers
 // Each returns hipSuccess or the launch error.  `dtype`: 0 f32, 1 f16, 2 bf16.
 
+// A launch holds fewer than 2^32 threads.  Launches `blocks` workgroups of
+// `threads` (fewer than 2^32 of them, or refused) in as many pieces as that
+// takes: launch(first, n) for the n from workgroup `first` on.
+template <typename Launch>
+hipError_t launch_in_pieces(long blocks, int threads, Launch launch)
+{
+    if (blocks > 0xffffffffL)
+        return hipErrorInvalidConfiguration;
+    const long most = 0xffffffffL / threads;
+    for (long first = 0; first < blocks; first += most) {
+        launch((unsigned)first, dim3((unsigned)(blocks - first < most ? blocks - first : most)));
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess)
+            return e;
+    }
+    return hipSuccess;
+}
+
 hipError_t launch_project_2d(int dtype, bool fan, const Geom2D &g, const float2 *views, const void *img, void *sino,
                              int batch, hipStream_t stream);
 hipError_t launch_backproject_2d(int dtype, bool fan, const Geom2D &g, const float2 *views, const void *sino,

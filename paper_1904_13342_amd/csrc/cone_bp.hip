@@ -320,12 +320,13 @@ template <typename T, typename TI, bool AXIAL>
 __global__ void __launch_bounds__(1024) bp_cone_wave_kernel(Geom3D g, const ConeBPView *__restrict__ views,
                                                             const ConeBPView64 *__restrict__ views64,
                                                             const TI *__restrict__ proj, T *__restrict__ vol, int ntx,
-                                                            int nty, int ntz, int nz_seg, int accumulate)
+                                                            int nty, int ntz, int nz_seg, int accumulate,
+                                                            unsigned tile0)
 {
     extern __shared__ float part[];   // WV_NZ per thread, for more than one wave
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int waves = blockDim.x >> 6;
-    const unsigned lin = blockIdx.x;
+    const unsigned lin = tile0 + blockIdx.x;
     const int tx = (int)(lin % (unsigned)ntx), ty = (int)((lin / (unsigned)ntx) % (unsigned)nty);
     const int tzb = (int)(lin / ((unsigned)ntx * (unsigned)nty));
     const int z0 = tzb % ntz * WV_NZ, b = tzb / ntz;
@@ -770,21 +771,21 @@ hipError_t bp_cone(const Geom3D &g, const ConeBPView *views, const ConeBPView64 
                             : bp_cone_nz<T, TI, 16>(g, views, proj, vol, batch, acc, s);
     const int ntx = (g.nx + 7) / 8, nty = (g.ny + 7) / 8, ntz = (g.nz + WV_NZ - 1) / WV_NZ;
     const long tiles = (long)ntx * nty * ntz * batch;
-    if (tiles > 0x7fffffffL)
-        return hipErrorInvalidConfiguration;
     // at least 64 waves per CU in all, four views each
     int waves = 1;
     while (waves < 16 && tiles * waves < 16384 && 4 * waves <= g.n_proj)
         waves *= 2;
-    const dim3 grid((unsigned)tiles), block(64 * waves);
+    const dim3 block(64 * waves);
     const size_t lds = waves > 1 ? (size_t)WV_NZ * 64 * waves * sizeof(float) : 0;
-    if (axial)
-        hipLaunchKernelGGL((bp_cone_wave_kernel<T, TI, true>), grid, block, lds, s, g, views,
-                           (const ConeBPView64 *)nullptr, (const TI *)proj, (T *)vol, ntx, nty, ntz, nz_seg, acc);
-    else
-        hipLaunchKernelGGL((bp_cone_wave_kernel<T, TI, false>), grid, block, lds, s, g, views, views64,
-                           (const TI *)proj, (T *)vol, ntx, nty, ntz, nz_seg, acc);
-    return hipGetLastError();
+    return launch_in_pieces(tiles, 64 * waves, [&](unsigned first, dim3 grid) {
+        if (axial)
+            hipLaunchKernelGGL((bp_cone_wave_kernel<T, TI, true>), grid, block, lds, s, g, views,
+                               (const ConeBPView64 *)nullptr, (const TI *)proj, (T *)vol, ntx, nty, ntz, nz_seg, acc,
+                               first);
+        else
+            hipLaunchKernelGGL((bp_cone_wave_kernel<T, TI, false>), grid, block, lds, s, g, views, views64,
+                               (const TI *)proj, (T *)vol, ntx, nty, ntz, nz_seg, acc, first);
+    });
 }
 
 }  // namespace

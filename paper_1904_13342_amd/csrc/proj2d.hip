@@ -52,16 +52,17 @@ constexpr int B_UNROLL = 4;   // views per wave of B
 // a pixel and for steps longer than one; the rest goes in slabs, below.
 template <typename T, bool FAN, int S>
 __global__ void __launch_bounds__(256) fp2d_kernel(Geom2D g, const float2 *__restrict__ views,
-                                                   const T *__restrict__ img, T *__restrict__ sino, int n_rays,
-                                                   int blocks)
+                                                   const T *__restrict__ img, T *__restrict__ sino, unsigned n_rays,
+                                                   unsigned blocks, unsigned block0)
 {
-    const int b = (int)(blockIdx.x / (unsigned)blocks);
-    const long t = (long)(blockIdx.x % (unsigned)blocks) * 256 + threadIdx.x;
-    const int r = (int)(t / S);
+    const unsigned block = block0 + blockIdx.x;
+    const int b = (int)(block / blocks);
+    const long t = (long)(block % blocks) * 256 + threadIdx.x;
+    const unsigned r = (unsigned)(t / S);
     const int s = (int)(t % S);
     if (r >= n_rays)
         return;   // whole rays only: the S lanes of a ray leave together
-    const int j = r % g.nu, k = r / g.nu;
+    const int j = (int)(r % (unsigned)g.nu), k = (int)(r / (unsigned)g.nu);
     const T *im = img + (size_t)b * g.nx * g.ny, *im1 = im + g.nx;
     float X0, Y0, eX, eY;
     make_ray_2d<FAN>(g, views[k], j, X0, Y0, eX, eY);
@@ -312,13 +313,15 @@ __device__ __forceinline__ float slab_walk_2d(const Geom2D &g, const T *im, floa
 
 template <typename T, bool FAN, int SW>
 __global__ void __launch_bounds__(1024) fp2d_slab_kernel(Geom2D g, const float2 *__restrict__ views,
-                                                         const T *__restrict__ img, T *__restrict__ sino, int groups)
+                                                         const T *__restrict__ img, T *__restrict__ sino, int groups,
+                                                         unsigned block0)
 {
     extern __shared__ float slabs[];   // SL_P * SW words per wave
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int waves = blockDim.x >> 6;
-    const int grp = (int)(blockIdx.x % (unsigned)groups);
-    const long kb_ = blockIdx.x / (unsigned)groups;
+    const unsigned block = block0 + blockIdx.x;
+    const int grp = (int)(block % (unsigned)groups);
+    const long kb_ = block / (unsigned)groups;
     const int k = (int)(kb_ % g.n_proj), b = (int)(kb_ / g.n_proj);
     const int j = grp * 64 + lane, last = min(63, g.nu - 1 - grp * 64);
     const T *im = img + (size_t)b * g.nx * g.ny;
@@ -377,12 +380,13 @@ __global__ void __launch_bounds__(1024) fp2d_slab_kernel(Geom2D g, const float2 
 // CU), and for bins too fine to stage, below.
 template <typename T, typename TI, bool FAN>
 __global__ void __launch_bounds__(1024) bp2d_kernel(Geom2D g, const float2 *__restrict__ views,
-                                                    const TI *__restrict__ sino, T *__restrict__ img, int ntx, int nty)
+                                                    const TI *__restrict__ sino, T *__restrict__ img, int ntx, int nty,
+                                                    unsigned tile0)
 {
     extern __shared__ float part[];   // one entry per thread, for more than one wave
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int waves = blockDim.x >> 6;
-    const unsigned tile = blockIdx.x;
+    const unsigned tile = tile0 + blockIdx.x;
     const int tx = (int)(tile % (unsigned)ntx), ty = (int)((tile / (unsigned)ntx) % (unsigned)nty);
     const int b = (int)(tile / ((unsigned)ntx * (unsigned)nty));
     const int ix = tx * 8 + (lane & 7), iy = ty * 8 + (lane >> 3);
@@ -454,7 +458,7 @@ constexpr int SB_BINS = 512;   // views times bins of a chunk
 template <typename T, typename TI, bool FAN, int NB, int W>
 __global__ void __launch_bounds__(1024) bp2d_seg_kernel(Geom2D g, const float2 *__restrict__ views,
                                                         const TI *__restrict__ sino, T *__restrict__ img, int ntx,
-                                                        int nty, int batch)
+                                                        int nty, int batch, unsigned tile0)
 {
     typedef float Items __attribute__((ext_vector_type(NB)));
     constexpr int LOADS = SB_BINS / 64, V = SB_BINS / W;   // V views to a chunk, at most one lane to a corner
@@ -462,7 +466,7 @@ __global__ void __launch_bounds__(1024) bp2d_seg_kernel(Geom2D g, const float2 *
     extern __shared__ __align__(16) char seg_lds[];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int waves = blockDim.x >> 6;
-    const unsigned tile = blockIdx.x;
+    const unsigned tile = tile0 + blockIdx.x;
     const int x0 = 16 * (int)(tile % (unsigned)ntx), y0 = 16 * (int)((tile / (unsigned)ntx) % (unsigned)nty);
     const int b0 = NB * (int)(tile / ((unsigned)ntx * (unsigned)nty));
     const size_t item = (size_t)g.n_proj * g.nu;
@@ -614,11 +618,12 @@ template <typename T, bool FAN, int S>
 hipError_t fp2d_s(const Geom2D &g, const float2 *views, const void *img, void *sino, int batch, hipStream_t s)
 {
     const long n_rays = (long)g.nu * g.n_proj, blocks = (n_rays * S + 255) / 256;   // of one item
-    if (n_rays > 0x7fffffffL || blocks * batch > 0x7fffffffL)
+    if (n_rays > 0xffffffffL)
         return hipErrorInvalidConfiguration;
-    hipLaunchKernelGGL((fp2d_kernel<T, FAN, S>), dim3((unsigned)(blocks * batch)), dim3(256), 0, s, g, views,
-                       (const T *)img, (T *)sino, (int)n_rays, (int)blocks);
-    return hipGetLastError();
+    return launch_in_pieces(blocks * batch, 256, [&](unsigned first, dim3 grid) {
+        hipLaunchKernelGGL((fp2d_kernel<T, FAN, S>), grid, dim3(256), 0, s, g, views, (const T *)img, (T *)sino,
+                           (unsigned)n_rays, (unsigned)blocks, first);
+    });
 }
 
 template <typename T, bool FAN, int SW>
@@ -626,8 +631,6 @@ hipError_t fp2d_slab(const Geom2D &g, const float2 *views, const void *img, void
 {
     const int groups = (g.nu + 63) / 64;
     const long blocks = (long)groups * g.n_proj * batch;
-    if (blocks > 0x7fffffffL)
-        return hipErrorInvalidConfiguration;
     // waves per 64 rays: about 64 on every CU in all (512^2, 360 fan views: 283,
     // 192, 161 and 160 us for 4096, 8192, 16384 and 32768 waves), at least
     // three slabs each, and two workgroups or more to a CU's LDS (the widest
@@ -638,8 +641,10 @@ hipError_t fp2d_slab(const Geom2D &g, const float2 *views, const void *img, void
     while (waves < 16 && blocks * waves < 16384 && 2 * waves * 3 * SL_D <= (g.nx < g.ny ? g.nx : g.ny) &&
            2 * waves * slab <= SL_LDS)
         waves *= 2;
-    hipLaunchKernelGGL((fp2d_slab_kernel<T, FAN, SW>), dim3((unsigned)blocks), dim3(64 * waves), waves * slab, s, g, views, (const T *)img, (T *)sino, groups);
-    return hipGetLastError();
+    return launch_in_pieces(blocks, 64 * waves, [&](unsigned first, dim3 grid) {
+        hipLaunchKernelGGL((fp2d_slab_kernel<T, FAN, SW>), grid, dim3(64 * waves), waves * slab, s, g, views,
+                           (const T *)img, (T *)sino, groups, first);
+    });
 }
 
 template <typename T, bool FAN>
@@ -686,18 +691,17 @@ hipError_t bp2d_seg(const Geom2D &g, const float2 *views, const void *sino, void
 {
     const int ntx = (g.nx + 15) / 16, nty = (g.ny + 15) / 16;
     const long tiles = (long)ntx * nty * ((batch + NB - 1) / NB);
-    if (tiles > 0x7fffffffL)
-        return hipErrorInvalidConfiguration;
     // waves per tile: about 32 on every CU in all (8 x 256^2, 360 parallel views
     // one item at a time, in the step of learning the filter: 438, 416 and 418
     // us for 4096, 8192 and 16384), a chunk of views each
     int waves = 1;
     while (waves < 8 && tiles * waves < 8192 && (2 * waves - 1) * (SB_BINS / W) < g.n_proj)
         waves *= 2;
-    hipLaunchKernelGGL((bp2d_seg_kernel<T, TI, FAN, NB, W>), dim3((unsigned)tiles), dim3(64 * waves),
-                       (size_t)waves * SB_BINS * NB * sizeof(float), s, g, views, (const TI *)sino, (T *)img, ntx, nty,
-                       batch);
-    return hipGetLastError();
+    return launch_in_pieces(tiles, 64 * waves, [&](unsigned first, dim3 grid) {
+        hipLaunchKernelGGL((bp2d_seg_kernel<T, TI, FAN, NB, W>), grid, dim3(64 * waves),
+                           (size_t)waves * SB_BINS * NB * sizeof(float), s, g, views, (const TI *)sino, (T *)img, ntx,
+                           nty, batch, first);
+    });
 }
 
 template <typename T, typename TI, bool FAN, int NB>
@@ -738,16 +742,15 @@ hipError_t bp2d_f(const Geom2D &g, const float2 *views, const void *sino, void *
     }
     const int ntx = (g.nx + 7) / 8, nty = (g.ny + 7) / 8;
     const long tiles = (long)ntx * nty * batch;
-    if (tiles > 0x7fffffffL)
-        return hipErrorInvalidConfiguration;
     // waves per tile: at least 64 per CU in all (512^2, 360 fan views with the
     // filter: 107, 89, 86 and 89 us for 16, 32, 64 and 128), four views each
     int waves = 1;
     while (waves < 16 && tiles * waves < 16384 && 8 * waves <= g.n_proj)
         waves *= 2;
-    hipLaunchKernelGGL((bp2d_kernel<T, TI, FAN>), dim3((unsigned)tiles), dim3(64 * waves),
-                       waves > 1 ? 64 * waves * sizeof(float) : 0, s, g, views, (const TI *)sino, (T *)img, ntx, nty);
-    return hipGetLastError();
+    return launch_in_pieces(tiles, 64 * waves, [&](unsigned first, dim3 grid) {
+        hipLaunchKernelGGL((bp2d_kernel<T, TI, FAN>), grid, dim3(64 * waves), waves > 1 ? 64 * waves * sizeof(float) : 0,
+                           s, g, views, (const TI *)sino, (T *)img, ntx, nty, first);
+    });
 }
 
 template <typename T, typename TI>

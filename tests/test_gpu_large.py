@@ -111,3 +111,55 @@ def test_half_storage_512(ph, ora, coarse, dtype):
     assert rec.dtype == dtype
     check(to_np(rec[fdk_slices]), ora.backproject(SPEC, q, slices=fdk_slices)[fdk_slices], f"FDK {tag}", tol=tol,
           elem=elem)
+
+
+# ---- more than 2^32 threads, in launches of fewer
+
+def _spots(n):
+    return [0, 1, n // 3, n // 2, n - 2, n - 1]
+
+
+def test_backproject_2d_of_many_pixels(ph):
+    """4.3e9 pixels in tiles of 8 x 8: bins too fine to be staged, 1032 items."""
+    n, items, nu = 2048, 1032, 64
+    say(f"[B 2D] {items} images of {n}^2, f16")
+    g = ph.geom2d((n, n), (1.0, 1.0), nu, 0.05, 1, math.pi, sid=3000.0, sdd=4000.0)
+    rv = ph.ray_vectors_2d(g)
+    p = torch.rand((items, 1, nu), device=gc.device(), generator=torch.Generator(gc.device()).manual_seed(1)).half()
+    out = ph.backproject_fan2d(g, rv, p)
+    assert out.abs().max() > 0
+    for k in _spots(items):
+        assert (out[k] == ph.backproject_fan2d(g, rv, p[k].contiguous())).all(), k
+
+
+def test_project_2d_of_many_rays(ph):
+    """2.2e9 rays in waves of 64 bins, every second part empty."""
+    items = (1 << 25) + 3
+    say(f"[A 2D] {items} images of 4^2, f16")
+    g = ph.geom2d((4, 4), (1.0, 1.0), 65, 0.1, 1, math.pi)
+    rv = ph.ray_vectors_2d(g)
+    f = torch.rand((items, 4, 4), device=gc.device(), generator=torch.Generator(gc.device()).manual_seed(2),
+                   dtype=torch.float16)
+    out = ph.project_par2d(g, rv, f)
+    for k in _spots(items) + [1 << 24, (1 << 25) - 1, 1 << 25]:
+        # the same kernel takes a run of items around it
+        a = min(max(k - 300, 0), items - 600)
+        assert (out[a:a + 600] == ph.project_par2d(g, rv, f[a:a + 600].contiguous())).all(), k
+
+
+def test_backproject_general_of_many_voxels(ph):
+    """1.7e10 voxels (34 GB in f16) by single waves: a tilted orbit."""
+    vol, items = (125, 256, 256), 2100
+    spec = synth.config("cone3d_crop32").with_(vol_shape=vol, vol_spacing=(1.0, 1.0, 1.0), det_shape=(40, 50),
+                                               det_spacing=(10.0, 10.0), n_proj=1, sid=700.0, sdd=1100.0)
+    g = ph.from_spec(spec)
+    mats = np.array(ph.projection_matrices_3d(g), dtype=np.float64).reshape(1, 3, 4)
+    c, s = math.cos(0.1), math.sin(0.1)
+    mats[0, :, :3] = mats[0, :, :3] @ np.array([[1, 0, 0], [0, c, -s], [0, s, c]])
+    say(f"[B general] {items} volumes of {vol}, f16")
+    p = torch.rand((items, 1, 40, 50), device=gc.device(), generator=torch.Generator(gc.device()).manual_seed(3)).half()
+    out = ph.backproject_cone3d(g, mats.astype(np.float32), p)
+    for k in _spots(items):
+        one = ph.backproject_cone3d(g, mats.astype(np.float32), p[k].contiguous())
+        assert one.abs().max() > 0
+        assert (out[k] == one).all(), k
