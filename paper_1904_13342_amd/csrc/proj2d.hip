@@ -719,12 +719,14 @@ hipError_t bp2d_f(const Geom2D &g, const float2 *views, const void *sino, void *
     // from the near side of the image, fit 64 with the margins.  Items of a
     // batch go together as long as 256 workgroups are left (180 fan views of
     // 128^2: 20, 22 us for one and two together of 2 items, with the filter).
-    // Parallel views gain from the staging alone (512^2, 360 views, with the
-    // filter: 74 and 60 us), fan views, bound by the arithmetic of their
-    // coordinates, only where two items or more share it (512^2, 360 arc views
-    // of one, two and five items: 103, 189 and 418 us from memory, 118, 123
-    // and 247 staged; since the coordinate's forms are told apart 96 for one
-    // and 114 for two).
+    // Parallel views gain from the staging alone, once there are tiles for every
+    // CU and work to outweigh it (one item, us from memory and staged: 64^2, 90
+    // views 4.4 and 9.4, 168^2, 300 views 10 and 13, 256^2, 30, 90 and 180 views
+    // 4.6 and 6.0, 9.2 and 9.6, 12.1 and 9.9, 320^2, 90 views 13.9 and 10.5, 512^2,
+    // 30 and 300 views 9.5 and 6.7, 46.7 and 31.2); fan views, bound by the
+    // arithmetic of their coordinates, only where two items or more share it
+    // (256^2, 180 flat views of one, two and five items: 16, 30 and 63 us from
+    // memory, 20 and 35 for two and five staged).
     const float wx = g.nx * g.sx, wy = g.ny * g.sy, near = g.sid - 0.5f * sqrtf(wx * wx + wy * wy);
     const float diag = 15.0f * sqrtf(g.sx * g.sx + g.sy * g.sy);
     const float span = !FAN ? diag * g.ru : near > 0.0f ? diag * g.ru / near : 3.0e38f;
@@ -732,7 +734,8 @@ hipError_t bp2d_f(const Geom2D &g, const float2 *views, const void *sino, void *
     int nb = 1;
     while (nb < 4 && nb < batch && pieces * ((batch + 2 * nb - 1) / (2 * nb)) >= 256)
         nb *= 2;
-    if (span <= 60.0f) {
+    const long work = pieces * batch;   // tiles
+    if (span <= 60.0f && (FAN || (work >= 256 && work * g.n_proj >= 30000))) {
         if (nb == 4)
             return bp2d_seg_w<T, TI, FAN, 4>(span, g, views, sino, img, batch, s);
         if (nb == 2)

@@ -68,3 +68,37 @@ def test_transposes_2d_of_zeros(ph, beam, detector):
         us = [_us(lambda: op(g, rv, x)) for x in (dense, zero, one)]
         say(f"[cost] {name} {beam} {detector}: dense, zeros, one value {us}")
         assert max(us[1:]) < 0.7 * us[0]
+
+
+def _device_us(call):
+    """Microseconds of a call on the device: twenty in a captured graph."""
+    call()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        for _ in range(20):
+            call()
+    graph.replay()
+    torch.cuda.synchronize()
+    best = math.inf
+    for _ in range(5):
+        t = time.perf_counter()
+        graph.replay()
+        torch.cuda.synchronize()
+        best = min(best, (time.perf_counter() - t) / 20)
+    return 1e6 * best
+
+
+@pytest.mark.parametrize("n", [64, 128])
+def test_backproject_2d_small_parallel(ph, n):
+    """A small parallel item costs no more than a fan of the same size, whose
+    coordinates are the dearer ones: it is not staged by a few workgroups."""
+    us = {}
+    for beam, src in (("par", {}), ("fan", dict(sid=750.0, sdd=1200.0))):
+        g = ph.geom2d((n, n), (1.0, 1.0), 2 * n, 1.0, 360, 360 * DEG, **src)
+        rv = ph.ray_vectors_2d(g)
+        p, out = torch.rand((360, 2 * n), device=gc.device()), torch.empty((n, n), device=gc.device())
+        op = getattr(ph, f"backproject_{beam}2d")
+        us[beam] = _device_us(lambda: op(g, rv, p, out))
+    say(f"[cost] B {n}^2, 360 views: {us}")
+    assert us["par"] < 1.3 * us["fan"]

@@ -144,3 +144,16 @@ def test_project_2d_wide_slabs(ph, ora, nu, du, views):
     f = as_f32(np.random.default_rng(12).uniform(0.5, 1.5, spec.vol_shape))
     say(f"[A 2D] {nu} bins of {du}, {views} views")
     check(to_np(ph.project_par2d(g, ph.ray_vectors_2d(g), to_dev(f))), ora.project(spec, f), "A", tol=2e-5)
+
+
+@pytest.mark.parametrize("du,nu", [(1.0, 380), (0.45, 860), (0.3, 1250)])
+def test_backproject_2d_one_item_staged(ph, ora, du, nu):
+    """One parallel item with enough tiles and views to be staged: 32 and 64
+    bins to a view, and more than fit, tiles and chunks of views with
+    remainders."""
+    spec = synth.config("par2d_64").with_(vol_shape=(258, 270), vol_spacing=(1.0, 1.0), det_shape=(nu,),
+                                          det_spacing=(du,), n_proj=107, angular_range=math.pi)
+    g = ph.from_spec(spec)
+    p = as_f32(np.random.default_rng(15).uniform(0.5, 1.5, (107, nu)))
+    say(f"[B 2D] one item, bins of {du}")
+    check(to_np(ph.backproject_par2d(g, ph.ray_vectors_2d(g), to_dev(p))), ora.backproject(spec, p), "B", tol=2e-5)
