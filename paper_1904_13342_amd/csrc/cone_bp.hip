@@ -760,17 +760,19 @@ hipError_t bp_cone(const Geom3D &g, const ConeBPView *views, const ConeBPView64 
 {
     if (!axial && !views64)
         return hipErrorInvalidValue;
-    // Bricks are worth their staging once there are two for each CU: circular
-    // views, 128^3 (256 bricks, 124 views) 470 us in bricks and 254 by waves,
-    // 176^3 (726 bricks, 133 views) 568 and 687 us.  General views spend their
-    // time in FP64 and are taken by waves at every size: 256^3, 124 views 2.47
-    // and 2.19 ms, 512^3, 30 views 4.29 and 4.25 ms.
+    // Bricks that do not fill the GPU take one time whatever their number, waves
+    // one in proportion to the voxels: circular views go in bricks once there are
+    // two for each CU, or about 2.8 million voxels (60 views, bricks and waves, us:
+    // 96^3 170 and 69, 136^3 189 and 164, 144^3 181 and 199, 160^3 192 and 253 with
+    // pixels of 1.3 voxels, 235 and 199, 240 and 256 for the last two with pixels
+    // of one).  General views spend their time in FP64 and are taken by waves at
+    // every size: 256^3, 124 views 2.47 and 2.19 ms, 512^3, 30 views 4.29 and 4.25.
     const long bricks = (long)((g.nx + 15) / 16) * ((g.ny + 15) / 16) * ((g.nz + nz_seg - 1) / nz_seg) * batch;
-    if (axial && bricks >= 512)
-        return nz_seg >= 32 ? bp_cone_nz<T, TI, 32>(g, views, proj, vol, batch, acc, s)
-                            : bp_cone_nz<T, TI, 16>(g, views, proj, vol, batch, acc, s);
     const int ntx = (g.nx + 7) / 8, nty = (g.ny + 7) / 8, ntz = (g.nz + WV_NZ - 1) / WV_NZ;
     const long tiles = (long)ntx * nty * ntz * batch;
+    if (axial && (bricks >= 512 || tiles >= 11000))
+        return nz_seg >= 32 ? bp_cone_nz<T, TI, 32>(g, views, proj, vol, batch, acc, s)
+                            : bp_cone_nz<T, TI, 16>(g, views, proj, vol, batch, acc, s);
     // at least 64 waves per CU in all, four views each
     int waves = 1;
     while (waves < 16 && tiles * waves < 16384 && 4 * waves <= g.n_proj)

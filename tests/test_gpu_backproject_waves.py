@@ -66,3 +66,16 @@ def test_waves_and_bricks_agree(ph):
     whole = ph.backproject_cone3d(g, mats, p)
     for b in range(3):
         check(to_np(ph.backproject_cone3d(g, mats, p[b].contiguous())), to_np(whole[b]), f"item {b}")
+
+
+@pytest.mark.parametrize("det_spacing", [(2.4, 2.3), (0.9, 0.8)])
+def test_bricks_by_voxels(ph, ora, det_spacing):
+    """Fewer than 512 bricks, but voxels enough that they beat the waves; columns
+    of 32 and of 16 voxels."""
+    vol, views = (150, 150, 139), 5
+    n = int(150 * 1.75 / det_spacing[1])
+    spec = BASE.with_(vol_shape=vol, det_shape=(n, n), det_spacing=det_spacing, n_proj=views, sid=700.0, sdd=1100.0)
+    g = ph.from_spec(spec)
+    p = as_f32(np.random.default_rng(6).uniform(0.5, 1.5, (views, n, n)))
+    say(f"[B bricks] {vol}, pixels {det_spacing}")
+    check(to_np(ph.backproject_cone3d(g, ph.projection_matrices_3d(g), to_dev(p))), ora.backproject(spec, p), "B")

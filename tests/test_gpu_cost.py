@@ -102,3 +102,21 @@ def test_backproject_2d_small_parallel(ph, n):
         us[beam] = _device_us(lambda: op(g, rv, p, out))
     say(f"[cost] B {n}^2, 360 views: {us}")
     assert us["par"] < 1.3 * us["fan"]
+
+
+def _cone(ph, n, views):
+    s = 256.0 / n
+    nu = int(1.75 * n / 1.3)
+    g = ph.geom3d((n, n, n), (s, s, s), (int(0.8 * nu), nu), (1.3 * s, 1.3 * s), views, 360 * DEG, 750.0, 1200.0)
+    return g, ph.projection_matrices_3d(g)
+
+
+def test_backproject_cone_between_waves_and_bricks(ph):
+    """160^3 costs no more than 176^3, which goes in bricks."""
+    us = {}
+    for n in (160, 176):
+        g, mats = _cone(ph, n, 60)
+        p = torch.rand((60,) + tuple(g.det_shape), device=gc.device())
+        us[n] = _us(lambda: ph.backproject_cone3d(g, mats, p))
+    say(f"[cost] B: {us}")
+    assert us[160] < 1.12 * us[176]
