@@ -18,6 +18,8 @@
 // along a column, and only the row coordinate moves with z: one FMA per voxel.
 // General matrices project every voxel in FP64; they, and volumes of few
 // bricks, are taken by single waves without staging (bp_cone_wave_kernel).
+#include <algorithm>
+
 #include "device_util.h"
 
 namespace ph {
@@ -817,15 +819,22 @@ hipError_t bpT_cone(const Geom3D &g, const ConeBPView *views, const ConeBPView64
     const int NZ = nz_seg >= 32 ? 32 : 16;
     const int nbx = (g.nx + 15) / 16, nby = (g.ny + 15) / 16, nzb = (g.nz + NZ - 1) / NZ;
     const long bricks = (long)nbx * nby * nzb * batch;
-    // Shares of the views, which have projections of their own: a small volume
-    // has few bricks, and a larger one a last round of workgroups that is
-    // partly empty.  Up to 8192 workgroups of at least six views: 61 x 64 x 67,
-    // 62 views: 300 -> 53 us; with the back-projection, 128^3, 124 views 1068 ->
-    // 825 us (B^T alone 377), 200^3, 193 views 3.26 -> 2.74 ms, 256^3, 248 views
-    // 6.97 -> 6.69 ms (4096 and 16384 workgroups: 2.80 and 2.81, 6.75 and 6.75).
-    long shares = bricks < 8192 ? 8192 / bricks : 1;
-    if (shares > g.n_proj / 6)
-        shares = g.n_proj / 6 > 1 ? g.n_proj / 6 : 1;
+    // Shares of the views, which have projections of their own.  A small volume
+    // has few bricks: up to about 1024 workgroups, which run together, of four
+    // views or more, or as many as a brick's loads then cost (61 x 64 x 67, 62
+    // views 246 -> 40 us; 128^3, 60 views 249, 157, 125, 148 and 174 us for 1, 2, 4, 6
+    // and 14 shares of 256 bricks; 160^3, 500 bricks, 1 and 2 shares: 24 views 146 and
+    // 140, 12 views 94 and 107).  Beyond, shares only even out the last rounds: of
+    // about 20 views, of 30 where there are several rounds anyway, up to 8192
+    // workgroups (190^3, 864 bricks: 57 views 441, 397, 413 and 704 us for 1, 2, 3 and
+    // 9, 200 views 1324, 1149, 1105 and 1128; 256^3, 2048 bricks, 100 views 1337, 1329,
+    // 1316 and 1357 for 1, 2, 3 and 5).
+    // General views cost a share's loads six times over: up to 4096 workgroups of
+    // six views (90 x 181 x 181, 35 views, 398 us in one, 346 in two, 301 in five).
+    const long n_views = g.n_proj;
+    const long fill = std::min(1024 / bricks, n_views / std::max(4L, bricks / 40));
+    const long even = std::min(8192 / bricks, n_views / (bricks < 1536 ? 19 : 28));
+    const long shares = std::max(axial ? std::max(fill, even) : std::min(4096 / bricks, n_views / 6), 1L);
     const dim3 grid((unsigned)bricks, (unsigned)shares);
     const TI *v = (const TI *)vol;
     if (NZ == 32) {

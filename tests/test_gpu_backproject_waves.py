@@ -79,3 +79,15 @@ def test_bricks_by_voxels(ph, ora, det_spacing):
     p = as_f32(np.random.default_rng(6).uniform(0.5, 1.5, (views, n, n)))
     say(f"[B bricks] {vol}, pixels {det_spacing}")
     check(to_np(ph.backproject_cone3d(g, ph.projection_matrices_3d(g), to_dev(p))), ora.backproject(spec, p), "B")
+
+
+@pytest.mark.parametrize("views", [9, 24, 25, 60])
+def test_backproject_adjoint_shares_of_large_volumes(ph, ora, views):
+    """B^T with one, two and three shares of a few hundred bricks."""
+    vol = (130, 140, 150)
+    spec = BASE.with_(vol_shape=vol, det_shape=(60, 70), det_spacing=(5.0, 5.0), n_proj=views, sid=700.0, sdd=1100.0)
+    g = ph.from_spec(spec)
+    f = as_f32(np.random.default_rng(7).uniform(0.5, 1.5, vol))
+    say(f"[B^T shares] {vol}, {views} views")
+    check(to_np(ph.backproject_adjoint_cone3d(g, ph.projection_matrices_3d(g), to_dev(f))),
+          ora.backproject_adjoint(spec, f), "B^T")

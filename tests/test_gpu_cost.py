@@ -111,6 +111,18 @@ def _cone(ph, n, views):
     return g, ph.projection_matrices_3d(g)
 
 
+def test_backproject_adjoint_cone_few_views(ph):
+    """A quarter of the views costs B^T well under half: they are not dealt into
+    shares of a handful of views."""
+    us = {}
+    x = torch.rand((190, 190, 190), device=gc.device())
+    for views in (60, 240):
+        g, mats = _cone(ph, 190, views)
+        us[views] = _us(lambda: ph.backproject_adjoint_cone3d(g, mats, x))
+    say(f"[cost] B^T 190^3: {us}")
+    assert us[60] < 0.42 * us[240]
+
+
 def test_backproject_cone_between_waves_and_bricks(ph):
     """160^3 costs no more than 176^3, which goes in bricks."""
     us = {}
