@@ -719,9 +719,10 @@ hipError_t bp2d_f(const Geom2D &g, const float2 *views, const void *sino, void *
     // from the near side of the image, fit 64 with the margins.  Items of a
     // batch go together as long as 256 workgroups are left (180 fan views of
     // 128^2: 20, 22 us for one and two together of 2 items, with the filter).
-    // Parallel views gain from the staging alone, once there are tiles for every
-    // CU and work to outweigh it (one item, us from memory and staged: 64^2, 90
-    // views 4.4 and 9.4, 168^2, 300 views 10 and 13, 256^2, 30, 90 and 180 views
+    // Parallel views gain from the staging alone, once there are tiles for most
+    // CUs and work to outweigh it (one item, us from memory and staged: 64^2, 90
+    // views 4.4 and 9.4, 168^2, 300 views 10 and 13, 200^2, 300 views 13.0 and 13.1,
+    // 236^2, 246 views 15.1 and 11.8 with the call, 256^2, 30, 90 and 180 views
     // 4.6 and 6.0, 9.2 and 9.6, 12.1 and 9.9, 320^2, 90 views 13.9 and 10.5, 512^2,
     // 30 and 300 views 9.5 and 6.7, 46.7 and 31.2); fan views, bound by the
     // arithmetic of their coordinates, only where two items or more share it
@@ -735,7 +736,7 @@ hipError_t bp2d_f(const Geom2D &g, const float2 *views, const void *sino, void *
     while (nb < 4 && nb < batch && pieces * ((batch + 2 * nb - 1) / (2 * nb)) >= 256)
         nb *= 2;
     const long work = pieces * batch;   // tiles
-    if (span <= 60.0f && (FAN || (work >= 256 && work * g.n_proj >= 30000))) {
+    if (span <= 60.0f && (FAN || (work >= 200 && work * g.n_proj >= 30000))) {
         if (nb == 4)
             return bp2d_seg_w<T, TI, FAN, 4>(span, g, views, sino, img, batch, s);
         if (nb == 2)
