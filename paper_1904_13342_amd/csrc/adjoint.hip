@@ -60,12 +60,18 @@ __device__ __forceinline__ float hat(float d)
     return r;
 }
 
-template <typename T, typename TI, bool FAN, int V, int NB>
+//
+// PX = 4: the wave's lanes hold a tile of 4 x 4 pixels four times over, each
+// sixteen with one of the four views that are set up together, and add up at
+// the end.  A small image then has four times the workgroups, of a quarter of
+// the chain; it sets up two and a half times the rays for each pixel.
+template <typename T, typename TI, bool FAN, int V, int NB, int PX>
 __global__ void __launch_bounds__(1024) fpT2d_kernel(Geom2D g, const float2 *__restrict__ views,
                                                      const TI *__restrict__ sino, T *__restrict__ img, int ntx,
                                                      int nty, int batch, unsigned tile0)
 {
     constexpr int L = 64 / V;   // lanes (and rays) per view
+    static_assert(PX == 8 || (PX == 4 && V == 4), "a view to each group of pixels");
     extern __shared__ __align__(16) char at_lds[];   // 64 rays per wave
     TileRay<NB> *s_rays = (TileRay<NB> *)at_lds;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -74,12 +80,12 @@ __global__ void __launch_bounds__(1024) fpT2d_kernel(Geom2D g, const float2 *__r
     const unsigned tile = tile0 + blockIdx.x;
     const int tx = (int)(tile % (unsigned)ntx), ty = (int)((tile / (unsigned)ntx) % (unsigned)nty);
     const int b0 = NB * (int)(tile / ((unsigned)ntx * (unsigned)nty));
-    const int ix = tx * 8 + (lane & 7), iy = ty * 8 + (lane >> 3);
+    const int ix = tx * PX + lane % PX, iy = ty * PX + lane / PX % PX;
     const float fx = (float)ix, fy = (float)iy;
     const float x = fmaf(fx, g.sx, g.ox), y = fmaf(fy, g.sy, g.oy);
     // this lane's corner of the tile's support (lane mod 4)
-    const float qx = fmaf((float)((lane & 1) ? min(tx * 8 + 8, g.nx) : tx * 8 - 1), g.sx, g.ox);
-    const float qy = fmaf((float)((lane & 2) ? min(ty * 8 + 8, g.ny) : ty * 8 - 1), g.sy, g.oy);
+    const float qx = fmaf((float)((lane & 1) ? min(tx * PX + PX, g.nx) : tx * PX - 1), g.sx, g.ox);
+    const float qy = fmaf((float)((lane & 2) ? min(ty * PX + PX, g.ny) : ty * PX - 1), g.sy, g.oy);
     const float margin = fmaf(1e-6f, (float)g.nu, 0.02f);   // rounding of the coordinates (bins)
     const size_t item = (size_t)g.n_proj * g.nu;
     float acc[NB];
@@ -117,11 +123,8 @@ __global__ void __launch_bounds__(1024) fpT2d_kernel(Geom2D g, const float2 *__r
             if (some == 0)
                 continue;
             wave_lds_fence();
-#pragma unroll 1
-            for (int v = 0; v < V && k0 + v < g.n_proj; ++v) {
-                const float2 c = views[k0 + v];
-                const int jv = __builtin_amdgcn_readlane(j_lo, v * L) + c0;   // bin of the view's first ray
-                const int je = min(__builtin_amdgcn_readlane(j_hi, v * L), jv + L - 1);
+            // the view's rays, in LDS from base + jv (bins jv .. je)
+            auto gather = [&](float2 c, int jv, int je, int base) {
                 // bins whose rays cross this pixel's support: its centre's
                 // coordinate and a bound on the support's half width (central
                 // projection of the box |dx| < sx, |dy| < sy; the fan angle
@@ -138,7 +141,7 @@ __global__ void __launch_bounds__(1024) fpT2d_kernel(Geom2D g, const float2 *__r
                 h = fmaf(h, g.ru, margin);
                 const int ja = (int)ceilf(fmaxf(fu + (t - h), (float)jv)), jb = (int)floorf(fminf(fu + (t + h), (float)je));
                 for (int j = ja; j <= jb; ++j) {
-                    const TileRay<NB> r = rays[v * L + j - jv];
+                    const TileRay<NB> r = rays[base + j];
                     // the samples inside the support; the clip only picks the
                     // range to visit (hardware reciprocals, widened), the
                     // weights decide every sample
@@ -158,8 +161,24 @@ __global__ void __launch_bounds__(1024) fpT2d_kernel(Geom2D g, const float2 *__r
                     for (int n = 0; n < NB; ++n)
                         acc[n] = fmaf(r.g[n], w, acc[n]);
                 }
+            };
+            if constexpr (PX == 8) {
+#pragma unroll 1
+                for (int v = 0; v < V && k0 + v < g.n_proj; ++v) {
+                    const int jv = __builtin_amdgcn_readlane(j_lo, v * L) + c0;   // bin of the view's first ray
+                    gather(views[k0 + v], jv, min(__builtin_amdgcn_readlane(j_hi, v * L), jv + L - 1), v * L - jv);
+                }
+            } else if (k0 + lane / L < g.n_proj) {
+                gather(cl, j_lo + c0, min(j_hi, j_lo + c0 + L - 1), lane / L * L - j_lo - c0);
             }
             wave_lds_fence();
+        }
+    }
+    if constexpr (PX == 4) {
+#pragma unroll
+        for (int n = 0; n < NB; ++n) {
+            acc[n] += __shfl_xor(acc[n], 16);
+            acc[n] += __shfl_xor(acc[n], 32);
         }
     }
     if (waves > 1) {
@@ -176,7 +195,7 @@ __global__ void __launch_bounds__(1024) fpT2d_kernel(Geom2D g, const float2 *__r
             for (int n = 0; n < NB; ++n)
                 acc[n] += part[n * blockDim.x + w * 64 + lane];
     }
-    if (ix < g.nx && iy < g.ny)
+    if (ix < g.nx && iy < g.ny && lane < PX * PX)
 #pragma unroll
         for (int n = 0; n < NB; ++n)
             if (b0 + n < batch)
@@ -864,10 +883,10 @@ __global__ void __launch_bounds__(1024) bpT2d_run_kernel(Geom2D g, const float2 
     }
 }
 
-template <typename T, typename TI, bool FAN, int V, int NB>
+template <typename T, typename TI, bool FAN, int V, int NB, int PX = 8>
 hipError_t fpT2d_n(const Geom2D &g, const float2 *views, const void *sino, void *img, int batch, hipStream_t s)
 {
-    const int ntx = (g.nx + 7) / 8, nty = (g.ny + 7) / 8;
+    const int ntx = (g.nx + PX - 1) / PX, nty = (g.ny + PX - 1) / PX;
     const long tiles = (long)ntx * nty * ((batch + NB - 1) / NB);
     // waves per tile: about 32 on every CU in all, at least V views each (a
     // small image's time is one wave's chain of views: 256^2 with 30 views, 15.0
@@ -878,7 +897,7 @@ hipError_t fpT2d_n(const Geom2D &g, const float2 *views, const void *sino, void 
     waves = waves < 16 ? waves : 16;
     const int threads = (int)(64 * waves);
     return launch_in_pieces(tiles, threads, [&](unsigned first, dim3 grid) {
-        hipLaunchKernelGGL((fpT2d_kernel<T, TI, FAN, V, NB>), grid, dim3(threads), threads * sizeof(TileRay<NB>), s, g,
+        hipLaunchKernelGGL((fpT2d_kernel<T, TI, FAN, V, NB, PX>), grid, dim3(threads), threads * sizeof(TileRay<NB>), s, g,
                            views, (const TI *)sino, (T *)img, ntx, nty, batch, first);
     });
 }
@@ -901,6 +920,14 @@ hipError_t fpT2d_v(const Geom2D &g, const float2 *views, const void *sino, void 
 template <typename T, typename TI, bool FAN>
 hipError_t fpT2d_f(const Geom2D &g, const float2 *views, const void *sino, void *img, int batch, hipStream_t s)
 {
+    // Tiles of 4 x 4 pixels where those of 8 x 8 leave half of the CUs without
+    // one: their waves are chains of views (one item, 200 parallel and fan views,
+    // us for tiles of eight and four: 32^2 22.5 and 9.9, 33.2 and 13.5; 64^2 22.2 and
+    // 10.9, 33.6 and 14.6; 80^2 22.3 and 15.1, 33.6 and 24.8; 96^2 22.3 and 20.4, 34.4
+    // and 36.5; three items of 48^2 23.8 and 15.6, 36.2 and 25.9, of 64^2 23.7 and
+    // 22.3, 35.8 and 41.1).
+    if ((long)((g.nx + 7) / 8) * ((g.ny + 7) / 8) * batch <= 128)
+        return fpT2d_n<T, TI, FAN, 4, 1, 4>(g, views, sino, img, batch, s);
     // Views set up together, so that the rays of an 8 x 8 tile's support at the
     // isocentre (its diagonal and three bins for the rounded-out ends) fill the
     // wave; a view that needs more lanes is set up in several passes.  512^2,

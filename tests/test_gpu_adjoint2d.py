@@ -146,3 +146,40 @@ def test_project_adjoint_2d_item_groups(ph, ora, name, items):
     out = aT(g, rv, to_dev(p))
     say(f"[A^T 2D, {items} items] {name}")
     check(to_np(out), np.stack([ora.project_adjoint(spec, v) for v in p]), name, tol=TOL_AT)
+
+
+@pytest.mark.parametrize("items", [1, 2, 3, 4, 5, 9])
+@pytest.mark.parametrize("kind,du,step", [("par2d", 0.7, 0.0), ("par2d", 0.31, 0.0), ("par2d", 2.2, 0.2),
+                                          ("fan2d", 1.1, 0.0), ("fan2d_curved", 0.6, 1.4)])
+def test_project_adjoint_2d_tiles_of_eight(ph, ora, kind, du, step, items):
+    """Images with enough tiles that the waves hold 8 x 8 pixels, items alone and
+    in groups of two, four and eight (the smaller images above have tiles of
+    4 x 4); footprints of one, two and more passes of rays."""
+    import numpy as np
+    src = dict(sid=160.0, sdd=256.0) if kind != "par2d" else {}
+    nu = int(135 * (1.7 if src else 1.0) / du)
+    spec = synth.config("par2d_64").with_(kind=kind, vol_shape=(90, 101), vol_spacing=(1.0, 1.0), det_shape=(nu,),
+                                          det_spacing=(du,), n_proj=7, angular_range=2 * math.pi, step_mm=step, **src)
+    g = ph.from_spec(spec)
+    p = as_f32(np.random.default_rng(17).standard_normal((items, 7, nu)))
+    aT = ph.project_adjoint_fan2d if src else ph.project_adjoint_par2d
+    say(f"[A^T 2D, {items} items] {kind} bins of {du}, step {step}")
+    out = to_np(aT(g, ph.ray_vectors_2d(g), to_dev(p)))
+    for n in {0, items // 2, items - 1}:
+        check(out[n], ora.project_adjoint(spec, p[n]), f"item {n}", tol=TOL_AT)
+
+
+@pytest.mark.parametrize("shape,items,views", [((3, 5), 1, 4), ((64, 61), 2, 13), ((88, 64), 1, 35), ((90, 96), 1, 35)])
+@pytest.mark.parametrize("du", [0.2, 1.0, 4.0])
+def test_project_adjoint_2d_tiles_of_four(ph, ora, shape, items, views, du):
+    """Small images, up to where tiles of 8 x 8 fill half of the GPU and one
+    beyond; views in numbers that are no multiple of the four of a wave."""
+    import numpy as np
+    nu = int(1.45 * max(shape) / du) + 2
+    spec = synth.config("par2d_64").with_(vol_shape=shape, vol_spacing=(1.0, 1.0), det_shape=(nu,), det_spacing=(du,),
+                                          n_proj=views, angular_range=math.pi)
+    g = ph.from_spec(spec)
+    p = as_f32(np.random.default_rng(18).standard_normal((items, views, nu)))
+    say(f"[A^T 2D] {shape} x {items}, bins of {du}")
+    out = to_np(ph.project_adjoint_par2d(g, ph.ray_vectors_2d(g), to_dev(p)))
+    check(out, np.stack([ora.project_adjoint(spec, v) for v in p]), "A^T", tol=TOL_AT)
