@@ -633,12 +633,15 @@ hipError_t fp2d_slab(const Geom2D &g, const float2 *views, const void *img, void
     const long blocks = (long)groups * g.n_proj * batch;
     // waves per 64 rays: about 64 on every CU in all (512^2, 360 fan views: 283,
     // 192, 161 and 160 us for 4096, 8192, 16384 and 32768 waves), at least
-    // three slabs each, and two workgroups or more to a CU's LDS (the widest
-    // slabs, 512^2 and 60, 120 and 170 fan views: 52, 88 and 120 us for the 16
-    // waves of one workgroup, 45, 72 and 90 for at most eight)
+    // three slabs each along the mean of the image's sides (125 x 37, 500 fan
+    // views: 37, 26 and 22 us by the shorter, the mean and the longer side; 430 x
+    // 129, 48 views 32 and 54 by the shorter and the longer), and two workgroups
+    // or more to a CU's LDS (the widest slabs, 512^2 and 60, 120 and 170 fan
+    // views: 52, 88 and 120 us for the 16 waves of one workgroup, 45, 72 and 90
+    // for at most eight)
     constexpr size_t slab = (size_t)SL_P * SW * sizeof(float);   // LDS of a wave
     int waves = 1;
-    while (waves < 16 && blocks * waves < 16384 && 2 * waves * 3 * SL_D <= (g.nx < g.ny ? g.nx : g.ny) &&
+    while (waves < 16 && blocks * waves < 16384 && 4 * waves * 3 * SL_D <= g.nx + g.ny &&
            2 * waves * slab <= SL_LDS)
         waves *= 2;
     return launch_in_pieces(blocks, 64 * waves, [&](unsigned first, dim3 grid) {
@@ -650,11 +653,15 @@ hipError_t fp2d_slab(const Geom2D &g, const float2 *views, const void *img, void
 template <typename T, bool FAN>
 hipError_t fp2d_f(const Geom2D &g, const float2 *views, const void *img, void *sino, int batch, hipStream_t s)
 {
-    // Slabs, once the waves' rays fill the GPU (256^2: 30 views, 180 waves of
-    // rays: 16 us direct, 20 in slabs; 120 views, 44 and 26 us; 8 items of 360
-    // views 853 and 324 us) and 64 of them fit a slab: the pixels they span
-    // along a plane of the walk, at most, are their spacing at the far side of
-    // the image, seen along the plane, and the plane's own advance and margins.
+    // Slabs, once the waves of rays fill the GPU with as many slabs each as the
+    // image is narrow (direct and in slabs, us: 256^2, 180 and 720 waves of rays, 16
+    // and 20, 44 and 26; 128^2, 520 and 1300 waves 19.7 and 19.0, 40 and 24; 64^2, 800
+    // and 1300 waves 16.7 and 17.2, 24.3 and 18.8; 512 x 64, 800 and 1300 waves 28 and
+    // 29, 39 and 35; 121 x 36, 1300 and 2500 waves 13.9 and 16.7, 21.9 and 21.0; below
+    // 32 pixels 89 x 26, 5000 waves 27 and 36) and 64 of them fit a slab: the
+    // pixels they span along a plane of the walk, at most, are their spacing at
+    // the far side of the image, seen along the plane, and the plane's own advance
+    // and margins.
     const float wx = g.nx * g.sx, wy = g.ny * g.sy;
     const float far = FAN ? (g.sid + 0.5f * sqrtf(wx * wx + wy * wy)) / g.ru : g.du;
     const float span = 63.0f * 1.4143f * far / fminf(g.sx, g.sy) + SL_D + 5.0f;
@@ -662,8 +669,10 @@ hipError_t fp2d_f(const Geom2D &g, const float2 *views, const void *img, void *s
     // lanes have one (256^2 and 40000 rays of 1, 9, 25, 33, 45, 65 and 96 bins: 51
     // us direct at all, in slabs 626, 88, 44, 36, 32, 41 and 40; 700^2: 87 direct,
     // 1700, 220, 140, 108, 91, 122 and 119).
-    const long groups = (g.nu + 63) / 64;
-    if (groups * g.n_proj * batch >= 512 && 2L * g.nu > 64 * groups && g.step <= fminf(g.sx, g.sy)) {
+    const long groups = (g.nu + 63) / 64, rays = groups * g.n_proj * batch;   // in waves
+    const int narrow = g.nx < g.ny ? g.nx : g.ny;
+    if (rays >= 512 && rays * narrow >= 64000 && narrow >= 32 && 2L * g.nu > 64 * groups &&
+        g.step <= fminf(g.sx, g.sy)) {
         if (span <= 104.0f)
             return fp2d_slab<T, FAN, 104>(g, views, img, sino, batch, s);
         if (span <= 168.0f)

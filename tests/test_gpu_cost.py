@@ -132,3 +132,34 @@ def test_backproject_cone_between_waves_and_bricks(ph):
         us[n] = _us(lambda: ph.backproject_cone3d(g, mats, p))
     say(f"[cost] B: {us}")
     assert us[160] < 1.12 * us[176]
+
+
+@pytest.mark.parametrize("beam", ["par", "fan"])
+def test_project_adjoint_2d_small_images(ph, beam):
+    """32^2 costs A^T well under what 128^2 does, with sixteen times the pixels:
+    its views are not one long chain to each of a few waves."""
+    src = dict(sid=750.0, sdd=1200.0) if beam == "fan" else {}
+    us = {}
+    for n in (32, 128):
+        g = ph.geom2d((n, n), (1.0, 1.0), 3 * n // 2, 1.0, 500, 360 * DEG, **src)
+        rv = ph.ray_vectors_2d(g)
+        p, out = torch.rand((500, 3 * n // 2), device=gc.device()), torch.empty((n, n), device=gc.device())
+        op = getattr(ph, f"project_adjoint_{beam}2d")
+        us[n] = _device_us(lambda: op(g, rv, p, out))
+    say(f"[cost] A^T, 500 {beam} views: {us}")
+    assert us[32] < 0.65 * us[128]
+
+
+@pytest.mark.parametrize("shape", [(1000, 30), (121, 36), (36, 121)])
+def test_project_2d_thin_images(ph, shape):
+    """A thin image costs A no more than a square one that is longer on its rays:
+    its few slabs across are not walked by one wave."""
+    us = {}
+    for s in (shape, (256, 256)):
+        nu = int(1.45 * max(s))
+        g = ph.geom2d(s, (1.0, 1.0), nu, 1.0, 2400 * 64 // nu, 360 * DEG)
+        rv = ph.ray_vectors_2d(g)
+        x, out = torch.rand(s, device=gc.device()), torch.empty((g.n_proj, nu), device=gc.device())
+        us[s] = _device_us(lambda: ph.project_par2d(g, rv, x, out))
+    say(f"[cost] A, 153600 rays: {us}")
+    assert us[shape] < 1.1 * us[(256, 256)]
