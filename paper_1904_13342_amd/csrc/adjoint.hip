@@ -235,8 +235,10 @@ __global__ void __launch_bounds__(1024) fpT2d_kernel(Geom2D g, const float2 *__r
 // 87 to 63 ms (2, 4, 8 and 16 starts, two of them walking backwards in the
 // first: 73, 66, 63, 66 ms); at 512^3 (one ray per voxel) there were few and
 // it gains 4%.  VALU and LDS are then busy 67 and 76% of the time.  512
-// threads and 1024 rays, so that a view's footprint is one pass, measured 61
-// ms against 63 for 256 threads and 640 rays, and 4.4 against 5.1 ms at 128^3.
+// threads and a table of 1024 rays, so that a view's footprint is one pass (two
+// workgroups fit a CU's LDS), measured 61 ms against 63 for 256 threads and 640
+// rays (three workgroups), and 4.4 against 5.1 ms at 128^3; coarse detectors
+// take the latter.
 //
 // Sample ranges come from a clip with hardware reciprocals (relative error
 // ~1e-7 of a few thousand steps), widened by 0.01 step or half a voxel: every
@@ -253,21 +255,17 @@ constexpr int AT_PY = AT_B + 3;                // row pitch (words)
 constexpr int AT_PZ = AT_PY * AT_PY;           // plane pitch (words)
 constexpr int AT_ZERO = AT_PZ + AT_PY + 1;     // word of cell (x0 - 1, y0 - 1, z0 - 1)
 constexpr int AT_CELLS = AT_ZERO + (AT_B + 3) * AT_PZ;
-constexpr int AT_T = 512;                      // threads
-constexpr int AT_RAYS = 1024;                  // footprint pixels per pass (ray-table capacity; with the
-                                               // accumulator, two workgroups fit a CU's LDS)
-constexpr int AT_Z = AT_B * AT_B * AT_B / AT_T;   // voxels per thread (a piece of a z-column)
-constexpr int AT_PER_THREAD = (AT_RAYS + AT_T - 1) / AT_T;
 constexpr int AT_BINS = 256;                   // sample-count bins of the ray sort
 constexpr float AT_FIX = 1073741824.0f;        // 2^30
 
-template <typename T, typename TI>
-__global__ void __launch_bounds__(AT_T, 4) fpT_cone_kernel(Geom3D g, const ConeFPView *__restrict__ fviews,
-                                                        const ConeBPView *__restrict__ bviews,
-                                                        const TI *__restrict__ proj, T *__restrict__ vol,
-                                                        double *__restrict__ part, int nbx, int nby, int nbz,
-                                                        unsigned brick0)
+template <typename T, typename TI, int AT_T, int AT_RAYS>
+__global__ void __launch_bounds__(AT_T, AT_T == 512 ? 4 : 3) fpT_cone_kernel(
+    Geom3D g, const ConeFPView *__restrict__ fviews, const ConeBPView *__restrict__ bviews,
+    const TI *__restrict__ proj, T *__restrict__ vol, double *__restrict__ part, int nbx, int nby, int nbz,
+    unsigned brick0)
 {
+    constexpr int AT_Z = AT_B * AT_B * AT_B / AT_T;   // voxels per thread (a piece of a z-column)
+    constexpr int AT_PER_THREAD = (AT_RAYS + AT_T - 1) / AT_T;
     __shared__ int acc[AT_CELLS];
     __shared__ float4 s_ra[AT_RAYS];   // biased anchor X, Y, Z and the ray's value
     __shared__ float4 s_rb[AT_RAYS];   // step e_x, e_y, e_z and the first sample (int bits)
@@ -503,11 +501,12 @@ __global__ void __launch_bounds__(AT_T, 4) fpT_cone_kernel(Geom3D g, const ConeF
 
 // Adds the shares' partial sums in order and writes the volume: one thread per
 // voxel of a brick, in the order the bricks' threads wrote them.
-template <typename T>
+template <typename T, int AT_T>
 __global__ void __launch_bounds__(256) fpT_cone_sum_kernel(Geom3D g, const double *__restrict__ part,
                                                            T *__restrict__ vol, int nbx, int nby, int nbz, int shares,
                                                            unsigned bricks)
 {
+    constexpr int AT_Z = AT_B * AT_B * AT_B / AT_T;
     const unsigned brick = blockIdx.x / (AT_B * AT_B * AT_B / 256);
     const int e = (int)(blockIdx.x % (AT_B * AT_B * AT_B / 256)) * 256 + threadIdx.x;
     const int z = e / AT_T, t = e % AT_T;
@@ -948,23 +947,40 @@ hipError_t fpT2d(bool fan, const Geom2D &g, const float2 *views, const void *sin
                : fpT2d_f<T, TI, false>(g, views, sino, img, batch, s);
 }
 
-template <typename T>
-hipError_t fpT_cone(const Geom3D &g, const ConeFPView *fviews, const ConeBPView *bviews, const void *proj, void *vol,
-                    int batch, double *part, int shares, hipStream_t s)
+template <typename T, int AT_T, int AT_RAYS>
+hipError_t fpT_cone_t(const Geom3D &g, const ConeFPView *fviews, const ConeBPView *bviews, const void *proj, void *vol,
+                      int batch, double *part, int shares, hipStream_t s)
 {
     const int nbx = (g.nx + AT_B - 1) / AT_B, nby = (g.ny + AT_B - 1) / AT_B, nbz = (g.nz + AT_B - 1) / AT_B;
     const long blocks = (long)nbx * nby * nbz * batch;
     // (shares only where there are few bricks: one piece)
     const hipError_t e = launch_in_pieces(blocks, AT_T, [&](unsigned first, dim3 grid) {
         grid.y = (unsigned)shares;
-        hipLaunchKernelGGL((fpT_cone_kernel<T, T>), grid, dim3(AT_T), 0, s, g, fviews, bviews, (const T *)proj, (T *)vol,
-                           shares > 1 ? part : nullptr, nbx, nby, nbz, first);
+        hipLaunchKernelGGL((fpT_cone_kernel<T, T, AT_T, AT_RAYS>), grid, dim3(AT_T), 0, s, g, fviews, bviews,
+                           (const T *)proj, (T *)vol, shares > 1 ? part : nullptr, nbx, nby, nbz, first);
     });
     if (e != hipSuccess || shares == 1)
         return e;
-    hipLaunchKernelGGL(fpT_cone_sum_kernel<T>, dim3((unsigned)blocks * (AT_B * AT_B * AT_B / 256)), dim3(256), 0, s, g,
-                       part, (T *)vol, nbx, nby, nbz, shares, (unsigned)blocks);
+    hipLaunchKernelGGL((fpT_cone_sum_kernel<T, AT_T>), dim3((unsigned)blocks * (AT_B * AT_B * AT_B / 256)), dim3(256), 0,
+                       s, g, part, (T *)vol, nbx, nby, nbz, shares, (unsigned)blocks);
     return hipGetLastError();
+}
+
+template <typename T>
+hipError_t fpT_cone(const Geom3D &g, const ConeFPView *fviews, const ConeBPView *bviews, const void *proj, void *vol,
+                    int batch, double *part, int shares, hipStream_t s)
+{
+    // A footprint (at the isocentre, with the corners' roundings) of few rays keeps
+    // few of 512 threads busy: 256^3, 40 views, ms with 512 and 256 threads for
+    // footprints of 1121, 700, 487, 333 and 174 rays 8.33 and 7.98, 4.85 and 5.13, 3.63
+    // and 3.29, 3.08 and 2.36, 2.76 and 1.84; 41^3, 60 views, us 196 and 216, 131 and
+    // 144, 91 and 128, 76 and 73, 71 and 66.
+    const float mag = g.sdd / g.sid;
+    const float rays = ((float)AT_B * sqrtf(g.sx * g.sx + g.sy * g.sy) * mag / g.du + 3.0f) *
+                       ((float)AT_B * g.sz * mag / g.dv + 3.0f);
+    if (rays <= 400.0f)
+        return fpT_cone_t<T, 256, 640>(g, fviews, bviews, proj, vol, batch, part, shares, s);
+    return fpT_cone_t<T, 512, 1024>(g, fviews, bviews, proj, vol, batch, part, shares, s);
 }
 
 }  // namespace

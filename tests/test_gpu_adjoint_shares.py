@@ -153,3 +153,19 @@ def test_project_adjoint_workspace_of_the_caller(ph, monkeypatch):
     monkeypatch.setattr(torch, "empty", none_left)
     one = ph.project_adjoint_cone3d(g, mats, p)
     assert (one - ref).abs().max() <= 2.0 ** -23 * ref.abs().max()
+
+
+@pytest.mark.parametrize("d", [3.0, 7.0, 40.0])
+@pytest.mark.parametrize("vol,views", [((16, 16, 16), 5), ((33, 20, 47), 30), ((40, 17, 16), 90)])
+def test_project_adjoint_coarse_detectors(ph, ora, vol, views, d):
+    """Pixels of several voxels: workgroups of 256 threads, with one share of the
+    views and with more; a footprint of a handful of rays."""
+    n = max(3, int(2.4 * max(vol) / d) | 1)   # odd: the central ray hits
+    spec = synth.config("cone3d_crop32").with_(vol_shape=vol, vol_spacing=(1.0, 1.0, 1.0), det_shape=(n, n + 2),
+                                               det_spacing=(d, d), n_proj=views, sid=300.0, sdd=500.0)
+    g = ph.from_spec(spec)
+    p = as_f32(np.random.default_rng(10).uniform(0.5, 1.5, (2, views, n, n + 2)))
+    say(f"[A^T coarse] {vol}, {views} views, pixels of {d}")
+    out = ph.project_adjoint_cone3d(g, ph.projection_matrices_3d(g), to_dev(p))
+    check(to_np(out), np.stack([ora.project_adjoint(spec, v) for v in p]), "A^T")
+    assert (ph.project_adjoint_cone3d(g, ph.projection_matrices_3d(g), to_dev(p)) == out).all()
