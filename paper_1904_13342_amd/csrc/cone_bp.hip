@@ -824,16 +824,17 @@ hipError_t bpT_cone(const Geom3D &g, const ConeBPView *views, const ConeBPView64
     // views or more, or as many as a brick's loads then cost (61 x 64 x 67, 62
     // views 246 -> 40 us; 128^3, 60 views 249, 157, 125, 148 and 174 us for 1, 2, 4, 6
     // and 14 shares of 256 bricks; 160^3, 500 bricks, 1 and 2 shares: 24 views 146 and
-    // 140, 12 views 94 and 107).  Beyond, shares only even out the last rounds: of
-    // about 20 views, of 30 where there are several rounds anyway, up to 8192
-    // workgroups (190^3, 864 bricks: 57 views 441, 397, 413 and 704 us for 1, 2, 3 and
-    // 9, 200 views 1324, 1149, 1105 and 1128; 256^3, 2048 bricks, 100 views 1337, 1329,
-    // 1316 and 1357 for 1, 2, 3 and 5).
+    // 140, 12 views 94 and 107).  Beyond, shares only even out the last rounds,
+    // which many views repay: of 24 or more, up to 8192 workgroups, from 96 views on
+    // (one share, the rule's number and nine: 190^3, 864 bricks, 100 views 713, 630
+    // and 760 us, 200 views 1324, 1098 and 1128; 59 x 295 x 295, 722 bricks, 100 views
+    // 585, 545 and 662; with 57 views two shares of these two are 397 for 441 and 371
+    // for 355; 256^3, 2048 bricks, 100 views 1337, 1320 and 1559).
     // General views cost a share's loads six times over: up to 4096 workgroups of
     // six views (90 x 181 x 181, 35 views, 398 us in one, 346 in two, 301 in five).
     const long n_views = g.n_proj;
     const long fill = std::min(1024 / bricks, n_views / std::max(4L, bricks / 40));
-    const long even = std::min(8192 / bricks, n_views / (bricks < 1536 ? 19 : 28));
+    const long even = n_views >= 96 ? std::min(8192 / bricks, n_views / 24) : 1;
     const long shares = std::max(axial ? std::max(fill, even) : std::min(4096 / bricks, n_views / 6), 1L);
     const dim3 grid((unsigned)bricks, (unsigned)shares);
     const TI *v = (const TI *)vol;
