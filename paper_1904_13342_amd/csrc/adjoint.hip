@@ -1090,15 +1090,15 @@ template <typename TI>
 hipError_t bpT2d(bool fan, const Geom2D &g, const float2 *views, const void *img, float *sino, int batch,
                  hipStream_t stream)
 {
-    // Runs, where a view per workgroup fills the GPU or the image is small
-    // (strips and runs, us: 256^2, 60, 120 and 180 parallel views 29 and 28, 30
-    // and 29, 46 and 28, fan views 25 and 34, 39 and 34, 50 and 34; 512^2, 180,
-    // 256 and 360 parallel views 131 and 153, 139 and 154, 245 and 196, arc views
-    // 219 and 246, 261 and 246, 385 and 294, with atan2f now 278 by strips, 274
-    // and 337 by runs; 128^2 and 64^2: runs no slower at
-    // any number) and the pixels of a run move by at least a quarter of a bin:
-    // the faster axis moves by 1 / sqrt(2) of a spacing on the detector, seen
-    // from the far side of the image.
+    // Runs, where a view to a workgroup fills the GPU, and the pixels of a run
+    // move by at least a quarter of a bin: the faster axis moves by 1 / sqrt(2) of a
+    // spacing on the detector, seen from the far side of the image.  The larger a
+    // view's work for its one workgroup (its pixels, in runs of whole waves), the
+    // more views it takes: 0.55 sqrt(pixels), and any number up to 128^2, where the
+    // sixteen waves have a few runs each.  Runs to strips break even at about (views
+    // of one item, parallel, flat and arc): 128^2 none, 160^2 70, 45 and 45 (rule 97),
+    // 256^2 60, 170 and 170 (141), 320^2 80, 185 and 140 (176), 512^2 230, 400 and 230
+    // (282), 700^2 400, 450 and 256 (386).
     const float wx = g.nx * g.sx, wy = g.ny * g.sy;
     const float rate = 0.7071f * fminf(g.sx, g.sy) * (fan ? g.ru / (g.sid + 0.5f * sqrtf(wx * wx + wy * wy)) : g.ru);
     const int P = rate >= 1.0f ? 1 : rate >= 0.5f ? 2 : rate >= 0.3334f ? 3 : rate >= 0.25f ? 4 : 0;
@@ -1109,8 +1109,8 @@ hipError_t bpT2d(bool fan, const Geom2D &g, const float2 *views, const void *img
     // 360 of 8: 43, 76 and 200 us alone, 52, 75 and 155 by twos; 512^2, 360 fan
     // views of 1020 bins, four waves to a workgroup: 382 and 452).
     const int nb = batch > 1 && 16 * bins <= RUN_LDS && (long)g.n_proj * ((batch + 1) / 2) >= 512 ? 2 : 1;
-    const long pixels = (long)g.nx * g.ny, least = pixels <= 128 * 128 ? 1 : pixels <= 256 * 256 ? 96 : 256;
-    if (P > 0 && bins <= RUN_LDS && items >= least) {
+    const float pixels = 32.0f * ((float)((g.nx + 63) / 64) * g.ny + (float)((g.ny + 63) / 64) * g.nx);
+    if (P > 0 && bins <= RUN_LDS && (pixels <= 16384.0f || (float)items >= 0.55f * sqrtf(pixels))) {
         switch (P) {
         case 1: return bpT2d_run_p<TI, 1>(nb, fan, g, views, img, sino, batch, stream);
         case 2: return bpT2d_run_p<TI, 2>(nb, fan, g, views, img, sino, batch, stream);
