@@ -148,7 +148,7 @@ __global__ void __launch_bounds__(1024) fpT2d_kernel(Geom2D g, const float2 *__r
                     const float cx = (fx - r.X0) * r.rX, cy = (fy - r.Y0) * r.rY;
                     const float lo = fmaxf(cx - fabsf(r.rX), cy - fabsf(r.rY));
                     const float hi = fminf(cx + fabsf(r.rX), cy + fabsf(r.rY));
-                    if (!(lo < hi + 0.02f))
+                    if (!(lo < hi + 0.01f))
                         continue;
                     float w = 0.0f;
                     const int m1 = (int)floorf(hi + 0.02f);

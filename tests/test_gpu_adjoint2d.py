@@ -183,3 +183,38 @@ def test_project_adjoint_2d_tiles_of_four(ph, ora, shape, items, views, du):
     say(f"[A^T 2D] {shape} x {items}, bins of {du}")
     out = to_np(ph.project_adjoint_par2d(g, ph.ray_vectors_2d(g), to_dev(p)))
     check(out, np.stack([ora.project_adjoint(spec, v) for v in p]), "A^T", tol=TOL_AT)
+
+
+@pytest.mark.parametrize("n", [64, 120])
+def test_project_adjoint_2d_not_a_number(ph, n):
+    """A ray that is not a number spoils the pixels whose support it crosses, and
+    those it misses by a hundredth of a step at most (the clip's tolerance), in
+    its own item alone."""
+    import numpy as np
+    import torch
+    views, nu, items = 90, 3 * n // 2, 160
+    g = ph.geom2d((n, n), (1.0, 1.0), nu, 1.0, views, math.pi)
+    rv = ph.ray_vectors_2d(g)
+    p = torch.ones((items, views, nu), device=gc.device())
+    at = [((7 * i) % views, (13 * i + 5) % nu) for i in range(items)]
+    for i, (k, j) in enumerate(at):
+        p[i, k, j] = float("nan")
+    bad = torch.isnan(ph.project_adjoint_par2d(g, rv, p)).cpu().numpy()
+    ix = np.arange(n, dtype=np.float64)
+    step, total = 0.5, 0
+    for i, (k, j) in enumerate(at):
+        c = rv[k].astype(np.float64) / np.linalg.norm(rv[k].astype(np.float64))
+        u = j - 0.5 * (nu - 1)
+        X0, Y0 = -u * c[1] + 0.5 * (n - 1), u * c[0] + 0.5 * (n - 1)
+        eX, eY = step * c[0], step * c[1]
+        # steps at which the ray enters and leaves a pixel's support, per axis
+        with np.errstate(divide="ignore", invalid="ignore"):
+            tx = np.sort(np.stack([(ix - 1 - X0) / eX, (ix + 1 - X0) / eX]), axis=0)
+            ty = np.sort(np.stack([(ix - 1 - Y0) / eY, (ix + 1 - Y0) / eY]), axis=0)
+        gap = np.maximum(tx[0][None, :], ty[0][:, None]) - np.minimum(tx[1][None, :], ty[1][:, None])
+        if min(abs(eX), abs(eY)) < 1e-6:
+            continue
+        assert not bad[i][gap > 0.0105].any(), (i, k, j)
+        assert bad[i][gap < -1.0].all(), (i, k, j)   # a whole step inside
+        total += bad[i].sum()
+    assert total > 0
