@@ -30,7 +30,8 @@ if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
 # MI355X figures: 256 CUs at 2.4 GHz, 64 FP32 lanes per CU per clock without
-# packed math; HBM3E 8 TB/s.
+# packed math (the nominal rate: FMAs alone have been measured at 1.15 times it,
+# adds and multiplies at 1.6, conversions at 0.9); HBM3E 8 TB/s.
 PEAK_VALU_TOPS = 256 * 64 * 2.4e9 / 1e12   # 39.3 T lane-ops/s
 PEAK_HBM_GBS = 8000.0
 # Algorithmic lane-ops per unit of work: the operations the interpolation itself needs.
@@ -38,22 +39,22 @@ OPS_PER_UPDATE = 11.0      # back-projection: v coordinate, floor/fract, 3 lerps
 OPS_PER_SAMPLE = 26.0      # forward projection: 3 coordinates, 3 floor/fract, 7 lerps, accumulate
 
 # HBM bytes per launch at 512^3 from rocprofv3 --pmc FETCH_SIZE and WRITE_SIZE (KiB per dispatch), each scaled by
-# what the same counter reads for a plain 1 GiB device-to-device copy (FETCH_SIZE 524315 KiB, WRITE_SIZE 1048576 KiB).
+# what the same counter reads for a plain 1 GiB device-to-device copy (FETCH_SIZE 524316 KiB, WRITE_SIZE 1048576 KiB).
 # A record holds for the kernel's device sources it was taken on (hash below); after any change to them the traffic
 # is reported as null.
 COPY_BYTES = 1 << 30
-COPY_FETCH_KIB, COPY_WRITE_KIB = 524315.0, 1048576.0
+COPY_FETCH_KIB, COPY_WRITE_KIB = 524316.0, 1048576.0
 MEASURED_TRAFFIC = {
-    "fp_cone": {"fetch_kib": 6.03206e+07, "write_kib": 1.23984e+06,
-             "sources": ('cone_fp.hip', 'device_util.h'), "sha256_16": "808e4cbb11aadcc2"},
-    "bp_cone": {"fetch_kib": 9.02833e+06, "write_kib": 524288,
-             "sources": ('cone_bp.hip', 'device_util.h'), "sha256_16": "3e9a44094c708c39"},
-    "weight_filter": {"fetch_kib": 563476, "write_kib": 1.10592e+06,
+    "fp_cone": {"fetch_kib": 6.02869e+07, "write_kib": 1.23982e+06,
+             "sources": ('cone_fp.hip', 'device_util.h', 'fp64.h'), "sha256_16": "c597947bc7257cb7"},
+    "bp_cone": {"fetch_kib": 9.0657e+06, "write_kib": 524288,
+             "sources": ('cone_bp.hip', 'device_util.h', 'fp64.h'), "sha256_16": "f769d6b9f48c6b71"},
+    "weight_filter": {"fetch_kib": 563615, "write_kib": 1.10592e+06,
                    "sources": ('filter.hip', 'fft.h'), "sha256_16": "89a6c98d7d5f61cc"},
-    "fpT_cone": {"fetch_kib": 1.02448e+07, "write_kib": 524288,
-              "sources": ('adjoint.hip', 'device_util.h'), "sha256_16": "682c708c236ba2ff"},
-    "bpT_cone": {"fetch_kib": 2.74625e+06, "write_kib": 2.27029e+07,
-              "sources": ('cone_bp.hip', 'device_util.h'), "sha256_16": "3e9a44094c708c39"},
+    "fpT_cone": {"fetch_kib": 1.01273e+07, "write_kib": 524288,
+              "sources": ('adjoint.hip', 'device_util.h', 'fp64.h', 'ranges.h'), "sha256_16": "0645a2ad69a705c8"},
+    "bpT_cone": {"fetch_kib": 2.74575e+06, "write_kib": 2.27029e+07,
+              "sources": ('cone_bp.hip', 'device_util.h', 'fp64.h'), "sha256_16": "f769d6b9f48c6b71"},
 }
 
 

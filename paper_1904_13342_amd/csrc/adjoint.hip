@@ -31,11 +31,12 @@ namespace {
 // values; then every lane gathers over the two or three rays that cross its own
 // pixel's support, clipping each to it.  Setting the ray up in every pixel
 // instead is what the time went to: 3.19 ms for 512^2 and 360 fan views of 725
-// bins, against 0.59 ms (0.80 ms setting up one view at a time); 256^2 with 30
-// parallel views of 363 bins went from 46 to 16 us.  VALU-bound, and the weights
-// are the same for every item of a batch: another item costs one operation a
-// ray.  Rays that are zero in every item add nothing: a wave passes over its
-// chunk of views where all are (360 views of zeros, or of one value: 76 us).
+// bins, against 0.57 ms (0.80 ms setting up one view at a time); 256^2 with 30
+// parallel views of 363 bins went from 46 to 15 us.  VALU-bound (1.06
+// instructions a clock and CU at 512^2, 3% of them FP64), and the weights are the
+// same for every item of a batch: another item costs one operation a ray.  Rays
+// that are zero in every item add nothing: a wave passes over its chunk of views
+// where all are (360 views of zeros, or of one value: 76 us).
 // The W waves of a workgroup share a tile, wave w taking views w, w + W,
 // ..., and meet in LDS in a fixed order.
 template <int NB>
@@ -751,7 +752,8 @@ __device__ __forceinline__ int prev_lane(int x, int end)
 // ones are read by wide loads, so that each line is touched twice and not once
 // a run.  8 x 256^2, 360 parallel views: 252 us with four loads of a pixel
 // each, 211 with one of four, 200 with two for eight runs and 150 with two items
-// together, then bound by about 35 vector operations for each run and item.
+// together, then bound by about 31 vector operations for each pixel and item (0.9
+// a clock and CU).
 constexpr int RUN_COLS = 8;          // runs whose pixels are loaded together
 constexpr size_t RUN_LDS = 65536;    // LDS of a workgroup, at most
 

@@ -313,7 +313,7 @@ __global__ void __launch_bounds__(256) bp_cone_kernel(Geom3D g, const ConeBPView
 // pairs at 32-bit offsets from the view; elsewhere pixel by pixel, masked.
 // Bound by the scattered loads for circular views (256^3: 36 lane slots per
 // update, against 13 in bricks) and by FP64 for general ones.  32^3, 200
-// views: 637 us in bricks, 24 by waves; 64^3, 62 views 206 and 23 us; four
+// views: 637 us in bricks, 24 by waves; 64^3, 62 views 262 and 28 us; four
 // voxels per column against two and eight: 24, 20 and 43 us at 32^3, 2.19, 2.25
 // and 2.68 ms at 256^3 with 124 general views.
 constexpr int WV_NZ = 4;

@@ -118,8 +118,9 @@ __global__ void __launch_bounds__(256) fp2d_kernel(Geom2D g, const float2 *__res
 // line for every few lanes.  The W waves of a workgroup share the rays, each
 // taking a run of slabs, and meet in LDS in a fixed order.
 // Positions and interpolation are those of the direct kernel bit for bit.
-// 512^2, 360 fan views of 725 bins: 0.32 -> 0.16 ms (1.0 Tsamples/s; about 40
-// lane slots per sample, VALU-bound).
+// 512^2, 360 fan views of 725 bins: 0.32 -> 0.17 ms (0.9 Tsamples/s).  34 lane
+// operations a sample, 0.76 instructions a clock and CU; bank conflicts of the
+// reads keep the LDS for another quarter of the time.
 constexpr int SL_D = 7;          // planes a slab advances
 constexpr int SL_P = SL_D + 1;   // planes it holds
 constexpr size_t SL_LDS = 65536;   // LDS of a workgroup, at most
@@ -375,9 +376,10 @@ __global__ void __launch_bounds__(1024) fp2d_slab_kernel(Geom2D g, const float2 
 // where both bins of all four lie on the detector for the whole wave, each
 // pair is one load, otherwise two masked ones.  (With the lanes of a wave on 4
 // views of 16 pixels: 174 against 112 us for 8 x 256^2 and 360 parallel views.)
-// Taken for single items of fan views, bound by some 38 vector operations for
-// each sample's coordinate (512^2, 360 arc views: 81 us, 1.1 a clock on every
-// CU), and for bins too fine to stage, below.
+// Taken for single items of fan views, bound by the vector operations for each
+// sample's coordinate, an atan2f on long arcs (512^2, 360 arc views of 725 bins: 53
+// operations a sample in all, 1.1 a clock on every CU, 112 us), and for bins too
+// fine to stage, below.
 template <typename T, typename TI, bool FAN>
 __global__ void __launch_bounds__(1024) bp2d_kernel(Geom2D g, const float2 *__restrict__ views,
                                                     const TI *__restrict__ sino, T *__restrict__ img, int ntx, int nty,
@@ -451,8 +453,8 @@ __global__ void __launch_bounds__(1024) bp2d_kernel(Geom2D g, const float2 *__re
 // workgroup share a tile and meet in LDS in a fixed order.  Reading pairs from
 // memory cost about 25 clocks of a CU for each wave's sample; staged, it is 15
 // vector operations, of which an item's own are three (8 x 256^2, 360 parallel
-// views: 122 us from memory, 88 staged one item at a time, 61 and 45 two and
-// four).
+// views, with the launch: 122 us from memory, 88 staged one item at a time, 61 and
+// 45 two and four, of which the kernel is 40).
 constexpr int SB_BINS = 512;   // views times bins of a chunk
 
 template <typename T, typename TI, bool FAN, int NB, int W>
